@@ -108,7 +108,8 @@ csk_status csk_sketch_update(csk_sketch *s, const float *pos, uint64_t n, double
 csk_status csk_sketch_update_noalloc(csk_sketch *s, const float *pos, uint64_t n, double delta, double L,
                                      void *stream);
 
-#define CSK_UPDATE_AUTO   0 /* LDS-binned when the rows fit it, else global atomics  */
+#define CSK_UPDATE_AUTO   0 /* LDS-binned when the rows fit it, else global atomics; a
+                               short stream takes the atomics whatever the rows      */
 #define CSK_UPDATE_BINNED 1 /* LDS-binned tokens, summed per counter slice          */
 #define CSK_UPDATE_DIRECT 2 /* one global atomic add per row and particle           */
 
@@ -118,8 +119,8 @@ csk_status csk_sketch_update_noalloc(csk_sketch *s, const float *pos, uint64_t n
  * for the binned path behaves as CSK_UPDATE_AUTO. */
 csk_status csk_set_update_plan(csk_sketch *s, int32_t mode, uint32_t max_wg);
 
-#define CSK_BIN_AUTO      0 /* the sort-word kernel where it applies and is the faster, else
-                               the general one */
+#define CSK_BIN_AUTO      0 /* the append kernel where its buffers fit LDS (d <= 8, single
+                               cells), else the sort-word or the general one */
 #define CSK_BIN_GENERAL   1 /* row-interleaved hashing, bucket and sign taken apart per row */
 #define CSK_BIN_SORT_WORD 2 /* tokens counting-sorted by their LDS sort words; d = 5..8,
                                w <= 2^24, a mesh that is neither grouped nor packed (else:

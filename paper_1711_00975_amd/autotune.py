@@ -6,7 +6,8 @@ update add the same +-1s, Sec. 2.2 Add), so tuning only chooses speed.  The axes
 * where the increments are privatised: LDS tiles of 2^15 counters fed by a token
   partition (the binned update), or nowhere (one device-scope atomic per row and
   particle: fastest for short streams into narrow rows);
-* for the binned update, the bin kernel's form and tiling: the general row-interleaved
+* for the binned update, the bin kernel's form and tiling: the automatic choice (the append
+  kernel where it applies), the general row-interleaved
   kernel with a cap of 64..256 workgroups, or the sort-word kernel with 1024 threads and
   2 or 3 rows per LDS pass, or 512 threads with the next tile's positions prefetched;
 * per batch shape: the bin kernel form and the number of bin workgroups shared out
@@ -35,6 +36,7 @@ def _plan(mode, max_wg=0, form=CSK_BIN_AUTO, threads=0, rows=0, prefetch=0):
 
 UPDATE_CANDIDATES = [
     _plan(CSK_UPDATE_DIRECT),
+    _plan(CSK_UPDATE_BINNED),
     _plan(CSK_UPDATE_BINNED, 64, CSK_BIN_GENERAL),
     _plan(CSK_UPDATE_BINNED, 128, CSK_BIN_GENERAL),
     _plan(CSK_UPDATE_BINNED, 256, CSK_BIN_GENERAL),
@@ -43,7 +45,8 @@ UPDATE_CANDIDATES = [
     _plan(CSK_UPDATE_BINNED, 256, CSK_BIN_SORT_WORD, 512, 3, 2),
 ]
 BATCH_BUDGETS = [256, 512, 1024, 2048]
-BATCH_FORMS = [_plan(CSK_UPDATE_BINNED, 0, CSK_BIN_GENERAL), _plan(CSK_UPDATE_BINNED, 0, CSK_BIN_SORT_WORD, 1024, 3, 1)]
+BATCH_FORMS = [_plan(CSK_UPDATE_BINNED), _plan(CSK_UPDATE_BINNED, 0, CSK_BIN_GENERAL),
+               _plan(CSK_UPDATE_BINNED, 0, CSK_BIN_SORT_WORD, 1024, 3, 1)]
 
 
 def plan_key(p: dict) -> str:

@@ -208,10 +208,8 @@ struct csk_sketch {
   uint64_t* sel_key = nullptr;
   int32_t* sel_est = nullptr;
   uint32_t sel_cap = 0;
-  uint16_t* tok = nullptr;
-  uint64_t tok_bytes = 0;
-  uint32_t* cnt = nullptr;
-  uint64_t cnt_bytes = 0;
+  uint8_t* scr = nullptr;     // scratch of an update: token regions, their counts, partial slices
+  uint64_t scr_bytes = 0;
   SelState* host_sel = nullptr;   // pinned
   uint32_t* host_ctl = nullptr;   // pinned
   bool mesh_set = false;
@@ -256,7 +254,7 @@ hipError_t dmalloc(csk_sketch* s, T** p, uint64_t count) {
 
 void free_all(csk_sketch* s) {
   void* ptrs[] = {s->M, s->tab, s->tabi, s->tabp, s->tabs, s->tabq, s->fcols, s->filter, s->hot_table, s->set, s->ctl, s->sel, s->cand_key, s->cand_est, s->sel_key, s->sel_est,
-                  s->tok, s->cnt};
+                  s->scr};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (s->host_sel) (void)hipHostFree(s->host_sel);
@@ -278,6 +276,9 @@ void classify_mesh(Mesh* out, long long G, double L) {
   out->R = (double)G / L;
   out->Rf = (float)out->R;
   out->twoLf = (float)(2.0 * L);
+  float below = (float)L;
+  if ((double)below > L) below = std::nextafterf(below, 0.0f);
+  memcpy(&out->Lbits, &below, sizeof(below));
   if (std::fma(out->R, L, -(double)G) == 0.0 && std::isfinite(out->R) && out->R > 0.0) {
     int ex;
     const double mant = std::frexp(out->R, &ex);       // R = mant * 2^ex, mant in [0.5, 1)
@@ -477,32 +478,32 @@ namespace {
 // The update of a float (x, y, z) stream, or of a packed stream (src = 64-bit words).
 // noalloc: tokens go to the device's static scratch, never to memory allocated here;
 // a stream whose bin plan does not fit it is refused before anything runs.
-// The handle's token and count scratch grown to what the plan needs (a growth synchronizes
-// the stream first: earlier work may still read the old buffers).
-hipError_t ensure_update_scratch(csk_sketch* s, const BinPlan& plan, hipStream_t st) {
-  const uint64_t tok_need = (uint64_t)plan.P * plan.nwg * plan.cap * sizeof(uint16_t);
-  const uint64_t cnt_need = (uint64_t)plan.P * plan.nwg * sizeof(uint32_t);
-  if (tok_need <= s->tok_bytes && cnt_need <= s->cnt_bytes) return hipSuccess;
-  hipError_t e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return e;
-  if (tok_need > s->tok_bytes) {
-    if (s->tok) (void)hipFree(s->tok);
-    s->bytes -= s->tok_bytes;
-    s->tok = nullptr;
-    s->tok_bytes = 0;
-    e = dmalloc(s, &s->tok, tok_need / sizeof(uint16_t));
+// The handle's scratch for one update, grown to what the plan needs (a growth synchronizes the
+// stream first: earlier work may still read the old buffer).
+struct UpdateScratch {
+  uint16_t* tok;    // token regions
+  uint32_t* cnt;    // their counts
+  int32_t* part;    // partial slices of a split accumulate
+};
+hipError_t ensure_update_scratch(csk_sketch* s, const BinPlan& plan, uint32_t split, hipStream_t st,
+                                 UpdateScratch* u) {
+  const uint64_t cnt_at = ((uint64_t)plan.P * plan.nwg * plan.cap * sizeof(uint16_t) + 255) & ~255ull;
+  const uint64_t part_at = (cnt_at + (uint64_t)plan.P * plan.nwg * sizeof(uint32_t) + 255) & ~255ull;
+  const uint64_t need = part_at + accumulate_part_bytes(plan, split);
+  if (need > s->scr_bytes) {
+    hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
-    s->tok_bytes = tok_need;
-  }
-  if (cnt_need > s->cnt_bytes) {
-    if (s->cnt) (void)hipFree(s->cnt);
-    s->bytes -= s->cnt_bytes;
-    s->cnt = nullptr;
-    s->cnt_bytes = 0;
-    e = dmalloc(s, &s->cnt, cnt_need / sizeof(uint32_t));
+    if (s->scr) (void)hipFree(s->scr);
+    s->bytes -= s->scr_bytes;
+    s->scr = nullptr;
+    s->scr_bytes = 0;
+    e = dmalloc(s, &s->scr, need);
     if (e != hipSuccess) return e;
-    s->cnt_bytes = cnt_need;
+    s->scr_bytes = need;
   }
+  u->tok = (uint16_t*)s->scr;
+  u->cnt = (uint32_t*)(s->scr + cnt_at);
+  u->part = (int32_t*)(s->scr + part_at);
   return hipSuccess;
 }
 
@@ -550,7 +551,7 @@ csk_status update_impl(csk_sketch* s, const void* src, bool packed, uint64_t n, 
     uint16_t* tok = (uint16_t*)base;
     uint32_t* cnt = (uint32_t*)(base + tok_need);
     CSK_HIP(launch_bin((const float*)src, n, mesh, t, plan, tok, cnt, s->M, s->err(), st), "update_noalloc (bin)");
-    CSK_HIP(launch_accumulate(tok, cnt, plan, s->w, s->M, st), "update_noalloc (accumulate)");
+    CSK_HIP(launch_accumulate(tok, cnt, plan, s->w, s->M, 1, nullptr, st), "update_noalloc (accumulate)");
     return CSK_OK;
   }
   latch_mesh(s, delta, L, mesh);
@@ -562,14 +563,22 @@ csk_status update_impl(csk_sketch* s, const void* src, bool packed, uint64_t n, 
     const float* p = packed ? (const float*)((const uint64_t*)src + off) : (const float*)src + 3 * off;
     BinPlan plan;
     const uint64_t max_wg = bin_wg_cap(s->d, s->upd_max_wg);
-    if (s->upd_mode == CSK_UPDATE_DIRECT || !plan_bin_wg(m, s->d, s->w, max_wg, plan)) {
+    // Short streams: the direct update takes 8 us or 37 ps per particle and row (2.7e10 atomics
+    // per second), the binned one about 22 us and the read-modify-write of all the counters
+    // (150 us at w = 2^24, d = 5); both measured from 2^12 to 2^20 particles.
+    const bool brief = s->upd_mode == CSK_UPDATE_AUTO && s->upd_form == kFormAuto && m <= kShortStream &&
+                       m * s->d <= (1ull << 19) + (uint64_t)s->d * s->w / 21u;
+    if (brief || s->upd_mode == CSK_UPDATE_DIRECT || !plan_bin_wg(m, s->d, s->w, max_wg, plan)) {
       CSK_HIP(launch_update_direct(p, m, mesh, t, s->M, s->err(), st), "update (direct)");
       continue;
     }
-    (void)plan_sortbin(plan, s->d, mesh, t, s->upd_form, s->upd_nt, s->upd_rp, s->upd_pf, true);
-    CSK_HIP(ensure_update_scratch(s, plan, st), "update: token scratch");
-    CSK_HIP(launch_bin(p, m, mesh, t, plan, s->tok, s->cnt, s->M, s->err(), st), "update (bin)");
-    CSK_HIP(launch_accumulate(s->tok, s->cnt, plan, s->w, s->M, st), "update (accumulate)");
+    if (s->upd_form != kFormAuto || !plan_append(plan, m, s->d, s->w, s->upd_max_wg, mesh, t, false))
+      (void)plan_sortbin(plan, s->d, mesh, t, s->upd_form, s->upd_nt, s->upd_rp, s->upd_pf, true);
+    const uint32_t split = accumulate_split(plan, m, s->d);
+    UpdateScratch u;
+    CSK_HIP(ensure_update_scratch(s, plan, split, st, &u), "update: token scratch");
+    CSK_HIP(launch_bin(p, m, mesh, t, plan, u.tok, u.cnt, s->M, s->err(), st), "update (bin)");
+    CSK_HIP(launch_accumulate(u.tok, u.cnt, plan, s->w, s->M, split, u.part, st), "update (accumulate)");
   }
   return CSK_OK;
 }
@@ -945,11 +954,31 @@ csk_status batch_create_impl(csk_batch** out, csk_sketch* const* sketches, const
   uint64_t tok_words = 0, cnt_words = 0, lds = 0;
   std::vector<uint64_t> tok_off(count), cnt_off(count);
   std::vector<BinPlan> plans(count);
+  // the append kernel serves the batch when it serves every sketch in the same form (and unless
+  // the first sketch's tiling asks for another)
+  uint32_t kb = 4;
   for (uint32_t i = 0; i < count; ++i) {
-    uint64_t want = total_tiles ? (budget * tiles[i] + total_tiles / 2) / total_tiles : 1;
-    if (want < 1) want = 1;
+    Mesh m;
+    (void)check_mesh(sketches[i], delta[i], L[i], &m);
+    if (m.nch > kb) kb = m.nch;
+  }
+  auto share = [&](uint32_t i) {
+    const uint64_t want = total_tiles ? (budget * tiles[i] + total_tiles / 2) / total_tiles : 1;
+    return want < 1 ? (uint64_t)1 : want;
+  };
+  bool append_all = s0->upd_form == kFormAuto;
+  for (uint32_t i = 0; i < count && append_all; ++i) {
+    Mesh m;
+    (void)check_mesh(sketches[i], delta[i], L[i], &m);
     BinPlan& p = plans[i];
-    if (!plan_bin_wg(max_n[i] ? max_n[i] : 1, d, sketches[i]->w, want, p) || !p.fast)
+    append_all = plan_bin_wg(max_n[i] ? max_n[i] : 1, d, sketches[i]->w, share(i), p) &&
+                 plan_append(p, max_n[i] ? max_n[i] : 1, d, sketches[i]->w, (uint32_t)share(i), m,
+                             sketches[i]->tables(), false, kb) &&
+                 !p.hold && p.sort == plans[0].sort;
+  }
+  for (uint32_t i = 0; i < count; ++i) {
+    BinPlan& p = plans[i];
+    if (!append_all && (!plan_bin_wg(max_n[i] ? max_n[i] : 1, d, sketches[i]->w, share(i), p) || !p.fast))
       return fail(CSK_E_INVALID, "batch_create: sketch %u (w=%u) does not fit the binned path", i, sketches[i]->w);
     tok_off[i] = tok_words;
     cnt_off[i] = cnt_words;
@@ -962,7 +991,7 @@ csk_status batch_create_impl(csk_batch** out, csk_sketch* const* sketches, const
     for (uint32_t q = 0; q < p.P; ++q) acc_map.push_back((uint16_t)i);
   }
   // the sort-word kernel serves the batch when it serves every sketch in the same form
-  bool sort_all = true;
+  bool sort_all = !append_all;
   for (uint32_t i = 0; i < count && sort_all; ++i) {
     const csk_sketch* s = sketches[i];
     sort_all = plan_sortbin(plans[i], d, mesh0, s->tables(), s0->upd_form, s0->upd_nt, s0->upd_rp, s0->upd_pf,
@@ -970,7 +999,9 @@ csk_status batch_create_impl(csk_batch** out, csk_sketch* const* sketches, const
                plans[i].nt == plans[0].nt && plans[i].rp == plans[0].rp && plans[i].pf == plans[0].pf;
   }
   BinPlan form{};
-  if (sort_all) {
+  if (append_all) {
+    form = plans[0];
+  } else if (sort_all) {
     form = plans[0];
     for (uint32_t i = 0; i < count; ++i)
       if (plans[i].lds_bytes > lds) lds = plans[i].lds_bytes;
@@ -1024,6 +1055,8 @@ csk_status batch_create_impl(csk_batch** out, csk_sketch* const* sketches, const
       ha[i].plan = plans[i];
       ha[i].w = s->w;
       ha[i].M = s->M;
+      ha[i].split = 1;
+      ha[i].part = nullptr;
     }
     e = hipMemcpy(b->bin, hb.data(), count * sizeof(BinArgs), hipMemcpyHostToDevice);
   }
@@ -1136,7 +1169,10 @@ csk_status csk_batch_update(csk_batch* b, const float* const* pos, const uint64_
     call.n[i] = n[i];
   }
   hipStream_t st = (hipStream_t)stream;
-  if (b->form.sort)
+  if (is_append(b->form)) {
+    const AppendBatch ab{b->bin, b->wg_sketch, b->wg_first, b->nwg_total, b->lds_bytes, &call};
+    CSK_HIP(launch_append_batch(ab, b->d, b->mode, b->form, st), "batch_update (bin)");
+  } else if (b->form.sort)
     CSK_HIP(launch_sortbin_batch(b->bin, b->wg_sketch, b->wg_first, b->nwg_total, b->lds_bytes, b->d, b->mode, b->form, b->kb,
                                  call, st),
             "batch_update (bin)");
@@ -1899,7 +1935,10 @@ csk_status csk_sketch_update_routed(csk_sketch* s, const float* pos, uint64_t n,
     bool binned = s->upd_mode != CSK_UPDATE_DIRECT && s->d == 5 &&
                   plan_bin_wg(m, s->d, s->w, bin_wg_cap(s->d, s->upd_max_wg), plan) && plan.fast;
     bool sorted = false;
-    if (binned) {
+    // the append bin kernel with the exclusion; the handle's tiling may ask for the older forms
+    const bool append = binned && s->upd_form == kFormAuto &&
+                        plan_append(plan, m, s->d, s->w, s->upd_max_wg, mesh, t, true);
+    if (binned && !append) {
       // the sort-word kernel on the row tables (two rows per pass beside the exclusion's
       // table) when the handle's tiling asks for it: at 2^22 - 39 322 counters per row it
       // took 3.96 ms per 2^28 particles against 3.81 for the general kernel, which is the
@@ -1925,15 +1964,21 @@ csk_status csk_sketch_update_routed(csk_sketch* s, const float* pos, uint64_t n,
       CSK_HIP(launch_update_direct_routed(p, m, mesh, t, s->M, s->err(), ex, st), "update_routed (direct)");
       continue;
     }
-    CSK_HIP(ensure_update_scratch(s, plan, st), "update_routed: token scratch");
-    if (sorted) {
-      BinArgs a = make_bin_args(p, m, mesh, t, plan, s->tok, s->cnt, s->M, s->err());
+    const uint32_t split = accumulate_split(plan, m, s->d);
+    UpdateScratch u;
+    CSK_HIP(ensure_update_scratch(s, plan, split, st, &u), "update_routed: token scratch");
+    if (append) {
+      BinArgs a = make_bin_args(p, m, mesh, t, plan, u.tok, u.cnt, s->M, s->err());
+      a.ex = ex;
+      CSK_HIP(launch_append_routed(a, mesh.mode, st), "update_routed (bin)");
+    } else if (sorted) {
+      BinArgs a = make_bin_args(p, m, mesh, t, plan, u.tok, u.cnt, s->M, s->err());
       a.ex = ex;
       CSK_HIP(launch_sortbin_routed(a, mesh.mode, st), "update_routed (bin)");
     } else {
-      CSK_HIP(launch_bin_routed(p, m, mesh, t, plan, s->tok, s->cnt, s->M, s->err(), ex, st), "update_routed (bin)");
+      CSK_HIP(launch_bin_routed(p, m, mesh, t, plan, u.tok, u.cnt, s->M, s->err(), ex, st), "update_routed (bin)");
     }
-    CSK_HIP(launch_accumulate(s->tok, s->cnt, plan, s->w, s->M, st), "update_routed (accumulate)");
+    CSK_HIP(launch_accumulate(u.tok, u.cnt, plan, s->w, s->M, split, u.part, st), "update_routed (accumulate)");
   }
   CSK_HIP(launch_route_table(ex, (uint32_t)mesh.G, table_keys, table_counts, table_slots - 1, err, st),
           "update_routed (table)");

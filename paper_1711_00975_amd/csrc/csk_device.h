@@ -37,6 +37,7 @@ struct Mesh {
   double R;       // G / L when it is exact (modes 1, 2)
   float Rf;       // G / L as a float (mode 2: a power of two >= 1)
   float twoLf;    // 2L as a float (mode 2: exact)
+  uint32_t Lbits; // bits of the largest float <= L: p is in [0, L) when p's bits are below them
   uint32_t group; // items are cell keys divided by `group` (1: the cell keys themselves)
   double ginv;    // binary64(1 / group)
 };
@@ -110,6 +111,34 @@ __device__ __forceinline__ bool cell_index_m(float p, const Mesh& m, int32_t& ou
   return ok;
 }
 
+// The cell index of a coordinate known to be in [0, L): no wrap and no domain test.
+template <uint32_t MODE>
+__device__ __forceinline__ uint32_t cell_index_inside(float p, const Mesh& m) {
+  if (MODE == kMeshPow2Ratio) return (uint32_t)(p * m.Rf);
+  const double x = (double)p;
+  if (MODE == kMeshExactRatio) return (uint32_t)(x * m.R);
+  const double t = x * m.Gd;
+  const double q = __builtin_floor(t * m.invL);
+  const double r0 = __builtin_fma(-q, m.L, t);
+  const double r1 = __builtin_fma(-(q + 1.0), m.L, t);
+  return (uint32_t)((int32_t)q + ((r1 >= 0.0) ? 1 : 0) - ((r0 < 0.0) ? 1 : 0));
+}
+
+// Are all three coordinates in [0, L), by their bits (negative numbers and NaN compare above)?
+// L itself may be refused when it is no float: the caller's general path takes those.
+__device__ __forceinline__ bool inside_box(float x, float y, float z, const Mesh& m) {
+  return ((int)(__float_as_uint(x) < m.Lbits) & (int)(__float_as_uint(y) < m.Lbits) &
+          (int)(__float_as_uint(z) < m.Lbits)) != 0;
+}
+
+// Key of the cell (ix, iy, iz), each index in [0, G): G <= 65535, so ix * G + iy is a full-rate
+// 24-bit multiply-add below 2^32.
+__device__ __forceinline__ uint64_t cell_key_of(int32_t ix, int32_t iy, int32_t iz, const Mesh& m) {
+  const uint32_t G = (uint32_t)m.G & 0xFFFFu;
+  const uint32_t xy = __umul24((uint32_t)ix, G) + (uint32_t)iy;
+  return (uint64_t)xy * (uint64_t)G + (uint64_t)(uint32_t)iz;
+}
+
 // GROUPED = false: the caller has checked that the mesh's group is 1, so the division
 // of group_key() is left out of the code altogether (a uniform branch on the group was
 // compiled into a computed-and-discarded division per particle).
@@ -118,8 +147,7 @@ __device__ __forceinline__ bool cell_key_m(float x, float y, float z, const Mesh
   int32_t ix, iy, iz;
   const bool ok = (int)cell_index_m<MODE>(x, m, ix) & (int)cell_index_m<MODE>(y, m, iy) &
                   (int)cell_index_m<MODE>(z, m, iz);
-  const uint32_t xy = (uint32_t)ix * (uint32_t)m.G + (uint32_t)iy;  // < G^2 <= 2^32
-  const uint64_t k = (uint64_t)xy * (uint64_t)(uint32_t)m.G + (uint64_t)(uint32_t)iz;
+  const uint64_t k = cell_key_of(ix, iy, iz, m);
   key = GROUPED ? group_key(k, m) : k;
   return ok;
 }

@@ -61,6 +61,12 @@ struct BinPlan {
   uint32_t rp;          // its rows per LDS pass (2 or 3)
   uint32_t pf;          // 1: it loads the next tile's positions while sorting the current one
   uint32_t nt;          // its threads per workgroup (512 or 1024)
+  // the append bin kernel (sort == kAppendPacked or kAppendRows)
+  uint32_t ring;        // tokens a bin's LDS buffer holds (a multiple of 8)
+  uint32_t pp;          // particles per thread between two flushes (even)
+  uint32_t kb;          // key bytes it looks up (4, 5 or 6)
+  uint32_t tpb;         // threads that flush one bin (a power of two, at most 64)
+  uint32_t hold;        // 1: half a piece waits in registers (more bins than LDS has room for)
 };
 
 constexpr int kBin2Threads = 1024;                 // row-interleaved bin kernel
@@ -91,6 +97,12 @@ constexpr uint32_t kFormSortWord = 2;
 // fields), or on the row-interleaved tables with multiply-high buckets (any w <= 2^24).
 constexpr uint32_t kSortPacked = 1;
 constexpr uint32_t kSortRows = 2;
+// Append bin kernel forms (csk_append_body.h): on the packed sort-word table, or on the
+// row-interleaved tables.
+constexpr uint32_t kAppendPacked = 3;
+constexpr uint32_t kAppendRows = 4;
+constexpr uint32_t kAppendGranule = 32;   // tokens of one 64-byte piece of a region
+constexpr uint32_t kAppendHold = 16;      // tokens that a bin gives up at a time in its HOLD form
 // Turn a fast bin plan into a sort-word plan when the form asks for it (or leaves it
 // to us) and the sketch, the mesh (ungrouped, not packed) and LDS allow: want_nt 0 (auto),
 // 512 or 1024 threads; want_rp 0 (auto), 2 or 3 rows per pass; want_pf 0 (auto), 1 (off)
@@ -99,6 +111,14 @@ constexpr uint32_t kSortRows = 2;
 // uses the sort-word kernel.
 bool plan_sortbin(BinPlan& p, uint32_t d, const Mesh& mesh, const Tables& t, uint32_t form, uint32_t want_nt,
                   uint32_t want_rp, uint32_t want_pf, bool rows_ok);
+
+// Turn a fast bin plan into a plan of the append bin kernel when the mesh (ungrouped) and
+// LDS allow: its workgroups (at most want_wg; 0: automatic), regions and LDS buffers.  ex: with the router's
+// exclusion (d = 5, float positions).  Returns true if the plan now uses it.
+// kb_least: key bytes it looks up at least (a batch's meshes share one kernel).
+bool plan_append(BinPlan& p, uint64_t n, uint32_t d, uint32_t w, uint32_t want_wg, const Mesh& mesh, const Tables& t,
+                 bool ex, uint32_t kb_least = 4);
+inline bool is_append(const BinPlan& p) { return p.sort == kAppendPacked || p.sort == kAppendRows; }
 
 // The learned router's exclusion (csk_sketch_update_routed): a particle whose coarse parent
 // (its fine index divided by `factor` on each axis, on the mesh of G / factor cells a side)
@@ -149,6 +169,8 @@ struct AccArgs {
   BinPlan plan;
   uint32_t w;
   int32_t* __restrict__ M;
+  uint32_t split;               // workgroups that share one slice's regions (1: none)
+  int32_t* __restrict__ part;   // split > 1: their partial slices, [P][split][2^15]
 };
 
 // Per-call streams of a batched update: sketch i reads n[i] particles at pos[i].
@@ -169,6 +191,23 @@ hipError_t launch_sortbin_routed(const BinArgs& a, uint32_t mesh_mode, hipStream
 hipError_t launch_sortbin_batch(const BinArgs* descs, const uint16_t* wg_sketch, const uint32_t* wg_first,
                                 uint32_t nwg_total, uint32_t lds_bytes, uint32_t d, uint32_t mode, const BinPlan& form,
                                 uint32_t kb, const BatchCall& call, hipStream_t s);
+hipError_t launch_append(const BinArgs& a, uint32_t mesh_mode, hipStream_t s);
+hipError_t launch_append_rows(const BinArgs& a, uint32_t mesh_mode, hipStream_t s);   // d = 5..8
+hipError_t launch_append_few(const BinArgs& a, uint32_t mesh_mode, hipStream_t s);    // d = 1..4
+hipError_t launch_append_routed(const BinArgs& a, uint32_t mesh_mode, hipStream_t s); // a.ex, d = 5
+// One launch for many sketches of the same d, mesh mode and append form (form.sort, form.kb; none
+// of them holds half pieces): workgroup g serves sketch wg_sketch[g].
+struct AppendBatch {
+  const BinArgs* descs;
+  const uint16_t* wg_sketch;
+  const uint32_t* wg_first;
+  uint32_t nwg_total, lds_bytes;
+  const BatchCall* call;
+};
+hipError_t launch_append_batch(const AppendBatch& b, uint32_t d, uint32_t mesh_mode, const BinPlan& form, hipStream_t s);
+hipError_t launch_append_rows_batch(const AppendBatch& b, uint32_t d, uint32_t mesh_mode, uint32_t kb, hipStream_t s);
+hipError_t launch_append_few_batch(const AppendBatch& b, uint32_t d, uint32_t mesh_mode, uint32_t kb, hipStream_t s);
+uint32_t append_lds_bytes(uint32_t d, uint32_t kb, uint32_t P, uint32_t ring, bool rows, bool ex);
 BinArgs make_bin_args(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const BinPlan& plan,
                       uint16_t* tok, uint32_t* cnt, int32_t* M, uint32_t* err);
 // One bin launch for many sketches of the same d, mesh mode and hash mode (fast path,
@@ -183,8 +222,13 @@ hipError_t launch_accumulate_batch(const AccArgs* descs, const uint16_t* acc_ske
 
 hipError_t launch_bin(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const BinPlan& plan,
                       uint16_t* tok, uint32_t* cnt, int32_t* M, uint32_t* err, hipStream_t s);
+// Workgroups that share one slice's regions in the accumulate of a plan over n particles of d
+// rows, and the bytes of the partial slices they need (0 when one workgroup takes each slice).
+uint32_t accumulate_split(const BinPlan& plan, uint64_t n, uint32_t d);
+uint64_t accumulate_part_bytes(const BinPlan& plan, uint32_t split);
 hipError_t launch_accumulate(const uint16_t* tok, const uint32_t* cnt, const BinPlan& plan, uint32_t w,
-                             int32_t* M, hipStream_t s);
+                             int32_t* M, uint32_t split, int32_t* part, hipStream_t s);
+constexpr uint64_t kShortStream = 1u << 20;   // longest stream of the particle-and-row direct kernel
 hipError_t launch_update_direct(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, int32_t* M,
                                 uint32_t* err, hipStream_t s);
 // The update with the learned router's exclusion: the general bin kernel (d = 5, a fast

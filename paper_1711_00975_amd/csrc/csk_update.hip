@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+
 #include "csk_kernel_util.h"
 
 namespace csk {
@@ -400,6 +402,64 @@ bool plan_sortbin(BinPlan& p, uint32_t d, const Mesh& mesh, const Tables& t, uin
   return true;
 }
 
+bool plan_append(BinPlan& p, uint64_t n, uint32_t d, uint32_t w, uint32_t want_wg, const Mesh& mesh, const Tables& t,
+                 bool ex, uint32_t kb_least) {
+  if (!p.fast || t.tabi == nullptr || mesh.group != 1u || n == 0) return false;
+  if (ex && (d != 5 || mesh.mode == kMeshPacked)) return false;
+  const bool rows = t.tabs == nullptr || ex;   // the exclusion is compiled on the row tables
+  const uint32_t kb = mesh.nch <= kb_least ? kb_least : mesh.nch;
+  const uint32_t fixed = append_lds_bytes(d, kb, p.P, 0, rows, ex);
+  if (fixed + 32u >= kMaxLds) return false;
+  // Buffers: what LDS holds, in whole 16-byte parts.  A bin gives up 32 tokens at a time, or 16
+  // when there is no room for 32 and a phase's arrivals (the other half waits in registers).
+  uint32_t ring = ((kMaxLds - fixed) / (2u * p.P)) & ~7u;
+  if (ring > 4096u) ring = 4096u;
+  const uint32_t hold = ring < 48u ? 1u : 0u;
+  if (ring < 24u) return false;
+  if (hold) ring = 24u;
+  // Arrivals of a phase: 1024 pp particles over w / 2^15 slices.  pp is the largest that
+  // leaves room for them (mean + 2.5 sigma) above the tokens that wait for a granule.
+  const double per_iter = 1024.0 * (w < kSlice ? 1.0 : (double)kSlice / (double)w);
+  const double wait = hold ? kAppendHold - 1.0 : kAppendGranule - 1.0;
+  uint32_t pp = 8;
+  while (pp > 2 && pp * per_iter + 2.5 * std::sqrt(pp * per_iter) + wait > (double)ring) pp /= 2;
+  uint32_t tpb = hold ? 1u : 4u;
+  while (!hold && tpb < 64u && 2u * tpb * p.P <= (uint32_t)kBin2Threads) tpb *= 2;
+  if ((hold ? 3u : 5u) * (uint32_t)kBin2Threads / tpb < p.P) return false;
+  // Workgroups: a piece of 1024 particles each, but enough pieces that a bin gets 8 tokens or
+  // so (the last granule of every bin goes out partly filled).
+  const uint64_t pieces = (n + kBin2Threads - 1) / kBin2Threads;
+  const uint64_t least = (p.Pr * 8u + kBin2Threads - 1) / kBin2Threads;
+  const uint64_t span = (w < kSlice) ? w : kSlice;   // counters of a full slice
+  uint64_t nwg, cap;
+  for (uint64_t max_wg = want_wg ? want_wg : 256u;; max_wg *= 2) {
+    uint64_t per = least;
+    nwg = (pieces + least - 1) / least;
+    if (nwg > max_wg) {
+      nwg = max_wg;
+      per = (pieces + nwg - 1) / nwg;
+    }
+    const uint64_t per_wg = per * kBin2Threads;      // most particles one workgroup sees
+    cap = (per_wg * span * 13 + (uint64_t)w * 10 - 1) / ((uint64_t)w * 10) + 64;  // 1.3x mean + 64
+    if (cap > per_wg) cap = per_wg;
+    cap = (cap + kAppendGranule - 1) & ~(uint64_t)(kAppendGranule - 1);
+    // few slices and a long stream: more workgroups, so that a region's granules count in 16 bits
+    if (cap / kAppendHold <= 0xFFFFu || want_wg || max_wg >= 8192) break;
+  }
+  if ((uint64_t)p.P * cap >= 0x7FFFFFFFull || cap / kAppendHold > 0xFFFFull) return false;
+  p.sort = rows ? kAppendRows : kAppendPacked;
+  p.nwg = (uint32_t)nwg;
+  p.cap = (uint32_t)cap;
+  p.ring = ring;
+  p.pp = pp;
+  p.kb = kb;
+  p.tpb = tpb;
+  p.hold = hold;
+  p.nt = kBin2Threads;
+  p.lds_bytes = append_lds_bytes(d, kb, p.P, ring, rows, ex);
+  return true;
+}
+
 // Key bytes hashed: d = 5 with packed fields looks up exactly those its mesh needs (5 below
 // 2^40, else 6); every other form looks up all six.
 template <int D, uint32_t MM>
@@ -515,6 +575,7 @@ hipError_t launch_bin_batch(const BinArgs* descs, const uint16_t* wg_sketch, con
 hipError_t launch_bin(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const BinPlan& plan,
                       uint16_t* tok, uint32_t* cnt, int32_t* M, uint32_t* err, hipStream_t s) {
   const BinArgs a = make_bin_args(pos, n, mesh, t, plan, tok, cnt, M, err);
+  if (is_append(plan)) return launch_append(a, mesh.mode, s);
   if (plan.sort) return launch_sortbin(a, mesh.mode, s);
   if (plan.fast) {
     const dim3 grid(plan.nwg), block(kBin2Threads);
@@ -570,52 +631,126 @@ hipError_t launch_bin_routed(const float* pos, uint64_t n, const Mesh& mesh, con
 // ------------------------------------------------------------------ accumulate
 
 
-__device__ __forceinline__ void accumulate_body(const AccArgs& a, uint32_t s) {
-  extern __shared__ uint32_t lds[];
-  int32_t* acc = (int32_t*)lds;  // kSlice counters
+// Sum of slice s's tokens over this workgroup's share of the regions (part q of `split`).
+// The regions are walked as one array of 16-byte chunks (cap / 8 per region) whose valid part
+// is known from the counts in LDS, so that a thread's loads depend on nothing but the chunk's
+// number and 2 x kAccLoads of them are in flight: with one wave per region, the count and then
+// the tokens were waited for region by region (188 us per call of 2^25 particles into 640
+// slices, 134 now; the tokens and the counters' read-modify-write there are 0.5 GB).
+constexpr uint32_t kAccLoads = 4;
+constexpr uint32_t kAccCounts = 4096;   // region counts held in LDS at a time
+
+__device__ __forceinline__ void accumulate_body(const AccArgs& a, uint32_t s, uint32_t q) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  int32_t* acc = (int32_t*)lds;     // kSlice counters
+  uint32_t* count = lds + kSlice;   // kAccCounts
+  using V4 = uint32_t __attribute__((ext_vector_type(4)));
   const BinPlan& pl = a.plan;
   const uint32_t r = s / pl.Pr, sl = s % pl.Pr;
-  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
-  for (uint32_t i = tid; i < kSlice; i += kAccThreads) acc[i] = 0;
-  __syncthreads();
-  constexpr uint32_t U = 4;
-  for (uint32_t g = wave; g < pl.nwg; g += kAccThreads / 64) {
-    const uint32_t c = min(a.cnt[(uint64_t)s * pl.nwg + g], pl.cap);
-    const uint16_t* reg = a.tok + ((uint64_t)g * pl.P + s) * (uint64_t)pl.cap;
-    const uint4* t4 = (const uint4*)reg;
-    const uint32_t nfull = c / 8;  // whole 16-byte chunks
-    for (uint32_t q0 = 0; q0 < nfull; q0 += 64 * U) {
-      uint4 v[U];
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t q = q0 + u * 64 + lane;
-        v[u] = (q < nfull) ? t4[q] : make_uint4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) {
-        if (q0 + u * 64 + lane < nfull) {
-          const uint32_t wds[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-          for (uint32_t e = 0; e < 8; ++e) {
-            const uint32_t tk = (wds[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-            atomicAdd(&acc[tk & (kSlice - 1)], (tk & 0x8000u) ? -1 : 1);
-          }
-        }
-      }
-    }
-    if (lane < c - nfull * 8) {
-      const uint32_t tk = reg[nfull * 8 + lane];
-      atomicAdd(&acc[tk & (kSlice - 1)], (tk & 0x8000u) ? -1 : 1);
-    }
-  }
-  __syncthreads();
+  const uint32_t tid = threadIdx.x;
   const uint32_t b0 = sl * kSlice;
   const uint32_t len = min(kSlice, a.w - b0);
+  const uint32_t g_lo = (uint32_t)((uint64_t)pl.nwg * q / a.split);
+  const uint32_t g_hi = (uint32_t)((uint64_t)pl.nwg * (q + 1) / a.split);
+  for (uint32_t i = tid; i < kSlice / 4; i += kAccThreads) ((V4*)acc)[i] = V4{0, 0, 0, 0};
+  const uint32_t cpr = pl.cap / 8;   // 16-byte chunks per region
+  const uint32_t sg = kAccThreads / cpr, sc = kAccThreads % cpr;
+  const uint64_t region = (uint64_t)pl.P * pl.cap;   // tokens from a workgroup's region to the next one's
+  // token in the low (high) half of x: byte address of its counter, +1 or -1
+  auto add = [&](uint32_t x, bool high) {
+    const uint32_t at = (high ? x >> 14 : x << 2) & (4u * kSlice - 4u);
+    const int32_t one = (high ? (int32_t)x >> 31 : (int32_t)(x << 16) >> 31) | 1;
+    atomicAdd((int32_t*)((uint8_t*)acc + at), one);
+  };
+  for (uint32_t g0 = g_lo; g0 < g_hi; g0 += kAccCounts) {
+    const uint32_t ng = min(kAccCounts, g_hi - g0);
+    for (uint32_t i = tid; i < ng; i += kAccThreads) count[i] = min(a.cnt[(uint64_t)s * pl.nwg + g0 + i], pl.cap);
+    __syncthreads();
+    const uint16_t* base = a.tok + ((uint64_t)g0 * pl.P + s) * (uint64_t)pl.cap;
+    uint32_t g = tid / cpr, c = tid % cpr;   // chunk c of region g
+    V4 v[2][kAccLoads];
+    uint32_t have[2][kAccLoads];   // valid tokens of the chunk
+    auto load = [&](V4 (&x)[kAccLoads], uint32_t (&h)[kAccLoads]) {
+#pragma unroll
+      for (uint32_t u = 0; u < kAccLoads; ++u) {
+        const uint32_t n = g < ng ? count[g] : 0u;
+        h[u] = n > 8 * c ? min(n - 8 * c, 8u) : 0u;
+        if (h[u]) x[u] = __builtin_nontemporal_load((const V4*)(base + g * region + 8 * c));
+        g += sg;
+        c += sc;
+        if (c >= cpr) {
+          c -= cpr;
+          ++g;
+        }
+      }
+    };
+    auto sum = [&](const V4 (&x)[kAccLoads], const uint32_t (&h)[kAccLoads]) {
+#pragma unroll
+      for (uint32_t u = 0; u < kAccLoads; ++u) {
+        if (h[u] == 8u) {
+#pragma unroll
+          for (uint32_t e = 0; e < 8; ++e) add(x[u][e >> 1], e & 1);
+        } else if (h[u]) {   // the last chunk of a region
+#pragma unroll
+          for (uint32_t e = 0; e < 7; ++e)
+            if (e < h[u]) add(x[u][e >> 1], e & 1);
+        }
+      }
+    };
+    // one set of loads is in flight while the other is summed
+    load(v[0], have[0]);
+    for (;;) {
+      const bool more = g < ng;
+      if (more) load(v[1], have[1]);
+      sum(v[0], have[0]);
+      if (!more) break;
+      const bool again = g < ng;
+      if (again) load(v[0], have[0]);
+      sum(v[1], have[1]);
+      if (!again) break;
+    }
+    __syncthreads();
+  }
+  if (a.split > 1) {
+    V4* out = (V4*)(a.part + ((uint64_t)s * a.split + q) * kSlice);
+    for (uint32_t i = tid; i < (len + 3) / 4; i += kAccThreads) out[i] = ((const V4*)acc)[i];
+    return;
+  }
+  // the slice's counters, eight loads in flight per thread (one round trip to memory for each of
+  // the 32 otherwise)
   int32_t* Mrow = a.M + (uint64_t)r * a.w + b0;
-  for (uint32_t i = tid; i < len; i += kAccThreads) Mrow[i] = (int32_t)((uint32_t)Mrow[i] + (uint32_t)acc[i]);
+  for (uint32_t i0 = tid; i0 < len; i0 += 8 * kAccThreads) {
+    uint32_t m[8];
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      const uint32_t i = i0 + e * kAccThreads;
+      m[e] = (uint32_t)Mrow[i < len ? i : i0];
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      const uint32_t i = i0 + e * kAccThreads;
+      if (i < len) Mrow[i] = (int32_t)(m[e] + (uint32_t)acc[i]);
+    }
+  }
 }
 
-__global__ __launch_bounds__(kAccThreads) void accumulate_kernel(AccArgs a) { accumulate_body(a, blockIdx.x); }
+__global__ __launch_bounds__(kAccThreads) void accumulate_kernel(AccArgs a) {
+  accumulate_body(a, blockIdx.x / a.split, blockIdx.x % a.split);
+}
+
+// M += the partial slices of a split accumulate: one thread per counter.
+__global__ __launch_bounds__(256) void accumulate_reduce_kernel(AccArgs a) {
+  const uint32_t s = blockIdx.y, r = s / a.plan.Pr, sl = s % a.plan.Pr;
+  const uint32_t len = min(kSlice, a.w - sl * kSlice);
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= len) return;
+  const int32_t* p = a.part + (uint64_t)s * a.split * kSlice + i;
+  int32_t* m = a.M + (uint64_t)r * a.w + (uint64_t)sl * kSlice + i;
+  uint32_t sum = (uint32_t)*m;
+#pragma unroll 8
+  for (uint32_t q = 0; q < a.split; ++q) sum += (uint32_t)p[(uint64_t)q * kSlice];
+  *m = (int32_t)sum;
+}
 
 // Many sketches in one launch: block blockIdx.x sums slice blockIdx.x - acc_first[sketch]
 // of sketch acc_sketch[blockIdx.x].
@@ -623,24 +758,45 @@ __global__ __launch_bounds__(kAccThreads) void accumulate_batch_kernel(const Acc
                                                                        const uint16_t* __restrict__ acc_sketch,
                                                                        const uint32_t* __restrict__ acc_first) {
   const uint32_t i = acc_sketch[blockIdx.x];
-  accumulate_body(descs[i], blockIdx.x - acc_first[i]);
+  accumulate_body(descs[i], blockIdx.x - acc_first[i], 0);
+}
+
+constexpr uint32_t kAccLds = (kSlice + kAccCounts) * sizeof(int32_t);
+
+// With fewer slices than CUs, several workgroups share a slice (each needs a partial slice of
+// 128 KiB written and read again, worth it from about 2^16 tokens per workgroup).
+uint32_t accumulate_split(const BinPlan& plan, uint64_t n, uint32_t d) {
+  if (plan.P > 128) return 1;
+  uint64_t split = 256u / plan.P;
+  const uint64_t by_tokens = n * d / ((uint64_t)plan.P << 16);
+  if (split > by_tokens) split = by_tokens;
+  if (split > plan.nwg) split = plan.nwg;
+  return split > 1 ? (uint32_t)split : 1u;
+}
+
+uint64_t accumulate_part_bytes(const BinPlan& plan, uint32_t split) {
+  return split > 1 ? (uint64_t)plan.P * split * kSlice * sizeof(int32_t) : 0u;
 }
 
 hipError_t launch_accumulate(const uint16_t* tok, const uint32_t* cnt, const BinPlan& plan, uint32_t w,
-                             int32_t* M, hipStream_t s) {
+                             int32_t* M, uint32_t split, int32_t* part, hipStream_t s) {
   AccArgs a;
   a.tok = tok;
   a.cnt = cnt;
   a.plan = plan;
   a.w = w;
   a.M = M;
-  hipLaunchKernelGGL(accumulate_kernel, dim3(plan.P), dim3(kAccThreads), kSlice * sizeof(int32_t), s, a);
+  a.split = split;
+  a.part = part;
+  hipLaunchKernelGGL(accumulate_kernel, dim3(plan.P * split), dim3(kAccThreads), kAccLds, s, a);
+  if (split > 1)
+    hipLaunchKernelGGL(accumulate_reduce_kernel, dim3((min(w, kSlice) + 255) / 256, plan.P), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_accumulate_batch(const AccArgs* descs, const uint16_t* acc_sketch, const uint32_t* acc_first,
                                    uint32_t nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(accumulate_batch_kernel, dim3(nblocks), dim3(kAccThreads), kSlice * sizeof(int32_t), s, descs,
+  hipLaunchKernelGGL(accumulate_batch_kernel, dim3(nblocks), dim3(kAccThreads), kAccLds, s, descs,
                      acc_sketch, acc_first);
   return hipGetLastError();
 }
@@ -668,8 +824,40 @@ __global__ __launch_bounds__(256) void update_direct_kernel(const float* __restr
   }
 }
 
+// The direct update of a short stream: one thread per particle and row (blockIdx.y), so that a
+// few thousand particles are enough threads to hide the two memory round trips (position, the
+// row's six table entries) behind each other.  Lanes of a wave with the same counter and sign
+// (a stream in structure order) add together, for the first few such groups of the wave.
+__global__ __launch_bounds__(256) void update_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
+                                                           const uint32_t* __restrict__ tab, uint32_t w, uint32_t cm,
+                                                           int32_t* __restrict__ M, uint32_t* __restrict__ err) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
+  uint64_t key;
+  const bool in = i < n;
+  const bool ok = particle_key(pos, in ? i : n - 1, mesh, key) && in;
+  if (in && !ok && r == 0) atomicOr(err, kErrDomain);
+  const uint32_t h = row_hash(tab + r * kTableWords, key);   // every byte indexes its table in range
+  const uint32_t b = bucket_of(h, w), neg = (h >> 31) & (cm ^ 1u);
+  int32_t* Mr = M + (uint64_t)r * w;
+  uint64_t todo = __ballot(ok);
+  const uint32_t mine = (b << 1) | neg;   // w <= 2^30
+  for (int k = 0; k < 4 && todo; ++k) {
+    const uint32_t lead = (uint32_t)__ffsll((unsigned long long)todo) - 1u;
+    const uint64_t same = __ballot(ok && mine == (uint32_t)__builtin_amdgcn_readlane(mine, lead)) & todo;
+    const int32_t times = (int32_t)__popcll(same);
+    if (lane_id() == lead) atomicAdd(&Mr[b], neg ? -times : times);
+    todo &= ~same;
+  }
+  if ((todo >> lane_id()) & 1u) atomicAdd(&Mr[b], neg ? -1 : 1);
+}
+
 hipError_t launch_update_direct(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, int32_t* M,
                                 uint32_t* err, hipStream_t s) {
+  if (n <= kShortStream) {
+    hipLaunchKernelGGL(update_short_kernel, dim3((uint32_t)((n + 255) / 256), t.d), dim3(256), 0, s, pos, (uint32_t)n,
+                       mesh, t.tab, t.w, t.cm, M, err);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(update_direct_kernel, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, pos, n, mesh, t.tab,
                      t.d, t.w, t.cm, M, err);
   return hipGetLastError();

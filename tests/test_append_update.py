@@ -1,0 +1,126 @@
+"""The append bin kernel and the short-stream update against the oracle, bit for bit, where they
+can go wrong: streams of one piece of 1024 particles and its neighbours, many flushes per
+workgroup with a ragged end, bins that hold half a 64-byte piece in registers (w = 2^24), the
+narrowest rows, structure order and a single cell (repeated cells, full buffers, full regions),
+particles outside the domain, split accumulates, and both sides of the short-stream rule."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1711_00975_amd as csk
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _stream(n, L, seed, order):
+    rng = np.random.default_rng(seed)
+    if order == "one cell":
+        return np.full((n, 3), 0.3 * L, dtype=np.float32)
+    nclump = 40
+    which = rng.integers(0, nclump, n)
+    if order == "sorted":
+        which = np.sort(which)
+    centres = rng.uniform(0, L, (nclump, 3))
+    clump = centres[which] + rng.normal(0, 0.002 * L, (n, 3))
+    pos = np.where((rng.random(n) < 0.7)[:, None], clump, rng.uniform(0, L, (n, 3)))
+    pos = np.mod(pos, L).astype(np.float32)
+    pos[pos >= L] = 0.0
+    if order == "outside":
+        bad = rng.choice(n, max(1, n // 50), replace=False)
+        pos[bad, rng.integers(0, 3, bad.size)] = rng.choice(
+            np.array([np.nan, np.inf, 2 * L, -3 * L], dtype=np.float32), bad.size)
+        wrap = rng.choice(n, max(1, n // 20), replace=False)   # inside [-L, 2L): wrapped, not skipped
+        pos[wrap] = np.where(np.isfinite(pos[wrap]) & (np.abs(pos[wrap]) < L), pos[wrap] - np.float32(L), pos[wrap])
+    return pos
+
+
+def _check(n, d, w, L, delta, variant, order, max_wg, mode=None):
+    print("append", n, d, w, L, delta, variant, order, max_wg, flush=True)
+    pos = _stream(n, L, 17 + n % 97, order)
+    mode = csk.CSK_UPDATE_BINNED if mode is None else mode
+    s = csk.Sketch(d, w, 5, variant)
+    try:
+        s.set_update_plan(mode, max_wg)
+        p = _dev(pos)
+        s.update(p, delta, L)
+        s.update(p[: n // 3], delta, L)          # a second call adds to the first
+        if order == "outside":
+            with pytest.raises(csk.CskError) as ei:
+                s.check()
+            assert ei.value.code == csk.CSK_E_DOMAIN
+        M = s.counters().cpu().numpy()
+    finally:
+        s.close()
+    Mo, _ = oracle.sketch(pos, d, w, 5, delta, L, variant=variant, threads=8)
+    M2, _ = oracle.sketch(pos[: n // 3], d, w, 5, delta, L, variant=variant, threads=8)
+    assert np.array_equal(M, Mo + M2)
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 2049, 40_961])
+def test_pieces_of_1024(n):
+    _check(n, 5, 1 << 16, 100.0, 0.1, 0, "mixed", 0)
+
+
+@pytest.mark.parametrize("d,w,L,delta,variant", [
+    (5, 1 << 24, 1000.0, 0.25, 0),        # 2560 bins: half a piece waits in registers
+    (5, (1 << 24) - 77, 1000.0, 0.25, 1), # the same on the row tables (or without the append kernel)
+    (5, 1 << 23, 1000.0, 0.25, 0),        # 1280 bins, five per thread
+    (6, 1 << 21, 100.0, 0.1, 0),
+    (8, 3 * (1 << 20) + 5, 250.0, 250.0 / 768, 1),
+    (8, 1 << 15, 100.0, 0.1, 0),          # 16-bit packed fields: no slice bits
+    (7, 999, 3000.0, 0.5, 1),
+    (4, 1000, 100.0, 0.4, 0),             # four key bytes
+    (3, 1 << 18, 128.0, 0.125, 0),
+    (2, 3, 100.0, 0.1, 0),
+    (1, 1, 100.0, 0.1, 0),                # one counter: every token in one bin
+])
+@pytest.mark.parametrize("order", ["mixed", "sorted"])
+def test_widths_with_many_flushes(d, w, L, delta, variant, order):
+    _check(150_001, d, w, L, delta, variant, order, 3)
+
+
+@pytest.mark.parametrize("d,w", [(5, 1 << 24), (5, 1 << 16), (8, 100_003)])
+def test_one_cell(d, w):
+    _check(200_003, d, w, 100.0, 0.1, 0, "one cell", 2)
+
+
+@pytest.mark.parametrize("L,delta", [(1000.0, 0.25), (100.0, 0.1), (123.456, 0.123456)])
+def test_outside_the_domain(L, delta):
+    _check(60_001, 5, 1 << 20, L, delta, 0, "outside", 0)
+    _check(3_001, 5, 1 << 20, L, delta, 0, "outside", 0, mode=csk.CSK_UPDATE_AUTO)
+
+
+@pytest.mark.parametrize("d,w", [(5, 1 << 14), (3, 100_000), (1, 1 << 15)])
+def test_split_accumulate(d, w):
+    _check(1_500_001, d, w, 100.0, 0.1, 0, "mixed", 0)
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("order", ["mixed", "one cell"])
+def test_both_sides_of_the_short_stream_rule(order, variant):
+    # n d <= 2^19 + d w / 21 goes straight to the counters
+    d, w = 5, 1 << 16
+    edge = ((1 << 19) + d * w // 21) // d
+    for n in (255, 257, edge, edge + 1):
+        _check(n, d, w, 100.0, 0.1, variant, order, 0, mode=csk.CSK_UPDATE_AUTO)
+
+
+@pytest.mark.parametrize("w", [1 << 22, 99_991])
+def test_packed_stream(w):
+    n, d, L, delta = 200_001, 5, 1000.0, 0.25
+    print("append packed", w, flush=True)
+    pos = _stream(n, L, 3, "mixed")
+    s = csk.Sketch(d, w, 5)
+    try:
+        s.set_update_plan(csk.CSK_UPDATE_BINNED, 2)
+        s.update_packed(csk.pack_positions(_dev(pos), L), delta, L)
+        M = s.counters().cpu().numpy()
+    finally:
+        s.close()
+    keys = oracle.keys_packed(oracle.pack(pos, L), delta, L)
+    assert np.array_equal(M, oracle.sketch_keys(keys, d, w, 5))
