@@ -203,23 +203,25 @@ struct csk_sketch {
   uint32_t max_cand = 0;
   uint32_t* ctl = nullptr;   // [0] error latch, [1] set count
   SelState* sel = nullptr;
-  uint64_t* cand_key = nullptr;
+  uint64_t* cand_key = nullptr;  // the candidate keys as a list, in the order of insertion
   int32_t* cand_est = nullptr;
   uint64_t* sel_key = nullptr;
   int32_t* sel_est = nullptr;
   uint32_t sel_cap = 0;
   uint8_t* scr = nullptr;     // scratch of an update: token regions, their counts, partial slices
   uint64_t scr_bytes = 0;
-  SelState* host_sel = nullptr;   // pinned
+  SelHost* host_sel = nullptr;    // pinned
   uint32_t* host_ctl = nullptr;   // pinned
   bool mesh_set = false;
   double delta = 0, L = 0;
   Mesh mesh{};
+  uint64_t cand_likely = 0;   // items offered to the candidate set since the last clear, as the host saw them
   bool partial_set = false;   // some collect since the last clear used theta > INT32_MIN
   uint64_t bytes = 0;
 
   uint32_t* err() const { return ctl; }
   uint32_t* set_count() const { return ctl + 1; }
+  CandSet cand() const { return CandSet{set, slots - 1u, ctl + 1, max_cand, cand_key}; }
   Tables tables() const {
     Tables t;
     t.tab = tab;
@@ -317,6 +319,7 @@ csk_status clear_candidates(csk_sketch* s, hipStream_t st) {
   CSK_HIP(launch_fill_u64(s->set, s->slots, kEmptyKey, st), "clear candidates");
   CSK_HIP(launch_fill_u32(s->set_count(), 1, 0u, st), "clear candidates");
   s->partial_set = false;
+  s->cand_likely = 0;
   return CSK_OK;
 }
 
@@ -406,7 +409,7 @@ csk_status csk_sketch_init_group(csk_sketch** out, uint32_t d, uint32_t w, uint6
   if (e == hipSuccess) e = dmalloc(s, &s->sel, 1);
   if (e == hipSuccess) e = dmalloc(s, &s->cand_key, max_candidates);
   if (e == hipSuccess) e = dmalloc(s, &s->cand_est, max_candidates);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&s->host_sel, sizeof(SelState), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&s->host_sel, sizeof(SelHost), hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void**)&s->host_ctl, 4 * sizeof(uint32_t), hipHostMallocDefault);
   if (e == hipSuccess) e = hipMemcpy(s->tab, T.data(), T.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess && s->dp)
@@ -421,6 +424,7 @@ csk_status csk_sketch_init_group(csk_sketch** out, uint32_t d, uint32_t w, uint6
     e = hipMemcpy(s->fcols, Fc.data(), Fc.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = launch_fill_u32((uint32_t*)s->M, (uint64_t)d * w, 0u, nullptr);
   if (e == hipSuccess) e = launch_fill_u32(s->ctl, 4, 0u, nullptr);
+  if (e == hipSuccess) e = launch_fill_u32((uint32_t*)s->sel, sizeof(SelState) / 4, 0u, nullptr);
   if (e == hipSuccess) e = launch_fill_u64(s->set, slots, kEmptyKey, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
@@ -650,10 +654,15 @@ csk_status collect_impl(csk_sketch* s, const void* src, bool packed, uint64_t n,
   if (n > 0 && src == nullptr) return fail(CSK_E_INVALID, "collect: NULL positions");
   latch_mesh(s, delta, L, mesh);
   if (theta != INT32_MIN) s->partial_set = true;
+  s->cand_likely += n;
   if (n == 0) return CSK_OK;
   if (packed) mesh.mode = kMeshPacked;
   hipStream_t st = (hipStream_t)stream;
   const Tables t = s->tables();
+  if (collect_is_short(n, t)) {
+    CSK_HIP(launch_collect_short((const float*)src, n, mesh, t, s->M, theta, s->cand(), s->err(), st), "collect (short)");
+    return CSK_OK;
+  }
   const uint32_t* filter = nullptr;
   const uint32_t* hot = nullptr;
   if (s->filter != nullptr && theta > 0) {
@@ -662,8 +671,8 @@ csk_status collect_impl(csk_sketch* s, const void* src, bool packed, uint64_t n,
     filter = s->filter;
     hot = s->filter + kFilterAllocWords;
   }
-  CSK_HIP(launch_collect((const float*)src, n, mesh, t, s->M, theta, filter, hot, filter ? s->hot_table : nullptr, s->set,
-                         s->slots - 1, s->set_count(), s->max_cand, s->err(), true, st),
+  CSK_HIP(launch_collect((const float*)src, n, mesh, t, s->M, theta, filter, hot, filter ? s->hot_table : nullptr,
+                         s->cand(), s->err(), true, st),
           "collect");
   return CSK_OK;
 }
@@ -699,8 +708,9 @@ csk_status csk_collect_dictionary(csk_sketch* s, double delta, double L, int32_t
   }
   const uint64_t ncells = (uint64_t)mesh.G * mesh.G * mesh.G;
   const uint64_t nkeys = (ncells + s->group - 1) / s->group;   // the items: cell keys / group
-  CSK_HIP(launch_collect_dictionary(nkeys, mesh, t, s->M, theta, filter, hot, filter ? s->hot_table : nullptr, s->set,
-                                    s->slots - 1, s->set_count(), s->max_cand, s->err(), st),
+  s->cand_likely += nkeys;
+  CSK_HIP(launch_collect_dictionary(nkeys, mesh, t, s->M, theta, filter, hot, filter ? s->hot_table : nullptr,
+                                    s->cand(), s->err(), st),
           "collect_dictionary");
   return CSK_OK;
 }
@@ -716,12 +726,11 @@ csk_status csk_collect_children(csk_sketch* fine, csk_sketch* coarse, int32_t th
   if (fine->device != coarse->device) return fail(CSK_E_INVALID, "collect_children: handles on different devices");
   hipStream_t st = (hipStream_t)stream;
   const uint64_t ncells = (uint64_t)fine->mesh.G * fine->mesh.G * fine->mesh.G;
-  // the coarse handle's candidate list array and a spare control word serve as scratch
-  CSK_HIP(launch_collect_children(coarse->set, coarse->slots, coarse->cand_key, coarse->ctl + 2, coarse->max_cand,
-                                  coarse->group, ncells, fine->tables(), fine->M, theta, fine->set, fine->slots - 1,
-                                  fine->set_count(), fine->max_cand, fine->err(), st),
+  CSK_HIP(launch_collect_children(coarse->cand_key, coarse->set_count(), coarse->max_cand, coarse->group, ncells,
+                                  fine->tables(), fine->M, theta, fine->cand(), fine->err(), st),
           "collect_children");
   if (theta != INT32_MIN || coarse->partial_set) fine->partial_set = true;
+  fine->cand_likely += ncells;
   return CSK_OK;
 }
 
@@ -730,71 +739,83 @@ csk_status csk_candidates_clear(csk_sketch* s, void* stream) {
   return clear_candidates(s, (hipStream_t)stream);
 }
 
+}  // extern "C"
+
+namespace {
+
+// The selection scratch of a handle holds k winners (a growth synchronizes the stream first).
+csk_status ensure_select_scratch(csk_sketch* s, uint32_t k, hipStream_t st, const char* who) {
+  if (k <= s->sel_cap) return CSK_OK;
+  CSK_HIP(hipStreamSynchronize(st), who);
+  if (s->sel_key) (void)hipFree(s->sel_key);
+  if (s->sel_est) (void)hipFree(s->sel_est);
+  s->bytes -= (uint64_t)s->sel_cap * (sizeof(uint64_t) + sizeof(int32_t));
+  s->sel_key = nullptr;
+  s->sel_est = nullptr;
+  s->sel_cap = 0;
+  CSK_HIP(dmalloc(s, &s->sel_key, k), who);
+  CSK_HIP(dmalloc(s, &s->sel_est, k), who);
+  s->sel_cap = k;
+  return CSK_OK;
+}
+
+struct ExactTable {   // the router's exact table, or none
+  const uint64_t* keys;
+  const uint32_t* counts;
+  uint32_t mask;
+};
+
+// The top-k of a handle's candidates; with out the call's counts stay on the device, else the
+// stream is synchronized and *k_out set.
+csk_status topk_impl(csk_sketch* s, uint32_t k, uint64_t* keys, int32_t* est, uint32_t* out, uint32_t* k_out,
+                     const ExactTable& x, hipStream_t st, const char* who) {
+  csk_status rc = ensure_select_scratch(s, k, st, who);
+  if (rc != CSK_OK) return rc;
+  const uint32_t partial = s->partial_set ? 1u : 0u;
+  if (k > 0)
+    CSK_HIP(launch_topk(s->cand_key, s->set_count(), s->tables(), s->M, s->max_cand, s->cand_likely, k, s->sel,
+                        s->cand_est, s->sel_key,
+                        s->sel_est, keys, est, s->err(), partial, out, out ? nullptr : s->host_sel, st, x.keys,
+                        x.counts, x.mask),
+            who);
+  else if (out)
+    CSK_HIP(launch_fill_u32(out, 2, 0u, st), who);
+  if (out) return CSK_OK;
+  uint32_t bits = 0, m = 0;
+  if (k > 0) {   // the last kernel wrote both to pinned memory
+    CSK_HIP(hipStreamSynchronize(st), who);
+    m = s->host_sel->m;
+    bits = s->host_sel->err;
+    if (bits) CSK_HIP(launch_fill_u32(s->err(), 1, 0u, st), who);
+  } else {
+    rc = take_latch(s, st, &bits);
+    if (rc != CSK_OK) return rc;
+  }
+  rc = latch_status(bits);
+  if (rc != CSK_OK) return rc;
+  const uint32_t got = (k < m) ? k : m;
+  *k_out = got;
+  if (got < k && s->partial_set) return fail(CSK_W_INCOMPLETE, "%s: only %u of %u candidates passed theta", who, got, k);
+  return CSK_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 csk_status csk_topk(csk_sketch* s, uint32_t k, uint64_t* keys, int32_t* est, uint32_t* k_out, void* stream) {
   if (s == nullptr || k_out == nullptr) return fail(CSK_E_INVALID, "topk: NULL handle or k_out");
   *k_out = 0;
   if (k > 0 && (keys == nullptr || est == nullptr)) return fail(CSK_E_INVALID, "topk: NULL output");
   if (k > s->max_cand) return fail(CSK_E_INVALID, "topk: k=%u above max_candidates=%u", k, s->max_cand);
-  hipStream_t st = (hipStream_t)stream;
-  if (k > s->sel_cap) {
-    CSK_HIP(hipStreamSynchronize(st), "topk: grow scratch");
-    if (s->sel_key) (void)hipFree(s->sel_key);
-    if (s->sel_est) (void)hipFree(s->sel_est);
-    s->bytes -= (uint64_t)s->sel_cap * (sizeof(uint64_t) + sizeof(int32_t));
-    s->sel_key = nullptr;
-    s->sel_est = nullptr;
-    s->sel_cap = 0;
-    CSK_HIP(dmalloc(s, &s->sel_key, k), "topk: scratch");
-    CSK_HIP(dmalloc(s, &s->sel_est, k), "topk: scratch");
-    s->sel_cap = k;
-  }
-  if (k > 0) {
-    CSK_HIP(launch_topk(s->set, s->slots, s->tables(), s->M, s->max_cand, k, s->sel, s->cand_key, s->cand_est,
-                        s->sel_key, s->sel_est, keys, est, s->err(), st),
-            "topk");
-  } else {
-    CSK_HIP(launch_fill_u32((uint32_t*)s->sel, sizeof(SelState) / 4, 0u, st), "topk");
-  }
-  CSK_HIP(hipMemcpyAsync(s->host_sel, s->sel, sizeof(SelState), hipMemcpyDeviceToHost, st), "topk: read back");
-  uint32_t bits = 0;
-  csk_status rc = take_latch(s, st, &bits);
-  if (rc != CSK_OK) return rc;
-  rc = latch_status(bits);
-  if (rc != CSK_OK) return rc;
-  const uint32_t m = s->host_sel->m;
-  const uint32_t got = (k < m) ? k : m;
-  *k_out = got;
-  if (got < k && s->partial_set)
-    return fail(CSK_W_INCOMPLETE, "topk: only %u of %u candidates passed theta", got, k);
-  return CSK_OK;
+  return topk_impl(s, k, keys, est, nullptr, k_out, ExactTable{}, (hipStream_t)stream, "topk");
 }
 
 csk_status csk_topk_async(csk_sketch* s, uint32_t k, uint64_t* keys, int32_t* est, uint32_t* out, void* stream) {
   if (s == nullptr || out == nullptr) return fail(CSK_E_INVALID, "topk_async: NULL handle or out");
   if (k > 0 && (keys == nullptr || est == nullptr)) return fail(CSK_E_INVALID, "topk_async: NULL output");
   if (k > s->max_cand) return fail(CSK_E_INVALID, "topk_async: k=%u above max_candidates=%u", k, s->max_cand);
-  hipStream_t st = (hipStream_t)stream;
-  if (k > s->sel_cap) {   // first call with a larger k: grow the scratch (synchronizes)
-    CSK_HIP(hipStreamSynchronize(st), "topk_async: grow scratch");
-    if (s->sel_key) (void)hipFree(s->sel_key);
-    if (s->sel_est) (void)hipFree(s->sel_est);
-    s->bytes -= (uint64_t)s->sel_cap * (sizeof(uint64_t) + sizeof(int32_t));
-    s->sel_key = nullptr;
-    s->sel_est = nullptr;
-    s->sel_cap = 0;
-    CSK_HIP(dmalloc(s, &s->sel_key, k), "topk_async: scratch");
-    CSK_HIP(dmalloc(s, &s->sel_est, k), "topk_async: scratch");
-    s->sel_cap = k;
-  }
-  if (k > 0) {
-    CSK_HIP(launch_topk(s->set, s->slots, s->tables(), s->M, s->max_cand, k, s->sel, s->cand_key, s->cand_est,
-                        s->sel_key, s->sel_est, keys, est, s->err(), st),
-            "topk_async");
-  } else {
-    CSK_HIP(launch_fill_u32((uint32_t*)s->sel, sizeof(SelState) / 4, 0u, st), "topk_async");
-  }
-  CSK_HIP(launch_topk_out(s->sel, k, s->partial_set ? 1u : 0u, out, st), "topk_async");
-  return CSK_OK;
+  return topk_impl(s, k, keys, est, out, nullptr, ExactTable{}, (hipStream_t)stream, "topk_async");
 }
 
 csk_status csk_get_counters(const csk_sketch* cs, int32_t* out, void* stream) {
@@ -835,6 +856,7 @@ csk_status csk_reset(csk_sketch* s, void* stream) {
   CSK_HIP(launch_fill_spans(f, st), "reset");
   s->mesh_set = false;
   s->partial_set = false;
+  s->cand_likely = 0;
   return CSK_OK;
 }
 
@@ -1093,8 +1115,7 @@ csk_status batch_create_impl(csk_batch** out, csk_sketch* const* sketches, const
       b->w_max = s->w > b->w_max ? s->w : b->w_max;
       b->cdesc_host[i] = CollectDesc{m,           t,           s->M,          s->filter,
                                      s->filter ? s->filter + kFilterAllocWords : nullptr,
-                                     s->hot_table, s->set,     s->slots - 1,  s->set_count(),
-                                     s->max_cand, s->err()};
+                                     s->hot_table, s->cand(),  s->err()};
       uint64_t want = ct_total ? (cbudget * ct[i] + ct_total / 2) / ct_total : 1;
       if (want > ct[i]) want = ct[i];
       if (want < 1) want = 1;
@@ -1188,7 +1209,7 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
                           uint32_t* const* out, void* stream) {
   if (b == nullptr || k == nullptr || out == nullptr) return fail(CSK_E_INVALID, "batch_topk: NULL argument");
   hipStream_t st = (hipStream_t)stream;
-  uint32_t k_max = 0, slots_max = 0, mc_max = 0;
+  uint32_t k_max = 0, mc_max = 0;
   for (uint32_t i = 0; i < b->count; ++i) {
     const csk_sketch* s = b->sk[i];
     if (k[i] > s->max_cand)
@@ -1197,23 +1218,12 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
       return fail(CSK_E_INVALID, "batch_topk: NULL output of sketch %u", i);
     if (out[i] == nullptr) return fail(CSK_E_INVALID, "batch_topk: out[%u] is NULL", i);
     k_max = k[i] > k_max ? k[i] : k_max;
-    slots_max = s->slots > slots_max ? s->slots : slots_max;
     mc_max = s->max_cand > mc_max ? s->max_cand : mc_max;
   }
   // the selection scratch of each sketch holds its k (grown here, synchronizing, as by csk_topk_async)
   for (uint32_t i = 0; i < b->count; ++i) {
-    csk_sketch* s = b->sk[i];
-    if (k[i] <= s->sel_cap) continue;
-    CSK_HIP(hipStreamSynchronize(st), "batch_topk: grow scratch");
-    if (s->sel_key) (void)hipFree(s->sel_key);
-    if (s->sel_est) (void)hipFree(s->sel_est);
-    s->bytes -= (uint64_t)s->sel_cap * (sizeof(uint64_t) + sizeof(int32_t));
-    s->sel_key = nullptr;
-    s->sel_est = nullptr;
-    s->sel_cap = 0;
-    CSK_HIP(dmalloc(s, &s->sel_key, k[i]), "batch_topk: scratch");
-    CSK_HIP(dmalloc(s, &s->sel_est, k[i]), "batch_topk: scratch");
-    s->sel_cap = k[i];
+    csk_status rc = ensure_select_scratch(b->sk[i], k[i], st, "batch_topk: grow scratch");
+    if (rc != CSK_OK) return rc;
   }
   // descriptors: built once, rebuilt when a sketch's selection scratch moved
   bool stale = b->topk == nullptr || b->topk_host.size() != b->count;
@@ -1223,8 +1233,8 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
     std::vector<TopkDesc> h(b->count);
     for (uint32_t i = 0; i < b->count; ++i) {
       csk_sketch* s = b->sk[i];
-      h[i] = TopkDesc{s->set, s->slots, s->max_cand, s->tables(), s->M, s->sel, s->cand_key, s->cand_est,
-                      s->sel_key, s->sel_est, s->err()};
+      h[i] = TopkDesc{s->cand_key, s->set_count(), s->max_cand, s->tables(), s->M, s->sel, s->cand_est, s->sel_key,
+                      s->sel_est, s->err()};
     }
     CSK_HIP(hipStreamSynchronize(st), "batch_topk: descriptors");
     if (b->topk == nullptr) CSK_HIP(bmalloc(&b->topk, b->count), "batch_topk: descriptors");
@@ -1239,12 +1249,8 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
     call.out[i] = out[i];
     call.k[i] = k[i];
     call.partial[i] = b->sk[i]->partial_set ? 1u : 0u;
-    // the set holds keys of the latched mesh only (a different mesh needs a reset), all
-    // below G^3: the rank count compares (estimate, key) as one word when that is <= 2^32
-    const uint64_t G = b->sk[i]->mesh_set ? (uint64_t)b->sk[i]->mesh.G : 0u;
-    call.key32[i] = (b->sk[i]->mesh_set && G * G * G <= (1ull << 32)) ? 1u : 0u;
   }
-  CSK_HIP(launch_topk_batch(b->topk, b->count, b->d, slots_max, mc_max, k_max, call, st), "batch_topk");
+  CSK_HIP(launch_topk_batch(b->topk, b->count, b->d, mc_max, k_max, call, st), "batch_topk");
   return CSK_OK;
 }
 
@@ -1254,6 +1260,7 @@ csk_status csk_batch_reset(csk_batch* b, void* stream) {
   for (csk_sketch* s : b->sk) {
     s->mesh_set = false;
     s->partial_set = false;
+    s->cand_likely = 0;
   }
   return CSK_OK;
 }
@@ -1284,6 +1291,7 @@ csk_status csk_batch_collect(csk_batch* b, const float* const* pos, const uint64
     (void)check_mesh(s, b->delta[i], b->L[i], &m);
     latch_mesh(s, b->delta[i], b->L[i], m);
     if (theta[i] != INT32_MIN) s->partial_set = true;
+    s->cand_likely += n[i];
     call.pos[i] = n[i] ? pos[i] : nullptr;
     call.n[i] = n[i];
     call.theta[i] = theta[i];
@@ -1595,22 +1603,20 @@ csk_status csk_table_topk(const uint64_t* table_keys, const uint32_t* table_coun
   SelState* sel = nullptr;
   uint64_t* sk = nullptr;
   int32_t* se = nullptr;
-  uint32_t* rank = nullptr;
   uint32_t* err = nullptr;
   CSK_HIP(cs.get(&sel, 1), "table_topk: scratch");
   CSK_HIP(cs.get(&sk, k), "table_topk: scratch");
   CSK_HIP(cs.get(&se, k), "table_topk: scratch");
-  CSK_HIP(cs.get(&rank, k), "table_topk: scratch");
   CSK_HIP(cs.get(&err, 1), "table_topk: scratch");
   CSK_HIP(launch_fill_u32(err, 1, 0u, st), "table_topk");
   // counts below 2^31 order as int32; empty slots (count 0, key all ones) are never gathered
-  CSK_HIP(launch_select_pairs(table_keys, (const int32_t*)table_counts, table_slots, k, sel, sk, se, rank, keys,
+  CSK_HIP(launch_select_pairs(table_keys, (const int32_t*)table_counts, table_slots, k, sel, sk, se, keys,
                               (int32_t*)counts, err, st),
           "table_topk");
-  SelState h;
-  CSK_HIP(hipMemcpyAsync(&h, sel, sizeof(SelState), hipMemcpyDeviceToHost, st), "table_topk");
+  uint32_t n_sel = 0;
+  CSK_HIP(hipMemcpyAsync(&n_sel, &sel->n_sel, sizeof(n_sel), hipMemcpyDeviceToHost, st), "table_topk");
   CSK_HIP(hipStreamSynchronize(st), "table_topk");
-  *k_out = h.n_sel < k ? h.n_sel : k;
+  *k_out = n_sel < k ? n_sel : k;
   return CSK_OK;
 }
 
@@ -1683,18 +1689,17 @@ csk_status csk_route_admit(const uint64_t* cells, const float* logits, uint64_t 
   SelState* sel = nullptr;
   uint64_t *sk = nullptr, *ok = nullptr;
   int32_t *se = nullptr, *oe = nullptr;
-  uint32_t *rank = nullptr, *err = nullptr;
+  uint32_t* err = nullptr;
   CSK_HIP(cs.get(&ord, m), "route_admit: scratch");
   CSK_HIP(cs.get(&sel, 1), "route_admit: scratch");
   CSK_HIP(cs.get(&sk, take), "route_admit: scratch");
   CSK_HIP(cs.get(&se, take), "route_admit: scratch");
   CSK_HIP(cs.get(&ok, take), "route_admit: scratch");
   CSK_HIP(cs.get(&oe, take), "route_admit: scratch");
-  CSK_HIP(cs.get(&rank, take), "route_admit: scratch");
   CSK_HIP(cs.get(&err, 1), "route_admit: scratch");
   CSK_HIP(launch_fill_u32(err, 1, 0u, st), "route_admit");
   CSK_HIP(launch_logit_order(logits, m, ord, st), "route_admit");
-  CSK_HIP(launch_select_pairs(cells, ord, (uint32_t)m, take, sel, sk, se, rank, ok, oe, err, st), "route_admit");
+  CSK_HIP(launch_select_pairs(cells, ord, (uint32_t)m, take, sel, sk, se, ok, oe, err, st), "route_admit");
   CSK_HIP(launch_rank_sort(ok, take, admitted, st), "route_admit");
   CSK_HIP(hipStreamSynchronize(st), "route_admit");
   *na = take;
@@ -1712,37 +1717,10 @@ csk_status csk_topk_with_table(csk_sketch* s, const uint64_t* table_keys, const 
   if (k > 0 && (keys == nullptr || est == nullptr)) return fail(CSK_E_INVALID, "topk_with_table: NULL output");
   if (k > s->max_cand) return fail(CSK_E_INVALID, "topk_with_table: k=%u above max_candidates", k);
   hipStream_t st = (hipStream_t)stream;
-  CSK_HIP(launch_table_to_set(table_keys, table_slots, s->set, s->slots - 1, s->set_count(), s->max_cand, s->err(), st),
-          "topk_with_table");
-  if (k > s->sel_cap) {
-    CSK_HIP(hipStreamSynchronize(st), "topk_with_table: grow scratch");
-    if (s->sel_key) (void)hipFree(s->sel_key);
-    if (s->sel_est) (void)hipFree(s->sel_est);
-    s->bytes -= (uint64_t)s->sel_cap * (sizeof(uint64_t) + sizeof(int32_t));
-    s->sel_key = nullptr;
-    s->sel_est = nullptr;
-    s->sel_cap = 0;
-    CSK_HIP(dmalloc(s, &s->sel_key, k), "topk_with_table: scratch");
-    CSK_HIP(dmalloc(s, &s->sel_est, k), "topk_with_table: scratch");
-    s->sel_cap = k;
-  }
-  if (k > 0) {
-    CSK_HIP(launch_topk(s->set, s->slots, s->tables(), s->M, s->max_cand, k, s->sel, s->cand_key, s->cand_est,
-                        s->sel_key, s->sel_est, keys, est, s->err(), st, table_keys, table_counts, table_slots - 1),
-            "topk_with_table");
-  }
-  CSK_HIP(hipMemcpyAsync(s->host_sel, s->sel, sizeof(SelState), hipMemcpyDeviceToHost, st), "topk_with_table");
-  uint32_t bits = 0;
-  csk_status rc = take_latch(s, st, &bits);
-  if (rc != CSK_OK) return rc;
-  rc = latch_status(bits);
-  if (rc != CSK_OK) return rc;
-  const uint32_t m = k ? s->host_sel->m : 0;
-  const uint32_t got = (k < m) ? k : m;
-  *k_out = got;
-  if (got < k && s->partial_set)
-    return fail(CSK_W_INCOMPLETE, "topk_with_table: only %u of %u candidates", got, k);
-  return CSK_OK;
+  CSK_HIP(launch_table_to_set(table_keys, table_slots, s->cand(), s->err(), st), "topk_with_table");
+  s->cand_likely += table_slots;
+  return topk_impl(s, k, keys, est, nullptr, k_out, ExactTable{table_keys, table_counts, table_slots - 1}, st,
+                   "topk_with_table");
 }
 
 // ---------------------------------------------------------------- the sync-free routed step
@@ -1751,10 +1729,10 @@ namespace {
 
 uint64_t align256(uint64_t b) { return (b + 255) & ~255ull; }
 
-// Admission scratch: SelState | ord (cap int32) | sk, ok (A uint64) | se, oe, rank (A words) | err.
+// Admission scratch: SelState | ord (cap int32) | sk, ok (A uint64) | se, oe (A words) | err.
 uint64_t admit_workspace_bytes(uint64_t cap, uint32_t A) {
   return align256(sizeof(SelState)) + align256(cap * 4) + 2 * align256((uint64_t)A * 8) +
-         3 * align256((uint64_t)A * 4) + 256;
+         2 * align256((uint64_t)A * 4) + 256;
 }
 
 // The most admitted cells an exclusion of this factor and table serves.
@@ -1775,29 +1753,9 @@ csk_status topk_with_table_impl(csk_sketch* s, const uint64_t* table_keys, const
     return fail(CSK_E_INVALID, "%s: table_slots=%u is not a power of two", who, table_slots);
   if (k > 0 && (keys == nullptr || est == nullptr)) return fail(CSK_E_INVALID, "%s: NULL output", who);
   if (k > s->max_cand) return fail(CSK_E_INVALID, "%s: k=%u above max_candidates", who, k);
-  CSK_HIP(launch_table_to_set(table_keys, table_slots, s->set, s->slots - 1, s->set_count(), s->max_cand, s->err(), st),
-          who);
-  if (k > s->sel_cap) {   // first call with a larger k: grow the scratch (synchronizes)
-    CSK_HIP(hipStreamSynchronize(st), who);
-    if (s->sel_key) (void)hipFree(s->sel_key);
-    if (s->sel_est) (void)hipFree(s->sel_est);
-    s->bytes -= (uint64_t)s->sel_cap * (sizeof(uint64_t) + sizeof(int32_t));
-    s->sel_key = nullptr;
-    s->sel_est = nullptr;
-    s->sel_cap = 0;
-    CSK_HIP(dmalloc(s, &s->sel_key, k), who);
-    CSK_HIP(dmalloc(s, &s->sel_est, k), who);
-    s->sel_cap = k;
-  }
-  if (k > 0) {
-    CSK_HIP(launch_topk(s->set, s->slots, s->tables(), s->M, s->max_cand, k, s->sel, s->cand_key, s->cand_est,
-                        s->sel_key, s->sel_est, keys, est, s->err(), st, table_keys, table_counts, table_slots - 1),
-            who);
-  } else {
-    CSK_HIP(launch_fill_u32((uint32_t*)s->sel, sizeof(SelState) / 4, 0u, st), who);
-  }
-  CSK_HIP(launch_topk_out(s->sel, k, s->partial_set ? 1u : 0u, out, st), who);
-  return CSK_OK;
+  CSK_HIP(launch_table_to_set(table_keys, table_slots, s->cand(), s->err(), st), who);
+  s->cand_likely += table_slots;
+  return topk_impl(s, k, keys, est, out, nullptr, ExactTable{table_keys, table_counts, table_slots - 1}, st, who);
 }
 
 }  // namespace
@@ -1873,12 +1831,10 @@ csk_status csk_route_admit_async(const uint64_t* cells, const float* logits, con
   w += align256((uint64_t)A * 4);
   int32_t* oe = (int32_t*)w;
   w += align256((uint64_t)A * 4);
-  uint32_t* rank = (uint32_t*)w;
-  w += align256((uint64_t)A * 4);
   uint32_t* err = (uint32_t*)w;
   hipStream_t st = (hipStream_t)stream;
   CSK_HIP(launch_fill_u32(err, 1, 0u, st), "route_admit_async");
-  CSK_HIP(launch_admit_dev(cells, logits, m, cap, A, ord, sel, sk, se, rank, ok, oe, err, admitted, na, st),
+  CSK_HIP(launch_admit_dev(cells, logits, m, cap, A, ord, sel, sk, se, ok, oe, err, admitted, na, st),
           "route_admit_async");
   return CSK_OK;
 }

@@ -317,14 +317,20 @@ __host__ __device__ __forceinline__ uint32_t key_chars(int32_t G) {
 template <int DP>
 __device__ __forceinline__ void stage_tables(uint32_t* ti, const uint32_t* __restrict__ src, uint32_t nch,
                                              uint32_t bytes = kChars) {
-  for (uint32_t i = threadIdx.x; i < (uint32_t)(256 * DP) * bytes; i += blockDim.x) {
-    uint32_t v = src[i];
-    const uint32_t c = i / (256 * DP);
-    if (c == nch - 1) {
-      const uint32_t r = i % DP;
-      for (uint32_t c2 = nch; c2 < (uint32_t)kChars; ++c2) v ^= src[(c2 * 256) * DP + r];
+  // 16 bytes per load; with 6 words per entry the words of a 16-byte piece lie in one key byte too
+  static_assert((256 * DP) % 4 == 0, "whole 16-byte pieces per key byte");
+  using V4 = uint32_t __attribute__((ext_vector_type(4)));
+  constexpr uint32_t per = 64u * DP;   // pieces per key byte
+  for (uint32_t i = threadIdx.x; i < per * bytes; i += blockDim.x) {
+    V4 v = ((const V4*)src)[i];
+    if (i / per == nch - 1) {
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        const uint32_t r = (4 * i + e) % DP;
+        for (uint32_t c2 = nch; c2 < (uint32_t)kChars; ++c2) v[e] ^= src[(c2 * 256) * DP + r];
+      }
     }
-    ti[i] = v;
+    ((V4*)ti)[i] = v;
   }
   __syncthreads();
 }

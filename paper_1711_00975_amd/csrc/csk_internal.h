@@ -9,17 +9,34 @@
 
 namespace csk {
 
-// Candidate selection state (one per handle, device memory).
+// Candidate selection state (one per handle, device memory).  Between selections the histogram
+// and the block count are zero: every pass leaves them so for the next.
+constexpr uint32_t kSelBins = 4096;
 struct SelState {
-  uint32_t m;           // candidates compacted from the set
+  uint32_t m;           // candidates of the selection
   uint32_t k_rem;       // items still to take inside the current class
-  uint32_t est_prefix;  // chosen high bits of (est ^ 0x80000000)
-  uint32_t est_mask;
-  uint64_t key_prefix;  // chosen high bits of the key among est == T
-  uint64_t key_mask;
+  uint32_t T;           // threshold: est ^ 0x80000000 of the k-th item, digit by digit
+  uint32_t ties_all;    // every item at the threshold is taken
   uint32_t n_sel;       // items gathered
-  uint32_t err;         // snapshot of the error latch, read back by the host
-  uint32_t hist[256];
+  uint32_t err;         // snapshot of the error latch
+  uint32_t done;        // blocks that have finished the pass
+  uint32_t pad;
+  uint64_t K;           // largest key taken among the items at the threshold
+  uint32_t hist[kSelBins];
+};
+// What a synchronizing top-k reads back (pinned host memory that the last kernel writes).
+struct SelHost {
+  uint32_t m;
+  uint32_t err;
+};
+// A handle's set of distinct candidate keys: open addressing, and the keys in the order of their
+// insertion as a list (list[0 .. min(*count, max_cand))).
+struct CandSet {
+  uint64_t* set;
+  uint32_t slot_mask;
+  uint32_t* count;
+  uint32_t max_cand;
+  uint64_t* list;
 };
 
 struct Tables {
@@ -261,10 +278,7 @@ struct CollectDesc {
   uint32_t* filter;           // Bloom filter (device) or NULL
   uint32_t* hot;              // its hot-item count
   uint32_t* hot_table;        // exact hot-item set or NULL
-  uint64_t* set;
-  uint32_t slot_mask;
-  uint32_t* set_count;
-  uint32_t max_cand;
+  CandSet cand;
   uint32_t* err;
 };
 // Per-call arguments of a batched candidate pass (kernel argument).
@@ -290,24 +304,26 @@ hipError_t launch_collect_batch(const CollectDesc* descs, const CollectDesc* hos
 // sketch has probe tables, d = 5 and the packed hash).
 hipError_t launch_collect(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const int32_t* M,
                           int32_t theta, const uint32_t* filter, const uint32_t* hot, const uint32_t* hot_table,
-                          uint64_t* set, uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand, uint32_t* err,
-                          bool field, hipStream_t s);
+                          const CandSet& cand, uint32_t* err, bool field, hipStream_t s);
+// Short streams: reading every row's counter for every particle takes less than building the filter
+// from all the counters and staging it.  Measured, clear and collect, exact reads against the filter:
+// d = 5: w = 2^16, 2^18 particles 32 and 70 us, 2^19 58 and 86, 2^20 271 and 214; w = 2^20, 2^19
+// 72 and 105, 2^20 131 and 132; w = 2^24, 2^20 156 and 206; d = 8, w = 2^16: 2^19 66 and 91, 2^20
+// 118 and 123.
+bool collect_is_short(uint64_t n, const Tables& t);
+hipError_t launch_collect_short(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const int32_t* M,
+                                int32_t theta, const CandSet& cand, uint32_t* err, hipStream_t s);
 // Candidate pass over every key in [0, nkeys) (the whole G^3 dictionary); arguments as
 // launch_collect without the positions.
 hipError_t launch_collect_dictionary(uint64_t nkeys, const Mesh& mesh, const Tables& t, const int32_t* M,
                                      int32_t theta, const uint32_t* filter, const uint32_t* hot,
-                                     const uint32_t* hot_table, uint64_t* set, uint32_t slot_mask,
-                                     uint32_t* set_count, uint32_t max_cand, uint32_t* err, hipStream_t s);
-// Hierarchical query, second layer: list the coarse set's super-items (list_count is
-// zeroed here; more than list_cap latches the capacity error in err), then insert every
-// child key of theirs whose fine estimate is >= theta into the fine set.
-hipError_t launch_collect_children(const uint64_t* coarse_set, uint32_t coarse_slots, uint64_t* list,
-                                   uint32_t* list_count, uint32_t list_cap, uint32_t group, uint64_t ncells,
-                                   const Tables& t, const int32_t* M, int32_t theta, uint64_t* set,
-                                   uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand, uint32_t* err,
-                                   hipStream_t s);
-// out[0] = min(k, candidates), out[1] = 1 if that is below k and `partial`, else 0.
-hipError_t launch_topk_out(const SelState* st, uint32_t k, uint32_t partial, uint32_t* out, hipStream_t s);
+                                     const uint32_t* hot_table, const CandSet& cand, uint32_t* err, hipStream_t s);
+// Hierarchical query, second layer: insert every child key of the coarse set's super-items (list,
+// *list_count; more than list_cap latches the capacity error in err) whose fine estimate is >=
+// theta into the fine set.
+hipError_t launch_collect_children(const uint64_t* list, const uint32_t* list_count, uint32_t list_cap, uint32_t group,
+                                   uint64_t ncells, const Tables& t, const int32_t* M, int32_t theta,
+                                   const CandSet& cand, uint32_t* err, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
 // Up to kFillSpans spans of 32-bit words, span r set to v[r], in one launch (the clears of a
@@ -327,25 +343,25 @@ struct ResetSpans {
   uint32_t v[kMaxBatch][kFillSpans];
 };
 hipError_t launch_fill_spans_batch(const ResetSpans* spans, uint32_t count, uint64_t max_words, hipStream_t s);
+// The top-k of a candidate list (*count keys, at most max_cand) from the current counters: winners
+// in ok / oe; ce (max_cand), sk / se (k) scratch.  out (device, may be NULL) gets min(k, m) and the
+// incomplete flag (fewer than k from a partial set), *host (pinned, may be NULL) m and the latch.
+// likely: candidates that the host expects at most (it chooses between forms, any count is right).
 // ov_keys / ov_counts / ov_mask: an exact table whose counts replace the estimates of the
 // candidates found in it (NULL: none).
-hipError_t launch_topk(const uint64_t* set, uint32_t slots, const Tables& t, const int32_t* M,
-                       uint32_t max_cand, uint32_t k, SelState* st, uint64_t* cand_key, int32_t* cand_est,
-                       uint64_t* sel_key, int32_t* sel_est, uint64_t* out_key, int32_t* out_est,
-                       const uint32_t* err, hipStream_t s, const uint64_t* ov_keys = nullptr,
-                       const uint32_t* ov_counts = nullptr, uint32_t ov_mask = 0);
-// Top k of the m pairs (ck[i], ce[i]) in (ce desc, ck asc) order, keys distinct and below
-// 2^48 (equal keys only where they cannot reach the top k): winners in ok / oe, ranks in
-// `rank` (k words), sk / se (k) scratch.
+hipError_t launch_topk(const uint64_t* list, const uint32_t* count, const Tables& t, const int32_t* M,
+                       uint32_t max_cand, uint64_t likely, uint32_t k, SelState* st, int32_t* ce, uint64_t* sk,
+                       int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err, uint32_t partial, uint32_t* out,
+                       SelHost* host, hipStream_t s, const uint64_t* ov_keys = nullptr, const uint32_t* ov_counts = nullptr,
+                       uint32_t ov_mask = 0);
 // One sketch of a batched top-k (device array, built once per batch).
 struct TopkDesc {
-  const uint64_t* set;
-  uint32_t slots;
+  const uint64_t* list;
+  const uint32_t* count;
   uint32_t max_cand;
   Tables t;
   const int32_t* M;
   SelState* st;
-  uint64_t* ck;
   int32_t* ce;
   uint64_t* sk;
   int32_t* se;
@@ -359,20 +375,21 @@ struct TopkCall {
   uint32_t* out[kMaxBatch];
   uint32_t k[kMaxBatch];
   uint32_t partial[kMaxBatch];
-  uint32_t key32[kMaxBatch];   // 1: the sketch's keys are below 2^32 (G^3 <= 2^32)
 };
-hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint32_t slots_max,
-                             uint32_t max_cand_max, uint32_t k_max, const TopkCall& call, hipStream_t s);
+hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint32_t max_cand_max, uint32_t k_max,
+                             const TopkCall& call, hipStream_t s);
 
+// Top k of the m pairs (ck[i], ce[i]) in (ce desc, ck asc) order, keys distinct and below
+// 2^48 (equal keys only where they cannot reach the top k): winners in ok / oe, their number in
+// st->n_sel; sk / se (k) scratch, *st any contents.
 hipError_t launch_select_pairs(const uint64_t* ck, const int32_t* ce, uint32_t m, uint32_t k, SelState* st,
-                               uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok, int32_t* oe,
-                               const uint32_t* err, hipStream_t s);
+                               uint64_t* sk, int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err,
+                               hipStream_t s);
 // The same over the first min(*m_dev, cap) pairs of a device count.
 hipError_t launch_select_pairs_dev(const uint64_t* ck, const int32_t* ce, const uint64_t* m_dev, uint32_t cap,
-                                   uint32_t k, SelState* st, uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok,
+                                   uint32_t k, SelState* st, uint64_t* sk, int32_t* se, uint64_t* ok,
                                    int32_t* oe, const uint32_t* err, hipStream_t s);
 // Insert every non-empty key of an exact table (tslots slots) into a candidate set.
-hipError_t launch_table_to_set(const uint64_t* tk, uint32_t tslots, uint64_t* set, uint32_t slot_mask,
-                               uint32_t* set_count, uint32_t max_cand, uint32_t* err, hipStream_t s);
+hipError_t launch_table_to_set(const uint64_t* tk, uint32_t tslots, const CandSet& cand, uint32_t* err, hipStream_t s);
 
 }  // namespace csk

@@ -119,24 +119,26 @@ __device__ __forceinline__ bool set_contains(const uint64_t* set, uint32_t mask,
   return false;
 }
 
-__device__ __forceinline__ void set_insert(uint64_t* set, uint32_t mask, uint64_t key, uint32_t* count,
-                                           uint32_t max_cand, uint32_t* err) {
+__device__ __forceinline__ void set_insert(const CandSet& c, uint64_t key, uint32_t* err) {
+  const uint32_t mask = c.slot_mask;
   uint32_t i = (uint32_t)slot_mix(key) & mask;
   for (uint32_t probe = 0; probe <= mask && probe < kMaxProbe; ++probe) {
     // A slot only ever changes from empty to a key, so a stale read can only show
     // "empty"; the compare-and-swap then tells the truth.
-    const uint64_t cur = set[i];
+    const uint64_t cur = c.set[i];
     if (cur == key) return;
     if (cur == kEmptyKey) {
       // a new key: once the set holds max_candidates keys no more go in (capacity error)
-      if (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= max_cand) {
+      if (__hip_atomic_load(c.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= c.max_cand) {
         atomicOr(err, kErrCapacity);
         return;
       }
-      const uint64_t old = atomicCAS((unsigned long long*)&set[i], (unsigned long long)kEmptyKey,
+      const uint64_t old = atomicCAS((unsigned long long*)&c.set[i], (unsigned long long)kEmptyKey,
                                      (unsigned long long)key);
       if (old == kEmptyKey) {
-        if (atomicAdd(count, 1u) >= max_cand) atomicOr(err, kErrCapacity);
+        const uint32_t at = atomicAdd(c.count, 1u);
+        if (at < c.max_cand) c.list[at] = key;
+        else atomicOr(err, kErrCapacity);
         return;
       }
       if (old == key) return;

@@ -92,8 +92,7 @@ __global__ __launch_bounds__(kCollectThreads) void dict_collect_kernel(uint64_t 
                                                                        const uint32_t* __restrict__ hot,
                                                                        uint32_t use_filter,
                                                                        const uint32_t* __restrict__ hot_table,
-                                                                       uint64_t* set, uint32_t slot_mask,
-                                                                       uint32_t* set_count, uint32_t max_cand,
+                                                                       CandSet cand,
                                                                        uint32_t* err) {
   constexpr int DP = HashWords<D, HM>::value;
   extern __shared__ __align__(16) uint32_t lds4[];
@@ -147,15 +146,14 @@ __global__ __launch_bounds__(kCollectThreads) void dict_collect_kernel(uint64_t 
         if ((int32_t)(ng[r] ? 0u - c : c) >= theta) ++pass;
       }
     }
-    if (pass >= need) set_insert(set, slot_mask, key, set_count, max_cand, err);
+    if (pass >= need) set_insert(cand, key, err);
   }
 }
 
 // The same for any d, with row-major tables read from global memory (d > 8).
 __global__ __launch_bounds__(256) void dict_collect_generic_kernel(uint64_t nkeys, Tables t,
                                                                    const int32_t* __restrict__ M, int32_t theta,
-                                                                   uint64_t* set, uint32_t slot_mask,
-                                                                   uint32_t* set_count, uint32_t max_cand,
+                                                                   CandSet cand,
                                                                    uint32_t* err) {
   const uint32_t need = t.cm ? t.d : t.d - ((t.d - 1) >> 1);
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -165,41 +163,21 @@ __global__ __launch_bounds__(256) void dict_collect_generic_kernel(uint64_t nkey
       if (pass >= need || pass + (t.d - r) < need) break;
       if (row_estimate(t.tab + r * kTableWords, M + (uint64_t)r * t.w, t.w, t.cm, key) >= theta) ++pass;
     }
-    if (pass >= need) set_insert(set, slot_mask, key, set_count, max_cand, err);
-  }
-}
-
-// The keys of a candidate set as a list (order unspecified): out[0 .. *count).  At most
-// `cap` are written; more keys than that latches the capacity error in *err.
-__global__ __launch_bounds__(256) void set_list_kernel(const uint64_t* __restrict__ set, uint32_t slots,
-                                                       uint64_t* __restrict__ out, uint32_t* count, uint32_t cap,
-                                                       uint32_t* err) {
-  for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < slots; i0 += gridDim.x * blockDim.x) {
-    const uint32_t i = i0 + threadIdx.x;
-    const uint64_t key = (i < slots) ? set[i] : kEmptyKey;
-    const bool have = key != kEmptyKey;
-    const uint32_t slot = wave_append(count, have);
-    if (have) {
-      if (slot < cap) out[slot] = key;
-      else atomicOr(err, kErrCapacity);
-    }
+    if (pass >= need) set_insert(cand, key, err);
   }
 }
 
 // Every key of the router's exact table joins a candidate set.
-__global__ __launch_bounds__(256) void table_to_set_kernel(const uint64_t* __restrict__ tk, uint32_t tslots, uint64_t* set,
-                                                           uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand,
+__global__ __launch_bounds__(256) void table_to_set_kernel(const uint64_t* __restrict__ tk, uint32_t tslots, CandSet cand,
                                                            uint32_t* err) {
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < tslots; i += gridDim.x * blockDim.x) {
     const uint64_t key = tk[i];
-    if (key != kEmptyKey) set_insert(set, slot_mask, key, set_count, max_cand, err);
+    if (key != kEmptyKey) set_insert(cand, key, err);
   }
 }
 
-hipError_t launch_table_to_set(const uint64_t* tk, uint32_t tslots, uint64_t* set, uint32_t slot_mask,
-                               uint32_t* set_count, uint32_t max_cand, uint32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(table_to_set_kernel, dim3(grid_for(tslots, 256, 1024)), dim3(256), 0, s, tk, tslots, set,
-                     slot_mask, set_count, max_cand, err);
+hipError_t launch_table_to_set(const uint64_t* tk, uint32_t tslots, const CandSet& cand, uint32_t* err, hipStream_t s) {
+  hipLaunchKernelGGL(table_to_set_kernel, dim3(grid_for(tslots, 256, 1024)), dim3(256), 0, s, tk, tslots, cand, err);
   return hipGetLastError();
 }
 
@@ -211,8 +189,7 @@ template <int MAXD, bool TAB_LDS>
 __global__ __launch_bounds__(256) void children_kernel(const uint64_t* __restrict__ list,
                                                        const uint32_t* __restrict__ count, uint32_t cap,
                                                        uint32_t group, uint64_t ncells, Tables t,
-                                                       const int32_t* __restrict__ M, int32_t theta, uint64_t* set,
-                                                       uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand,
+                                                       const int32_t* __restrict__ M, int32_t theta, CandSet cand,
                                                        uint32_t* err) {
   __shared__ uint32_t tabs_lds[TAB_LDS ? kTabLdsRows * kTableWords : 1];
   const uint32_t* tabs = t.tab;
@@ -222,74 +199,66 @@ __global__ __launch_bounds__(256) void children_kernel(const uint64_t* __restric
     tabs = tabs_lds;
   }
   const uint32_t m = min(*count, cap);
+  if (*count > cap && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, kErrCapacity);
   for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
     const uint64_t lo = list[i] * group;
     const uint64_t hi = (lo + group < ncells) ? lo + group : ncells;
     for (uint64_t c = lo + threadIdx.x; c < hi; c += blockDim.x)
-      if (estimate_key<MAXD>(tabs, M, t.d, t.w, t.cm, c) >= theta) set_insert(set, slot_mask, c, set_count, max_cand, err);
+      if (estimate_key<MAXD>(tabs, M, t.d, t.w, t.cm, c) >= theta) set_insert(cand, c, err);
   }
 }
 
-hipError_t launch_collect_children(const uint64_t* coarse_set, uint32_t coarse_slots, uint64_t* list,
-                                   uint32_t* list_count, uint32_t list_cap, uint32_t group, uint64_t ncells,
-                                   const Tables& t, const int32_t* M, int32_t theta, uint64_t* set,
-                                   uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand, uint32_t* err,
-                                   hipStream_t s) {
-  hipError_t e = launch_fill_u32(list_count, 1, 0u, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(set_list_kernel, dim3(grid_for(coarse_slots, 256, 4096)), dim3(256), 0, s, coarse_set,
-                     coarse_slots, list, list_count, list_cap, err);
+hipError_t launch_collect_children(const uint64_t* list, const uint32_t* list_count, uint32_t list_cap, uint32_t group,
+                                   uint64_t ncells, const Tables& t, const int32_t* M, int32_t theta,
+                                   const CandSet& cand, uint32_t* err, hipStream_t s) {
   const dim3 grid(2048), block(256);
   if (t.d <= (uint32_t)kTabLdsRows)
     hipLaunchKernelGGL((children_kernel<kTabLdsRows, true>), grid, block, 0, s, list, list_count, list_cap, group,
-                       ncells, t, M, theta, set, slot_mask, set_count, max_cand, err);
+                       ncells, t, M, theta, cand, err);
   else
     hipLaunchKernelGGL((children_kernel<32, false>), grid, block, 0, s, list, list_count, list_cap, group, ncells, t,
-                       M, theta, set, slot_mask, set_count, max_cand, err);
+                       M, theta, cand, err);
   return hipGetLastError();
 }
 
 template <int D, int HM>
 static void launch_dict_one(dim3 grid, dim3 block, size_t lds, hipStream_t s, uint64_t nkeys, const Mesh& mesh,
                             const Tables& t, const int32_t* M, int32_t theta, const uint32_t* filter,
-                            const uint32_t* hot, uint32_t use_filter, const uint32_t* hot_table, uint64_t* set,
-                            uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand, uint32_t* err) {
+                            const uint32_t* hot, uint32_t use_filter, const uint32_t* hot_table, CandSet cand, uint32_t* err) {
   hipLaunchKernelGGL((dict_collect_kernel<D, HM>), grid, block, lds, s, nkeys, mesh, t, M, theta, filter, hot,
-                     use_filter, hot_table, set, slot_mask, set_count, max_cand, err);
+                     use_filter, hot_table, cand, err);
 }
 
 template <int D>
 static void launch_dict_d(int hm, dim3 grid, dim3 block, size_t lds, hipStream_t s, uint64_t nkeys, const Mesh& mesh,
                           const Tables& t, const int32_t* M, int32_t theta, const uint32_t* filter,
-                          const uint32_t* hot, uint32_t use_filter, const uint32_t* hot_table, uint64_t* set,
-                          uint32_t slot_mask, uint32_t* set_count, uint32_t max_cand, uint32_t* err) {
+                          const uint32_t* hot, uint32_t use_filter, const uint32_t* hot_table, CandSet cand, uint32_t* err) {
   if constexpr (D >= 5) {
     if (hm == kHashPacked) {
       launch_dict_one<D, kHashPacked>(grid, block, lds, s, nkeys, mesh, t, M, theta, filter, hot, use_filter,
-                                      hot_table, set, slot_mask, set_count, max_cand, err);
+                                      hot_table, cand, err);
       return;
     }
   }
   if (hm == kHashMulHi)
     launch_dict_one<D, kHashMulHi>(grid, block, lds, s, nkeys, mesh, t, M, theta, filter, hot, use_filter, hot_table,
-                                   set, slot_mask, set_count, max_cand, err);
+                                   cand, err);
   else
     launch_dict_one<D, kHashShift>(grid, block, lds, s, nkeys, mesh, t, M, theta, filter, hot, use_filter, hot_table,
-                                   set, slot_mask, set_count, max_cand, err);
+                                   cand, err);
 }
 
 hipError_t launch_collect_dictionary(uint64_t nkeys, const Mesh& mesh, const Tables& t, const int32_t* M,
                                      int32_t theta, const uint32_t* filter, const uint32_t* hot,
-                                     const uint32_t* hot_table, uint64_t* set, uint32_t slot_mask,
-                                     uint32_t* set_count, uint32_t max_cand, uint32_t* err, hipStream_t s) {
+                                     const uint32_t* hot_table, const CandSet& cand, uint32_t* err, hipStream_t s) {
   if (t.d <= (uint32_t)kTabLdsRows) {
     const uint32_t use_filter = (filter != nullptr && hot != nullptr) ? 1u : 0u;
     const size_t lds = ((size_t)kTableWords * t.dp + (use_filter ? kFilterWords : 0)) * sizeof(uint32_t);
     const dim3 grid(grid_for(nkeys, kCollectThreads, 1024)), block(kCollectThreads);
     const int hm = t.hash_mode();
 #define CSK_DICT(DD)                                                                                    \
-  launch_dict_d<DD>(hm, grid, block, lds, s, nkeys, mesh, t, M, theta, filter, hot, use_filter, hot_table, set, \
-                    slot_mask, set_count, max_cand, err)
+  launch_dict_d<DD>(hm, grid, block, lds, s, nkeys, mesh, t, M, theta, filter, hot, use_filter, hot_table, cand, \
+                    err)
     switch (t.d) {
       case 1: CSK_DICT(1); break;
       case 2: CSK_DICT(2); break;
@@ -303,7 +272,7 @@ hipError_t launch_collect_dictionary(uint64_t nkeys, const Mesh& mesh, const Tab
 #undef CSK_DICT
   } else {
     hipLaunchKernelGGL(dict_collect_generic_kernel, dim3(grid_for(nkeys, 256, 8192)), dim3(256), 0, s, nkeys, t, M,
-                       theta, set, slot_mask, set_count, max_cand, err);
+                       theta, cand, err);
   }
   return hipGetLastError();
 }
@@ -329,56 +298,65 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Word i of the concatenated spans goes to the span it falls in (spans of length 0 are skipped).
-__global__ void fill_spans_kernel(FillSpans f) {
-  const uint64_t total = f.n[0] + f.n[1] + f.n[2] + f.n[3];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    uint64_t j = i;
-    int r = 0;
-    while (r < kFillSpans - 1 && j >= f.n[r]) {
-      j -= f.n[r];
-      ++r;
-    }
-    f.p[r][j] = f.v[r];
-  }
+// n words of p set to v by the threads i, i + stride, ...: 16 bytes per store between the (fewer
+// than four) words before the first 16-byte boundary and those after the last.
+__device__ __forceinline__ void fill_span(uint32_t* __restrict__ p, uint64_t n, uint32_t v, uint64_t i, uint64_t stride) {
+  using V4 = uint32_t __attribute__((ext_vector_type(4)));
+  uint64_t head = ((16u - ((uintptr_t)p & 15u)) & 15u) / 4u;
+  head = head < n ? head : n;
+  const uint64_t quads = (n - head) / 4, rest = n - head - 4 * quads;
+  V4* q = (V4*)(p + head);
+  const V4 x = {v, v, v, v};
+  for (uint64_t j = i; j < quads; j += stride) q[j] = x;
+  if (i < head) p[i] = v;
+  if (i < rest) p[head + 4 * quads + i] = v;
 }
-__global__ void fill_spans_batch_kernel(const ResetSpans* __restrict__ sp) {
+__global__ __launch_bounds__(256) void fill_spans_kernel(FillSpans f) {
+  for (int r = 0; r < kFillSpans; ++r)
+    if (f.n[r])
+      fill_span(f.p[r], f.n[r], f.v[r], (uint64_t)blockIdx.x * 256 + threadIdx.x, (uint64_t)gridDim.x * 256);
+}
+__global__ __launch_bounds__(256) void fill_spans_batch_kernel(const ResetSpans* __restrict__ sp) {
   const uint32_t y = blockIdx.y;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (int r = 0; r < kFillSpans; ++r) {
-    uint32_t* __restrict__ p = sp->p[y][r];
-    const uint64_t n = sp->n[y][r];
-    const uint32_t v = sp->v[y][r];
-    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) p[j] = v;
-  }
+  for (int r = 0; r < kFillSpans; ++r)
+    if (sp->n[y][r])
+      fill_span(sp->p[y][r], sp->n[y][r], sp->v[y][r], (uint64_t)blockIdx.x * 256 + threadIdx.x, (uint64_t)gridDim.x * 256);
 }
 hipError_t launch_fill_spans_batch(const ResetSpans* spans, uint32_t count, uint64_t max_words, hipStream_t s) {
   if (count == 0 || max_words == 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_spans_batch_kernel, dim3(grid_for(max_words, 256, 1024), count), dim3(256), 0, s, spans);
+  hipLaunchKernelGGL(fill_spans_batch_kernel, dim3(grid_for(max_words, 1024, 1024), count), dim3(256), 0, s, spans);
   return hipGetLastError();
 }
 hipError_t launch_fill_spans(const FillSpans& f, hipStream_t s) {
   uint64_t total = 0;
   for (int r = 0; r < kFillSpans; ++r) total += f.n[r];
   if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_spans_kernel, dim3(grid_for(total, 256, 4096)), dim3(256), 0, s, f);
+  hipLaunchKernelGGL(fill_spans_kernel, dim3(grid_for(total, 1024, 4096)), dim3(256), 0, s, f);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ top-k
+//
+// Radix select on (estimate desc, key asc) over the candidate list that the inserts keep: three
+// digits of the estimate (11 + 11 + 10 bits), four of the key among the ties (12 bits each), one
+// launch per digit -- a histogram per block in LDS, summed in device memory, and the block that
+// finishes last picks the digit -- then a gather and a rank placement.  A pass is bound by its
+// launch and one memory round trip, so the launches are what counts: 9 in place of 28 (compaction
+// of the set, a histogram and a pick launch for each of ten 8-bit digits, and five more).  Only as
+// many blocks as the candidates need take part; when every tie at the threshold is taken the
+// key passes return at once.
 
-__device__ __forceinline__ void sel_init_body(SelState* st) {
-  uint32_t* w = (uint32_t*)st;
-  for (uint32_t i = threadIdx.x; i < sizeof(SelState) / 4; i += blockDim.x) w[i] = 0;
+constexpr uint32_t kSelThreads = 1024;
+constexpr uint32_t kSelItems = 4096;      // candidates per block before another block joins in
+constexpr uint32_t kSelGrid = 512;
+constexpr uint64_t kOneBlock = 8192;      // candidates at most for the selection in one block
+constexpr uint64_t kKeyMax = (1ull << 48) - 1;
+
+__device__ __forceinline__ uint32_t sel_blocks(uint32_t m) {
+  const uint32_t b = m / kSelItems + (m % kSelItems ? 1u : 0u);
+  return min(max(b, 1u), (uint32_t)gridDim.x);
 }
-__global__ void sel_init_kernel(SelState* st) { sel_init_body(st); }
 
-// Distinct keys of the set -> (key, estimate from the current counters).  Each block stages
-// the d hash tables (up to 30 KiB) in LDS and then walks kCompactSlots slots per thread, so
-// that the staging is paid once per 4096 slots rather than per 256 (with 2048 blocks per
-// sketch of 2^19 slots, a batch of 64 read 3.9 GB of tables from L2 for its compaction).
-constexpr uint32_t kCompactSlots = 16;
 // Exact count of key in the router's table (linear probing from table_slot), or -1.
 __device__ __forceinline__ int64_t table_count(const uint64_t* __restrict__ tk, const uint32_t* __restrict__ tc,
                                                uint32_t tmask, uint64_t key) {
@@ -392,145 +370,186 @@ __device__ __forceinline__ int64_t table_count(const uint64_t* __restrict__ tk, 
   return -1;
 }
 
-// With an exact table (ov_keys != NULL), a candidate found in it takes its exact count
-// as its estimate (the learned router's table; counts of up to 2^31 - 1).
-template <int MAXD, bool TAB_LDS>
-__device__ __forceinline__ void compact_body(const uint64_t* __restrict__ set, uint32_t slots, Tables t,
-                                                      const int32_t* __restrict__ M, uint32_t max_cand,
-                                                      SelState* st, uint64_t* __restrict__ ck,
-                                                      int32_t* __restrict__ ce, const uint64_t* __restrict__ ov_keys,
-                                                      const uint32_t* __restrict__ ov_counts, uint32_t ov_mask) {
-  __shared__ uint32_t tabs_lds[TAB_LDS ? kTabLdsRows * kTableWords : 1];
-  if (blockIdx.x * blockDim.x >= slots) return;   // no slot here (uniform): skip the table staging
-  const uint32_t* tabs = t.tab;
-  if (TAB_LDS) {
-    load_tables(tabs_lds, t.tab, t.d);
-    __syncthreads();
-    tabs = tabs_lds;
-  }
-  for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < slots; i0 += gridDim.x * blockDim.x) {
-    const uint32_t i = i0 + threadIdx.x;
-    const uint64_t key = (i < slots) ? set[i] : kEmptyKey;
-    const bool have = key != kEmptyKey;
-    const uint32_t slot = wave_append(&st->m, have);
-    if (have && slot < max_cand) {
-      ck[slot] = key;
-      const int64_t exact = ov_keys ? table_count(ov_keys, ov_counts, ov_mask, key) : -1;
-      ce[slot] = exact >= 0 ? (int32_t)exact : estimate_key<MAXD>(tabs, M, t.d, t.w, t.cm, key);
-    }
-  }
-}
-template <int MAXD, bool TAB_LDS>
-__global__ __launch_bounds__(256) void compact_kernel(const uint64_t* __restrict__ set, uint32_t slots, Tables t,
-                                                      const int32_t* __restrict__ M, uint32_t max_cand,
-                                                      SelState* st, uint64_t* __restrict__ ck,
-                                                      int32_t* __restrict__ ce, const uint64_t* __restrict__ ov_keys,
-                                                      const uint32_t* __restrict__ ov_counts, uint32_t ov_mask) {
-  compact_body<MAXD, TAB_LDS>(set, slots, t, M, max_cand, st, ck, ce, ov_keys, ov_counts, ov_mask);
+// Is this the last of the `blocks` blocks of a pass to get here?  What the others added to the
+// histogram is there when it is: the adds are device-scope atomics, and each wave waits for its
+// own before the block counts itself.  (A device-scope fence in every block instead writes back
+// the XCD's L2: 350 us a pass for 64 sketches.)  Every thread of the block calls it.
+__device__ __forceinline__ bool last_block(SelState* st, uint32_t blocks) {
+  __shared__ uint32_t last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == blocks - 1u ? 1u : 0u;
+  __syncthreads();
+  return last != 0u;
 }
 
-__device__ __forceinline__ void clamp_m_body(SelState* st, uint32_t max_cand) {
-  if (threadIdx.x == 0 && st->m > max_cand) st->m = max_cand;
-}
-__global__ void clamp_m_kernel(SelState* st, uint32_t max_cand) { clamp_m_body(st, max_cand); }
-
-// Histogram of one 8-bit digit over the current class (stage 1: est; stage 2: key
-// among est == T).
-template <bool KEYS>
-__device__ __forceinline__ void sel_hist_body(const uint64_t* __restrict__ ck, const int32_t* __restrict__ ce,
-                                                       SelState* st, int shift) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t m = st->m;
-  const uint32_t epre = st->est_prefix, emask = st->est_mask;
-  const uint64_t kpre = st->key_prefix, kmask = st->key_mask;
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
-    const uint32_t u = (uint32_t)ce[i] ^ 0x80000000u;
-    if (!KEYS) {
-      if ((u & emask) == epre) atomicAdd(&h[(u >> shift) & 255u], 1u);
-    } else {
-      const uint64_t k = ck[i];
-      if (u == epre && (k & kmask) == kpre) atomicAdd(&h[(uint32_t)(k >> shift) & 255u], 1u);
-    }
-  }
-  __syncthreads();
-  if (h[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], h[threadIdx.x]);
-}
-template <bool KEYS>
-__global__ __launch_bounds__(256) void sel_hist_kernel(const uint64_t* __restrict__ ck, const int32_t* __restrict__ ce,
-                                                       SelState* st, int shift) {
-  sel_hist_body<KEYS>(ck, ce, st, shift);
-}
-
-// Pick the digit holding the k_rem-th item: descending for estimates, ascending for keys.
-// One wave: position q of the scan order is digit 255 - q (estimates) or q (keys); lane l
-// holds positions 4l .. 4l + 3.  The chosen position is the first whose inclusive prefix
-// count reaches k_rem, or the last one (255) when none does; k_rem becomes k_rem minus the
-// count before it.  The histogram is cleared for the next pass.
-template <bool KEYS>
-__device__ __forceinline__ void sel_pick_body(SelState* st, uint32_t k, int shift) {
-  const uint32_t lane = threadIdx.x;
-  if (!KEYS && shift == 24 && lane == 0) st->k_rem = min(k, st->m);
-  __syncthreads();
-  const uint32_t need = st->k_rem;
-  uint32_t h[4], sum = 0;
+// The bin of a histogram that holds the need-th item: the first whose inclusive count reaches it
+// (the last bin, with nothing before it, when none does), the count before it and its own count.
+// `global`: the histogram is a pass's, summed by several blocks.  Every thread of the block calls it.
+struct SelDigit {
+  uint32_t bin, before, here;
+};
+template <int BITS>
+__device__ __forceinline__ SelDigit sel_digit(const uint32_t* hist, bool global, uint32_t need) {
+  constexpr uint32_t NB = 1u << BITS, PER = NB / kSelThreads;
+  static_assert(PER >= 1 && NB <= kSelBins, "whole bins per thread");
+  __shared__ uint32_t wsum[kSelThreads / 64];
+  __shared__ SelDigit found;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6;
+  uint32_t h[PER], sum = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t q = lane * 4 + (uint32_t)e;
-    h[e] = st->hist[KEYS ? q : 255u - q];
+  for (uint32_t e = 0; e < PER; ++e) {
+    h[e] = global ? __hip_atomic_load(&hist[tid * PER + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                  : hist[tid * PER + e];
     sum += h[e];
   }
   const uint32_t incl = wave_incl_scan(sum);
-  if (need > 0) {
-    const uint64_t hit = __ballot(incl >= need);
-    const uint32_t lead = hit ? (uint32_t)__ffsll((unsigned long long)hit) - 1u : 63u;
-    if (lane == lead) {
-      uint32_t cum = incl - sum, q = lane * 4;
+  if (lane_id() == 63) wsum[wave] = incl;
+  if (tid == 0) found = SelDigit{NB - 1u, 0u, 0u};
+  __syncthreads();
+  uint32_t cum = incl - sum, total = 0;
+  for (uint32_t w = 0; w < kSelThreads / 64; ++w) {
+    cum += w < wave ? wsum[w] : 0u;
+    total += wsum[w];
+  }
+  if (need > 0 && need <= total && cum < need && need <= cum + sum) {
+    uint32_t e = 0, here = h[0];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        q = lane * 4 + (uint32_t)e;
-        if (q == 255u || cum + h[e] >= need) break;
-        cum += h[e];
+    for (uint32_t q = 0; q + 1 < PER; ++q)
+      if (e == q && cum + h[q] < need) {
+        cum += h[q];
+        e = q + 1;
+        here = h[q + 1];
       }
-      const uint32_t dg = KEYS ? q : 255u - q;
-      if (!KEYS) {
-        st->est_prefix |= dg << shift;
-        st->est_mask |= 255u << shift;
-      } else {
-        st->key_prefix |= (uint64_t)dg << shift;
-        st->key_mask |= 255ull << shift;
-      }
-      st->k_rem = need - cum;
-    }
+    found = SelDigit{tid * PER + e, cum, here};
   }
   __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 4; ++e) st->hist[lane * 4 + (uint32_t)e] = 0;
-}
-template <bool KEYS>
-__global__ __launch_bounds__(64) void sel_pick_kernel(SelState* st, uint32_t k, int shift) {
-  sel_pick_body<KEYS>(st, k, shift);
+  const SelDigit f = found;
+  __syncthreads();   // read before the next call writes it
+  return f;
 }
 
-// Winners: est > T, or est == T and key <= K (T, K from the two stages).
+// Add the block's histogram to the pass's and, in the last block, pick the digit and move the state
+// on (bins are in the order of the selection: estimates descending).  The last block leaves the
+// histogram and the block count zero.  FIRST: m and k start the selection.
+template <int SHIFT, int BITS, bool KEYS, bool FIRST>
+__device__ __forceinline__ void sel_finish_pass(SelState* st, const uint32_t* h, uint32_t m, uint32_t k, uint32_t blocks) {
+  constexpr uint32_t NB = 1u << BITS;
+  __syncthreads();
+  const bool global = blocks > 1;
+  if (global) {
+    for (uint32_t b = threadIdx.x; b < NB; b += kSelThreads)
+      if (h[b]) __hip_atomic_fetch_add(&st->hist[b], h[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_block(st, blocks)) return;
+  }
+  const uint32_t need = FIRST ? min(k, m) : st->k_rem;
+  const SelDigit f = sel_digit<BITS>(global ? st->hist : h, global, need);
+  if (threadIdx.x == 0) {
+    const uint32_t digit = KEYS ? f.bin : NB - 1u - f.bin;
+    const uint32_t rem = need - f.before;
+    st->k_rem = rem;
+    if (!KEYS) {
+      st->T = (FIRST ? 0u : st->T) | (digit << SHIFT);
+      if (SHIFT == 0) {   // the threshold is known: the key passes are needed when not every tie is taken
+        st->ties_all = f.here == rem ? 1u : 0u;
+        st->K = f.here == rem ? kKeyMax : 0ull;
+      }
+    } else {
+      st->K |= (uint64_t)digit << SHIFT;
+    }
+    if (FIRST) {
+      st->m = m;
+      st->n_sel = 0;
+    }
+    st->done = 0;
+  }
+  if (global)
+    for (uint32_t b = threadIdx.x; b < NB; b += kSelThreads) st->hist[b] = 0;
+}
+
+// First pass of a sketch's top-k: the candidates' estimates from the current counters (with an
+// exact table, ov_keys != NULL, a candidate found in it takes its exact count, up to 2^31 - 1) and
+// the histogram of their top digit.  The d hash tables (up to 30 KiB) are staged in LDS when there
+// are enough candidates to pay for it.
+template <int MAXD>
+__device__ __forceinline__ void sel_estimate_body(const uint64_t* __restrict__ list, const uint32_t* __restrict__ count,
+                                                  uint32_t max_cand, const Tables& t, const int32_t* __restrict__ M,
+                                                  uint32_t k, SelState* st, int32_t* __restrict__ ce,
+                                                  const uint64_t* __restrict__ ov_keys,
+                                                  const uint32_t* __restrict__ ov_counts, uint32_t ov_mask) {
+  constexpr bool LDS = MAXD <= kTabLdsRows;
+  __shared__ uint32_t tabs_lds[LDS ? kTabLdsRows * kTableWords : 1];
+  __shared__ uint32_t h[1 << 11];
+  const uint32_t m = min(*count, max_cand), blocks = sel_blocks(m);
+  if (blockIdx.x >= blocks) return;
+  for (uint32_t b = threadIdx.x; b < (1u << 11); b += kSelThreads) h[b] = 0;
+  const bool staged = LDS && m > 8192u;
+  if (staged) load_tables(tabs_lds, t.tab, t.d);
+  __syncthreads();
+  for (uint32_t i = blockIdx.x * kSelThreads + threadIdx.x; i < m; i += blocks * kSelThreads) {
+    const uint64_t key = list[i];
+    const int64_t exact = ov_keys ? table_count(ov_keys, ov_counts, ov_mask, key) : -1;
+    int32_t e;
+    if (exact >= 0) e = (int32_t)exact;
+    else if (staged) e = estimate_key<MAXD>(tabs_lds, M, t.d, t.w, t.cm, key);
+    else e = estimate_key<MAXD>(t.tab, M, t.d, t.w, t.cm, key);
+    ce[i] = e;
+    atomicAdd(&h[(1u << 11) - 1u - (((uint32_t)e ^ 0x80000000u) >> 21)], 1u);
+  }
+  sel_finish_pass<21, 11, false, true>(st, h, m, k, blocks);
+}
+
+// A pass over given pairs (ck, ce): the histogram of one digit over the current class.
+template <int SHIFT, int BITS, bool KEYS, bool FIRST>
+__device__ __forceinline__ void sel_pass_body(const uint64_t* __restrict__ ck, const int32_t* __restrict__ ce,
+                                              SelState* st, uint32_t k) {
+  __shared__ uint32_t h[1 << BITS];
+  if (KEYS && st->ties_all) return;
+  const uint32_t m = st->m, blocks = sel_blocks(m);
+  if (blockIdx.x >= blocks) return;
+  const uint32_t T = st->T;
+  const uint64_t K = st->K;
+  for (uint32_t b = threadIdx.x; b < (1u << BITS); b += kSelThreads) h[b] = 0;
+  __syncthreads();
+  constexpr uint32_t mask = (1u << BITS) - 1u;
+  for (uint64_t i = (uint64_t)blockIdx.x * kSelThreads + threadIdx.x; i < m; i += (uint64_t)blocks * kSelThreads) {
+    const uint32_t u = (uint32_t)ce[i] ^ 0x80000000u;
+    if constexpr (KEYS) {
+      if (u == T) {
+        const uint64_t key = ck[i];
+        if ((key >> (SHIFT + BITS)) == (K >> (SHIFT + BITS))) atomicAdd(&h[(uint32_t)(key >> SHIFT) & mask], 1u);
+      }
+    } else {
+      bool in = true;
+      if constexpr (!FIRST) in = (u >> (SHIFT + BITS)) == (T >> (SHIFT + BITS));
+      if (in) atomicAdd(&h[mask - ((u >> SHIFT) & mask)], 1u);
+    }
+  }
+  sel_finish_pass<SHIFT, BITS, KEYS, FIRST>(st, h, m, k, blocks);
+}
+
+// Winners: est > T, or est == T and key <= K (T, K from the passes).
 __device__ __forceinline__ void sel_gather_body(const uint64_t* __restrict__ ck, const int32_t* __restrict__ ce,
-                                                         SelState* st, uint32_t k, uint64_t* __restrict__ sk,
-                                                         int32_t* __restrict__ se) {
-  const uint32_t m = st->m;
-  const uint32_t T = st->est_prefix;
-  const uint64_t K = st->key_prefix;
-  const bool any = min(k, m) > 0;
-  for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < m; i0 += gridDim.x * blockDim.x) {
-    const uint32_t i = i0 + threadIdx.x;
+                                                SelState* st, uint32_t k, uint64_t* __restrict__ sk,
+                                                int32_t* __restrict__ se) {
+  const uint32_t m = st->m, blocks = sel_blocks(m);
+  if (blockIdx.x >= blocks || min(k, m) == 0) return;
+  const uint32_t T = st->T;
+  const uint64_t K = st->K;
+  for (uint64_t i0 = (uint64_t)blockIdx.x * kSelThreads; i0 < m; i0 += (uint64_t)blocks * kSelThreads) {
+    const uint64_t i = i0 + threadIdx.x;
     bool take = false;
     uint64_t key = 0;
     int32_t e = 0;
-    if (i < m && any) {
-      key = ck[i];
+    if (i < m) {
       e = ce[i];
       const uint32_t u = (uint32_t)e ^ 0x80000000u;
-      take = (u > T) || (u == T && key <= K);
+      take = u >= T;
+      if (take) {
+        key = ck[i];
+        take = u > T || key <= K;
+      }
     }
     const uint32_t slot = wave_append(&st->n_sel, take);
     if (take && slot < k) {
@@ -539,264 +558,365 @@ __device__ __forceinline__ void sel_gather_body(const uint64_t* __restrict__ ck,
     }
   }
 }
-__global__ __launch_bounds__(256) void sel_gather_kernel(const uint64_t* __restrict__ ck, const int32_t* __restrict__ ce,
-                                                         SelState* st, uint32_t k, uint64_t* __restrict__ sk,
-                                                         int32_t* __restrict__ se) {
-  sel_gather_body(ck, ce, st, k, sk, se);
-}
 
-// Place each winner at its rank in (est desc, key asc); keys are distinct.
-// Rank of winner i = number of winners ahead of it in (estimate desc, key asc) order.
-// Block (x, y) counts, for the 256 winners of tile x, those ahead of them among the
-// `chunk` winners of chunk y, and adds the partial counts to rank[].  Keys are distinct,
-// so the ranks are a permutation of [0, n).
-constexpr uint32_t kRankChunk = 1024;      // smallest chunk
-constexpr uint32_t kMaxGridY = 65535;
-// (est, key) as one 64-bit word for keys below 2^32: j comes before i in the output order
-// (higher estimate, then lower key) exactly when its word is the larger.
-__device__ __forceinline__ uint64_t rank_word(int32_t e, uint64_t k) {
-  return ((uint64_t)((uint32_t)e ^ 0x80000000u) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)k);
+// Rank of a winner = number of winners ahead of it in (estimate desc, key asc) order; keys are
+// distinct, so the ranks are a permutation.  A block places 64 R winners: lane l of each of its 16
+// waves compares R of them with the wave's share of every 1024 winners staged in LDS (broadcast
+// reads), and the 16 partial counts meet in LDS.  Bound by those n^2 compares, so the usual one is a
+// single 64-bit word: the estimate's distance above the smallest winner's (16 bits), then
+// 2^48 - 1 - key; winners j come before i when their word is larger.  A staged part with a larger
+// distance is compared by (distance, key) in full; one's own larger distance saturates above every
+// word of the other parts.  64 sketches of up to 10^4 winners each: 224 us with three compares each, 133 us with one.
+// The first block also writes the call's counts: out[0] = min(k, m), out[1] = 1
+// (incomplete) when that is below k and the set is partial; *host (pinned, may be NULL) gets m and
+// the error latch for a caller that synchronizes.
+constexpr uint32_t kRankWide = 4;   // winners per lane when there are many
+__device__ __forceinline__ uint64_t rank_word(uint32_t dist, uint64_t k) {
+  return dist > 0xFFFFu ? ~0ull : ((uint64_t)dist << 48) | (kKeyMax - k);
 }
-
-__device__ __forceinline__ void rank_count_body(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se,
-                                                const SelState* st, uint32_t k, uint32_t chunk,
-                                                uint32_t* __restrict__ rank, uint32_t cy = blockIdx.y,
-                                                bool key32 = false) {
-  __shared__ uint64_t tk[256];
-  __shared__ int32_t te[256];
-  const uint32_t n = min(st->n_sel, k);
-  const uint32_t i0 = blockIdx.x * 256;
-  const uint64_t j_lo64 = (uint64_t)cy * chunk;
-  if (i0 >= n || j_lo64 >= n) return;   // uniform over the block
-  const uint32_t j_lo = (uint32_t)j_lo64;
-  const uint32_t j_hi = (uint32_t)min((uint64_t)n, j_lo64 + chunk);
-  const uint32_t i = i0 + threadIdx.x;
-  const bool act = i < n;
-  const uint64_t ki = act ? sk[i] : 0;
-  const int32_t ei = act ? se[i] : 0;
-  uint32_t cnt = 0;
-  if (key32) {   // one 64-bit comparison per pair
-    const uint64_t wi = rank_word(ei, ki);
-    for (uint32_t j0 = j_lo; j0 < j_hi; j0 += 256) {
-      __syncthreads();
-      if (j0 + threadIdx.x < j_hi) tk[threadIdx.x] = rank_word(se[j0 + threadIdx.x], sk[j0 + threadIdx.x]);
-      __syncthreads();
-      const uint32_t lim = min(256u, j_hi - j0);
-      for (uint32_t t = 0; t < lim; ++t) cnt += tk[t] > wi;
+// The winners [i0, i0 + 64 R) at their ranks among n (every thread of the block calls it).  T: the
+// smallest winner's estimate with its sign flipped.
+template <uint32_t R>
+__device__ __forceinline__ void rank_block(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se, uint32_t n,
+                                           uint32_t T, uint32_t i0, uint64_t* __restrict__ ok,
+                                           int32_t* __restrict__ oe) {
+  __shared__ uint64_t tw[kSelThreads];
+  __shared__ uint32_t td[kSelThreads];
+  __shared__ uint32_t rank[64 * R];
+  const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  uint64_t w[R];
+  uint32_t cnt[R];
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = i0 + 64 * r + lane;
+    w[r] = i < n ? rank_word(((uint32_t)se[i] ^ 0x80000000u) - T, sk[i]) : ~0ull;
+    cnt[r] = 0;
+  }
+  if (tid < 64 * R) rank[tid] = 0;
+  for (uint32_t j0 = 0; j0 < n; j0 += kSelThreads) {
+    __syncthreads();
+    const uint32_t j = j0 + tid;
+    const uint32_t dist = j < n ? ((uint32_t)se[j] ^ 0x80000000u) - T : 0u;
+    const int far = __syncthreads_or(dist > 0xFFFFu);
+    tw[tid] = j >= n ? 0ull : far ? kKeyMax - sk[j] : rank_word(dist, sk[j]);   // 0: ahead of nothing
+    td[tid] = dist;
+    __syncthreads();
+    if (n - j0 <= wave * 64u) continue;   // (the barriers above are reached by every thread again)
+    if (!far) {
+#pragma unroll 4
+      for (uint32_t q = wave * 64u; q < wave * 64u + 64u; ++q) {
+        const uint64_t x = tw[q];
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r) cnt[r] += x > w[r];
+      }
+    } else {
+      uint32_t d[R];
+      uint64_t c[R];
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = i0 + 64 * r + lane;
+        d[r] = i < n ? ((uint32_t)se[i] ^ 0x80000000u) - T : ~0u;
+        c[r] = i < n ? kKeyMax - sk[i] : ~0ull;
+      }
+      for (uint32_t q = wave * 64u; q < wave * 64u + 64u; ++q) {
+        const uint64_t x = tw[q];
+        const uint32_t e = td[q];
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r) cnt[r] += e > d[r] || (e == d[r] && x > c[r]);
+      }
     }
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r)
+    if (cnt[r]) atomicAdd(&rank[64 * r + lane], cnt[r]);
+  __syncthreads();
+  if (tid < 64 * R && i0 + tid < n) {
+    ok[rank[tid]] = sk[i0 + tid];
+    oe[rank[tid]] = se[i0 + tid];
+  }
+  __syncthreads();
+}
+__device__ __forceinline__ void sel_result(uint32_t m, uint32_t k, const uint32_t* err, uint32_t partial, SelState* st,
+                                           uint32_t* out, SelHost* host) {
+  const uint32_t bits = *err;
+  st->err = bits;
+  if (out) {
+    out[0] = min(k, m);
+    out[1] = (min(k, m) < k && partial) ? 1u : 0u;
+  }
+  if (host) {
+    __hip_atomic_store(&host->m, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&host->err, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+template <uint32_t R>
+__device__ __forceinline__ void sel_rank_body(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se,
+                                              SelState* st, uint32_t k, uint64_t* __restrict__ ok,
+                                              int32_t* __restrict__ oe, const uint32_t* err, uint32_t partial,
+                                              uint32_t* out, SelHost* host) {
+  const uint32_t n = min(st->n_sel, k);
+  if (blockIdx.x == 0 && threadIdx.x == 0) sel_result(st->m, k, err, partial, st, out, host);
+  for (uint32_t i0 = blockIdx.x * 64 * R; i0 < n; i0 += gridDim.x * 64 * R) rank_block<R>(sk, se, n, st->T, i0, ok, oe);
+}
+
+// The whole selection in one block, for few candidates (any number is right, a large one slow): the
+// same passes with their histograms in LDS, then the gather, and the rank placement when k is at
+// most kOneRank (else the rank kernel follows).
+constexpr uint32_t kOneRank = 1024;
+template <int MAXD>
+__global__ __launch_bounds__(kSelThreads) void sel_one_kernel(const uint64_t* __restrict__ list,
+                                                              const uint32_t* __restrict__ count, uint32_t max_cand,
+                                                              Tables t, const int32_t* __restrict__ M, uint32_t k,
+                                                              SelState* st, int32_t* __restrict__ ce,
+                                                              uint64_t* __restrict__ sk, int32_t* __restrict__ se,
+                                                              uint64_t* __restrict__ ok, int32_t* __restrict__ oe,
+                                                              const uint32_t* err, uint32_t partial, uint32_t* out,
+                                                              SelHost* host, const uint64_t* __restrict__ ov_keys,
+                                                              const uint32_t* __restrict__ ov_counts,
+                                                              uint32_t ov_mask) {
+  __shared__ uint32_t h[kSelBins];
+  __shared__ uint32_t n_sel;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t m = min(*count, max_cand);
+  uint32_t need = min(k, m), T = 0;
+  uint64_t K = 0;
+  auto clear = [&](uint32_t nb) {
+    for (uint32_t b = tid; b < nb; b += kSelThreads) h[b] = 0;
+    if (tid == 0) n_sel = 0;
+    __syncthreads();
+  };
+  // a thread reads back only the estimates it wrote itself
+  clear(1u << 11);
+  for (uint32_t i = tid; i < m; i += kSelThreads) {
+    const uint64_t key = list[i];
+    const int64_t exact = ov_keys ? table_count(ov_keys, ov_counts, ov_mask, key) : -1;
+    const int32_t e = exact >= 0 ? (int32_t)exact : estimate_key<MAXD>(t.tab, M, t.d, t.w, t.cm, key);
+    ce[i] = e;
+    atomicAdd(&h[2047u - (((uint32_t)e ^ 0x80000000u) >> 21)], 1u);
+  }
+  __syncthreads();
+  SelDigit f = sel_digit<11>(h, false, need);
+  T = (2047u - f.bin) << 21;
+  need -= f.before;
+  clear(1u << 11);
+  for (uint32_t i = tid; i < m; i += kSelThreads) {
+    const uint32_t u = (uint32_t)ce[i] ^ 0x80000000u;
+    if ((u >> 21) == (T >> 21)) atomicAdd(&h[2047u - ((u >> 10) & 2047u)], 1u);
+  }
+  __syncthreads();
+  f = sel_digit<11>(h, false, need);
+  T |= (2047u - f.bin) << 10;
+  need -= f.before;
+  clear(1u << 10);
+  for (uint32_t i = tid; i < m; i += kSelThreads) {
+    const uint32_t u = (uint32_t)ce[i] ^ 0x80000000u;
+    if ((u >> 10) == (T >> 10)) atomicAdd(&h[1023u - (u & 1023u)], 1u);
+  }
+  __syncthreads();
+  f = sel_digit<10>(h, false, need);
+  T |= 1023u - f.bin;
+  need -= f.before;
+  if (f.here == need) {
+    K = kKeyMax;
   } else {
-    for (uint32_t j0 = j_lo; j0 < j_hi; j0 += 256) {
-      __syncthreads();
-      if (j0 + threadIdx.x < j_hi) {
-        tk[threadIdx.x] = sk[j0 + threadIdx.x];
-        te[threadIdx.x] = se[j0 + threadIdx.x];
+#pragma unroll 1
+    for (int shift = 36; shift >= 0; shift -= 12) {
+      clear(1u << 12);
+      for (uint32_t i = tid; i < m; i += kSelThreads) {
+        if (((uint32_t)ce[i] ^ 0x80000000u) != T) continue;
+        const uint64_t key = list[i];
+        if ((key >> (shift + 12)) == (K >> (shift + 12))) atomicAdd(&h[(uint32_t)(key >> shift) & 4095u], 1u);
       }
       __syncthreads();
-      const uint32_t lim = min(256u, j_hi - j0);
-      for (uint32_t t = 0; t < lim; ++t) cnt += (te[t] > ei) || (te[t] == ei && tk[t] < ki);
+      f = sel_digit<12>(h, false, need);
+      K |= (uint64_t)f.bin << shift;
+      need -= f.before;
     }
   }
-  if (act && cnt) atomicAdd(&rank[i], cnt);
-}
-__global__ __launch_bounds__(256) void rank_count_kernel(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se,
-                                                         const SelState* st, uint32_t k, uint32_t chunk,
-                                                         uint32_t* __restrict__ rank) {
-  rank_count_body(sk, se, st, k, chunk, rank);
-}
-
-__device__ __forceinline__ void rank_place_body(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se,
-                                                         const SelState* st, uint32_t k,
-                                                         const uint32_t* __restrict__ rank, uint64_t* __restrict__ ok,
-                                                         int32_t* __restrict__ oe) {
-  const uint32_t n = min(st->n_sel, k);
-  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const uint32_t r = rank[i];
-    ok[r] = sk[i];
-    oe[r] = se[i];
+  clear(0);
+  const uint32_t want = min(k, m);
+  if (want > 0) {
+    for (uint32_t i0 = 0; i0 < m; i0 += kSelThreads) {
+      const uint32_t i = i0 + tid;
+      bool take = false;
+      uint64_t key = 0;
+      int32_t e = 0;
+      if (i < m) {
+        e = ce[i];
+        key = list[i];
+        const uint32_t u = (uint32_t)e ^ 0x80000000u;
+        take = u > T || (u == T && key <= K);
+      }
+      const uint32_t slot = wave_append(&n_sel, take);
+      if (take && slot < k) {
+        sk[slot] = key;
+        se[slot] = e;
+      }
+    }
   }
-}
-__global__ __launch_bounds__(256) void rank_place_kernel(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se,
-                                                         const SelState* st, uint32_t k,
-                                                         const uint32_t* __restrict__ rank, uint64_t* __restrict__ ok,
-                                                         int32_t* __restrict__ oe) {
-  rank_place_body(sk, se, st, k, rank, ok, oe);
-}
-
-// Number written and status of a top-k, for callers that do not synchronize: out[0] =
-// min(k, m); out[1] = 1 (incomplete) when fewer than k were found from a partial set.
-__device__ __forceinline__ void topk_out_body(const SelState* st, uint32_t k, uint32_t partial, uint32_t* out) {
-  if (threadIdx.x == 0) {
-    const uint32_t got = min(k, st->m);
-    out[0] = got;
-    out[1] = (got < k && partial) ? 1u : 0u;
+  __syncthreads();
+  const uint32_t n = min(n_sel, k);
+  if (tid == 0) {
+    st->m = m;
+    st->n_sel = n;
+    sel_result(m, k, err, partial, st, out, host);
   }
-}
-__global__ void topk_out_kernel(const SelState* st, uint32_t k, uint32_t partial, uint32_t* out) {
-  topk_out_body(st, k, partial, out);
-}
-
-hipError_t launch_topk_out(const SelState* st, uint32_t k, uint32_t partial, uint32_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(topk_out_kernel, dim3(1), dim3(64), 0, s, st, k, partial, out);
-  return hipGetLastError();
+  if (k <= kOneRank)
+    for (uint32_t i0 = 0; i0 < n; i0 += 64) rank_block<1>(sk, se, n, T, i0, ok, oe);
 }
 
-__device__ __forceinline__ void sel_finish_body(SelState* st, const uint32_t* err) {
-  if (threadIdx.x == 0) st->err = *err;
+// ---- one selection
+
+template <int MAXD>
+__global__ __launch_bounds__(kSelThreads) void sel_estimate_kernel(const uint64_t* __restrict__ list,
+                                                                   const uint32_t* __restrict__ count,
+                                                                   uint32_t max_cand, Tables t,
+                                                                   const int32_t* __restrict__ M, uint32_t k,
+                                                                   SelState* st, int32_t* __restrict__ ce,
+                                                                   const uint64_t* __restrict__ ov_keys,
+                                                                   const uint32_t* __restrict__ ov_counts,
+                                                                   uint32_t ov_mask) {
+  sel_estimate_body<MAXD>(list, count, max_cand, t, M, k, st, ce, ov_keys, ov_counts, ov_mask);
 }
-__global__ void sel_finish_kernel(SelState* st, const uint32_t* err) { sel_finish_body(st, err); }
-
-__global__ void sel_set_m_kernel(SelState* st, uint32_t m) {
-  if (threadIdx.x == 0) st->m = m;
+template <int SHIFT, int BITS, bool KEYS, bool FIRST>
+__global__ __launch_bounds__(kSelThreads) void sel_pass_kernel(const uint64_t* __restrict__ ck,
+                                                               const int32_t* __restrict__ ce, SelState* st, uint32_t k) {
+  sel_pass_body<SHIFT, BITS, KEYS, FIRST>(ck, ce, st, k);
 }
-
-__global__ void sel_set_m_dev_kernel(SelState* st, const uint64_t* m_dev, uint32_t cap) {
-  if (threadIdx.x == 0) st->m = (uint32_t)(*m_dev < cap ? *m_dev : cap);
+__global__ __launch_bounds__(kSelThreads) void sel_gather_kernel(const uint64_t* __restrict__ ck,
+                                                                 const int32_t* __restrict__ ce, SelState* st,
+                                                                 uint32_t k, uint64_t* __restrict__ sk,
+                                                                 int32_t* __restrict__ se) {
+  sel_gather_body(ck, ce, st, k, sk, se);
 }
-
-// Radix select of the top k of the st->m pairs (ck, ce) in (ce desc, ck asc) order (ck
-// below 2^48), then the winners placed at their ranks in ok / oe.  rank: k words.
-static hipError_t select_stages(const uint64_t* ck, const int32_t* ce, uint32_t m_max, uint32_t k, SelState* st,
-                                uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok, int32_t* oe,
-                                const uint32_t* err, hipStream_t s) {
-  const dim3 hgrid(grid_for(m_max, 256, 1024));
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(sel_hist_kernel<false>, hgrid, dim3(256), 0, s, ck, ce, st, shift);
-    hipLaunchKernelGGL(sel_pick_kernel<false>, dim3(1), dim3(64), 0, s, st, k, shift);
-  }
-  for (int shift = 40; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(sel_hist_kernel<true>, hgrid, dim3(256), 0, s, ck, ce, st, shift);
-    hipLaunchKernelGGL(sel_pick_kernel<true>, dim3(1), dim3(64), 0, s, st, k, shift);
-  }
-  hipLaunchKernelGGL(sel_gather_kernel, hgrid, dim3(256), 0, s, ck, ce, st, k, sk, se);
-  hipError_t e = launch_fill_u32(rank, k, 0u, s);
-  if (e != hipSuccess) return e;
-  uint64_t chunk = kRankChunk;
-  while ((k + chunk - 1) / chunk > kMaxGridY) chunk *= 2;
-  hipLaunchKernelGGL(rank_count_kernel, dim3((k + 255) / 256, (uint32_t)((k + chunk - 1) / chunk)), dim3(256), 0, s,
-                     sk, se, st, k, (uint32_t)chunk, rank);
-  hipLaunchKernelGGL(rank_place_kernel, dim3(grid_for(k, 256, 1024)), dim3(256), 0, s, sk, se, st, k, rank, ok, oe);
-  hipLaunchKernelGGL(sel_finish_kernel, dim3(1), dim3(64), 0, s, st, err);
-  return hipGetLastError();
+template <uint32_t R>
+__global__ __launch_bounds__(kSelThreads) void sel_rank_kernel(const uint64_t* __restrict__ sk,
+                                                               const int32_t* __restrict__ se, SelState* st, uint32_t k,
+                                                               uint64_t* __restrict__ ok, int32_t* __restrict__ oe,
+                                                               const uint32_t* err, uint32_t partial, uint32_t* out,
+                                                               SelHost* host) {
+  sel_rank_body<R>(sk, se, st, k, ok, oe, err, partial, out, host);
 }
-
-// ---- the top-k of many sketches at once: block row blockIdx.y (blockIdx.z for the rank
-// count) serves sketch y of the descriptors; per-call k and outputs come by value.
-__global__ void sel_init_batch_kernel(const TopkDesc* __restrict__ D) { sel_init_body(D[blockIdx.y].st); }
-
-template <int MAXD, bool TAB_LDS>
-__global__ __launch_bounds__(256) void compact_batch_kernel(const TopkDesc* __restrict__ D) {
-  const TopkDesc& d = D[blockIdx.y];
-  compact_body<MAXD, TAB_LDS>(d.set, d.slots, d.t, d.M, d.max_cand, d.st, d.ck, d.ce, nullptr, nullptr, 0u);
-}
-
-__global__ void clamp_m_batch_kernel(const TopkDesc* __restrict__ D) {
-  clamp_m_body(D[blockIdx.y].st, D[blockIdx.y].max_cand);
-}
-
-template <bool KEYS>
-__global__ __launch_bounds__(256) void sel_hist_batch_kernel(const TopkDesc* __restrict__ D, int shift) {
-  const TopkDesc& d = D[blockIdx.y];
-  sel_hist_body<KEYS>(d.ck, d.ce, d.st, shift);
-}
-
-template <bool KEYS>
-__global__ __launch_bounds__(64) void sel_pick_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call, int shift) {
-  sel_pick_body<KEYS>(D[blockIdx.y].st, call.k[blockIdx.y], shift);
-}
-
-__global__ __launch_bounds__(256) void sel_gather_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
-  const TopkDesc& d = D[blockIdx.y];
-  sel_gather_body(d.ck, d.ce, d.st, call.k[blockIdx.y], d.sk, d.se);
-}
-
-// ranks live in the first k words of each sketch's candidate estimates (no longer needed)
-__global__ __launch_bounds__(256) void rank_clear_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
-  uint32_t* r = (uint32_t*)D[blockIdx.y].ce;
-  const uint32_t k = call.k[blockIdx.y];
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) r[i] = 0;
-}
-
-__global__ __launch_bounds__(256) void rank_count_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call,
-                                                               uint32_t chunk) {
-  const TopkDesc& d = D[blockIdx.z];
-  rank_count_body(d.sk, d.se, d.st, call.k[blockIdx.z], chunk, (uint32_t*)d.ce, blockIdx.y, call.key32[blockIdx.z] != 0u);
-}
-
-__global__ __launch_bounds__(256) void rank_place_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
-  const TopkDesc& d = D[blockIdx.y];
-  rank_place_body(d.sk, d.se, d.st, call.k[blockIdx.y], (const uint32_t*)d.ce, call.keys[blockIdx.y],
-                  call.est[blockIdx.y]);
-}
-
-__global__ void sel_finish_out_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
-  const TopkDesc& d = D[blockIdx.y];
-  sel_finish_body(d.st, d.err);
-  topk_out_body(d.st, call.k[blockIdx.y], call.partial[blockIdx.y], call.out[blockIdx.y]);
-}
-
-hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint32_t slots_max,
-                             uint32_t max_cand_max, uint32_t k_max, const TopkCall& call, hipStream_t s) {
-  if (count == 0) return hipSuccess;
-  hipLaunchKernelGGL(sel_init_batch_kernel, dim3(1, count), dim3(256), 0, s, D);
-  const dim3 cgrid(grid_for(slots_max, 256 * kCompactSlots, 4096), count);
-  if (d <= (uint32_t)kTabLdsRows)
-    hipLaunchKernelGGL((compact_batch_kernel<kTabLdsRows, true>), cgrid, dim3(256), 0, s, D);
+// One winner per lane until its blocks fill the card, then four (a quarter of the LDS reads).
+static void launch_rank(const uint64_t* sk, const int32_t* se, SelState* st, uint32_t k, uint64_t* ok, int32_t* oe,
+                        const uint32_t* err, uint32_t partial, uint32_t* out, SelHost* host, hipStream_t s) {
+  if (k <= 16384u)
+    hipLaunchKernelGGL((sel_rank_kernel<1>), dim3(grid_for(k, 64, 4096)), dim3(kSelThreads), 0, s, sk, se, st, k, ok, oe,
+                       err, partial, out, host);
   else
-    hipLaunchKernelGGL((compact_batch_kernel<32, false>), cgrid, dim3(256), 0, s, D);
-  hipLaunchKernelGGL(clamp_m_batch_kernel, dim3(1, count), dim3(64), 0, s, D);
-  const dim3 hgrid(grid_for(max_cand_max, 256, 1024), count);
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(sel_hist_batch_kernel<false>, hgrid, dim3(256), 0, s, D, shift);
-    hipLaunchKernelGGL(sel_pick_batch_kernel<false>, dim3(1, count), dim3(64), 0, s, D, call, shift);
-  }
-  for (int shift = 40; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(sel_hist_batch_kernel<true>, hgrid, dim3(256), 0, s, D, shift);
-    hipLaunchKernelGGL(sel_pick_batch_kernel<true>, dim3(1, count), dim3(64), 0, s, D, call, shift);
-  }
-  hipLaunchKernelGGL(sel_gather_batch_kernel, hgrid, dim3(256), 0, s, D, call);
-  if (k_max > 0) {
-    hipLaunchKernelGGL(rank_clear_batch_kernel, dim3(grid_for(k_max, 256, 1024), count), dim3(256), 0, s, D, call);
-    uint64_t chunk = kRankChunk;
-    while ((k_max + chunk - 1) / chunk > kMaxGridY) chunk *= 2;
-    hipLaunchKernelGGL(rank_count_batch_kernel, dim3((k_max + 255) / 256, (uint32_t)((k_max + chunk - 1) / chunk), count),
-                       dim3(256), 0, s, D, call, (uint32_t)chunk);
-    hipLaunchKernelGGL(rank_place_batch_kernel, dim3(grid_for(k_max, 256, 1024), count), dim3(256), 0, s, D, call);
-  }
-  hipLaunchKernelGGL(sel_finish_out_batch_kernel, dim3(1, count), dim3(64), 0, s, D, call);
+    hipLaunchKernelGGL((sel_rank_kernel<kRankWide>), dim3(grid_for(k, 64 * kRankWide, 4096)), dim3(kSelThreads), 0, s, sk,
+                       se, st, k, ok, oe, err, partial, out, host);
+}
+
+// An empty state (a caller's scratch is not cleared) of m pairs: m, or *m_dev clamped to m.
+__global__ __launch_bounds__(kSelThreads) void sel_start_kernel(SelState* st, uint32_t m, const uint64_t* m_dev) {
+  uint32_t* w = (uint32_t*)st;
+  for (uint32_t i = threadIdx.x; i < sizeof(SelState) / 4; i += kSelThreads) w[i] = 0;
+  __syncthreads();
+  if (threadIdx.x == 0) st->m = m_dev ? (uint32_t)(*m_dev < m ? *m_dev : m) : m;
+}
+
+// The passes after the first, the gather and the rank placement.
+static hipError_t select_rest(const uint64_t* ck, const int32_t* ce, uint32_t m_max, uint32_t k, SelState* st,
+                              uint64_t* sk, int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err,
+                              uint32_t partial, uint32_t* out, SelHost* host, hipStream_t s) {
+  const dim3 g(grid_for(m_max, kSelItems, kSelGrid)), b(kSelThreads);
+  hipLaunchKernelGGL((sel_pass_kernel<10, 11, false, false>), g, b, 0, s, ck, ce, st, k);
+  hipLaunchKernelGGL((sel_pass_kernel<0, 10, false, false>), g, b, 0, s, ck, ce, st, k);
+  hipLaunchKernelGGL((sel_pass_kernel<36, 12, true, false>), g, b, 0, s, ck, ce, st, k);
+  hipLaunchKernelGGL((sel_pass_kernel<24, 12, true, false>), g, b, 0, s, ck, ce, st, k);
+  hipLaunchKernelGGL((sel_pass_kernel<12, 12, true, false>), g, b, 0, s, ck, ce, st, k);
+  hipLaunchKernelGGL((sel_pass_kernel<0, 12, true, false>), g, b, 0, s, ck, ce, st, k);
+  hipLaunchKernelGGL(sel_gather_kernel, g, b, 0, s, ck, ce, st, k, sk, se);
+  launch_rank(sk, se, st, k, ok, oe, err, partial, out, host, s);
   return hipGetLastError();
 }
 
-hipError_t launch_topk(const uint64_t* set, uint32_t slots, const Tables& t, const int32_t* M,
-                       uint32_t max_cand, uint32_t k, SelState* st, uint64_t* ck, int32_t* ce,
-                       uint64_t* sk, int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err,
+hipError_t launch_topk(const uint64_t* list, const uint32_t* count, const Tables& t, const int32_t* M,
+                       uint32_t max_cand, uint64_t likely, uint32_t k, SelState* st, int32_t* ce, uint64_t* sk, int32_t* se,
+                       uint64_t* ok, int32_t* oe, const uint32_t* err, uint32_t partial, uint32_t* out, SelHost* host,
                        hipStream_t s, const uint64_t* ov_keys, const uint32_t* ov_counts, uint32_t ov_mask) {
-  hipLaunchKernelGGL(sel_init_kernel, dim3(1), dim3(256), 0, s, st);
-  const dim3 cgrid(grid_for(slots, 256 * kCompactSlots, 4096));
+  const dim3 g(grid_for(max_cand, kSelItems, kSelGrid)), b(kSelThreads);
+  if (likely <= kOneBlock) {
+    if (t.d <= (uint32_t)kTabLdsRows)
+      hipLaunchKernelGGL((sel_one_kernel<kTabLdsRows>), dim3(1), b, 0, s, list, count, max_cand, t, M, k, st, ce, sk, se,
+                         ok, oe, err, partial, out, host, ov_keys, ov_counts, ov_mask);
+    else
+      hipLaunchKernelGGL((sel_one_kernel<32>), dim3(1), b, 0, s, list, count, max_cand, t, M, k, st, ce, sk, se, ok, oe,
+                         err, partial, out, host, ov_keys, ov_counts, ov_mask);
+    if (k > kOneRank) launch_rank(sk, se, st, k, ok, oe, err, partial, out, host, s);
+    return hipGetLastError();
+  }
   if (t.d <= (uint32_t)kTabLdsRows)
-    hipLaunchKernelGGL((compact_kernel<kTabLdsRows, true>), cgrid, dim3(256), 0, s, set, slots, t, M, max_cand, st,
-                       ck, ce, ov_keys, ov_counts, ov_mask);
+    hipLaunchKernelGGL((sel_estimate_kernel<kTabLdsRows>), g, b, 0, s, list, count, max_cand, t, M, k, st, ce, ov_keys,
+                       ov_counts, ov_mask);
   else
-    hipLaunchKernelGGL((compact_kernel<32, false>), cgrid, dim3(256), 0, s, set, slots, t, M, max_cand, st, ck,
-                       ce, ov_keys, ov_counts, ov_mask);
-  hipLaunchKernelGGL(clamp_m_kernel, dim3(1), dim3(64), 0, s, st, max_cand);
-  // the candidate estimates are no longer needed once gathered: their first k words hold the ranks
-  return select_stages(ck, ce, max_cand, k, st, sk, se, (uint32_t*)ce, ok, oe, err, s);
+    hipLaunchKernelGGL((sel_estimate_kernel<32>), g, b, 0, s, list, count, max_cand, t, M, k, st, ce, ov_keys,
+                       ov_counts, ov_mask);
+  return select_rest(list, ce, max_cand, k, st, sk, se, ok, oe, err, partial, out, host, s);
+}
+
+static hipError_t select_pairs(const uint64_t* ck, const int32_t* ce, uint32_t m, const uint64_t* m_dev, uint32_t k,
+                               SelState* st, uint64_t* sk, int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(sel_start_kernel, dim3(1), dim3(kSelThreads), 0, s, st, m, m_dev);
+  hipLaunchKernelGGL((sel_pass_kernel<21, 11, false, true>), dim3(grid_for(m, kSelItems, kSelGrid)), dim3(kSelThreads),
+                     0, s, ck, ce, st, k);
+  return select_rest(ck, ce, m, k, st, sk, se, ok, oe, err, 0u, nullptr, nullptr, s);
 }
 
 hipError_t launch_select_pairs_dev(const uint64_t* ck, const int32_t* ce, const uint64_t* m_dev, uint32_t cap,
-                                   uint32_t k, SelState* st, uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok,
+                                   uint32_t k, SelState* st, uint64_t* sk, int32_t* se, uint64_t* ok,
                                    int32_t* oe, const uint32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(sel_init_kernel, dim3(1), dim3(256), 0, s, st);
-  hipLaunchKernelGGL(sel_set_m_dev_kernel, dim3(1), dim3(64), 0, s, st, m_dev, cap);
-  return select_stages(ck, ce, cap, k, st, sk, se, rank, ok, oe, err, s);
+  return select_pairs(ck, ce, cap, m_dev, k, st, sk, se, ok, oe, err, s);
 }
 
 hipError_t launch_select_pairs(const uint64_t* ck, const int32_t* ce, uint32_t m, uint32_t k, SelState* st,
-                               uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok, int32_t* oe,
-                               const uint32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(sel_init_kernel, dim3(1), dim3(256), 0, s, st);
-  hipLaunchKernelGGL(sel_set_m_kernel, dim3(1), dim3(64), 0, s, st, m);
-  return select_stages(ck, ce, m, k, st, sk, se, rank, ok, oe, err, s);
+                               uint64_t* sk, int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err,
+                               hipStream_t s) {
+  return select_pairs(ck, ce, m, nullptr, k, st, sk, se, ok, oe, err, s);
+}
+
+// ---- the top-k of many sketches at once: block row blockIdx.y serves sketch y of the
+// descriptors; per-call k and outputs come by value.
+
+template <int MAXD>
+__global__ __launch_bounds__(kSelThreads) void sel_estimate_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
+  const TopkDesc& d = D[blockIdx.y];
+  sel_estimate_body<MAXD>(d.list, d.count, d.max_cand, d.t, d.M, call.k[blockIdx.y], d.st, d.ce, nullptr, nullptr, 0u);
+}
+template <int SHIFT, int BITS, bool KEYS>
+__global__ __launch_bounds__(kSelThreads) void sel_pass_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
+  const TopkDesc& d = D[blockIdx.y];
+  sel_pass_body<SHIFT, BITS, KEYS, false>(d.list, d.ce, d.st, call.k[blockIdx.y]);
+}
+__global__ __launch_bounds__(kSelThreads) void sel_gather_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
+  const TopkDesc& d = D[blockIdx.y];
+  sel_gather_body(d.list, d.ce, d.st, call.k[blockIdx.y], d.sk, d.se);
+}
+__global__ __launch_bounds__(kSelThreads) void sel_rank_batch_kernel(const TopkDesc* __restrict__ D, TopkCall call) {
+  const uint32_t y = blockIdx.y;
+  const TopkDesc& d = D[y];
+  sel_rank_body<kRankWide>(d.sk, d.se, d.st, call.k[y], call.keys[y], call.est[y], d.err, call.partial[y], call.out[y], nullptr);
+}
+
+hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint32_t max_cand_max, uint32_t k_max,
+                             const TopkCall& call, hipStream_t s) {
+  if (count == 0) return hipSuccess;
+  const dim3 g(grid_for(max_cand_max, kSelItems, kSelGrid), count), b(kSelThreads);
+  if (d <= (uint32_t)kTabLdsRows)
+    hipLaunchKernelGGL((sel_estimate_batch_kernel<kTabLdsRows>), g, b, 0, s, D, call);
+  else
+    hipLaunchKernelGGL((sel_estimate_batch_kernel<32>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL((sel_pass_batch_kernel<10, 11, false>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL((sel_pass_batch_kernel<0, 10, false>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL((sel_pass_batch_kernel<36, 12, true>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL((sel_pass_batch_kernel<24, 12, true>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL((sel_pass_batch_kernel<12, 12, true>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL((sel_pass_batch_kernel<0, 12, true>), g, b, 0, s, D, call);
+  hipLaunchKernelGGL(sel_gather_batch_kernel, g, b, 0, s, D, call);
+  hipLaunchKernelGGL(sel_rank_batch_kernel, dim3(grid_for(k_max, 64 * kRankWide, 1024), count), b, 0, s, D, call);
+  return hipGetLastError();
 }
 
 }  // namespace csk

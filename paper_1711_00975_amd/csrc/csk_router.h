@@ -78,7 +78,7 @@ hipError_t launch_route_score(const uint32_t* counts, uint32_t Gc, const uint64_
 // Admission over a device count: ord (cap words), st, sk / se / rank / ok / oe (A each) and
 // err are scratch; admitted (A keys, ascending) and *na (device) are the result.
 hipError_t launch_admit_dev(const uint64_t* cells, const float* logits, const uint64_t* m_dev, uint64_t cap, uint32_t A,
-                            int32_t* ord, SelState* st, uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok,
+                            int32_t* ord, SelState* st, uint64_t* sk, int32_t* se, uint64_t* ok,
                             int32_t* oe, uint32_t* err, uint64_t* admitted, uint32_t* na, hipStream_t s);
 // The exclusion's child counters added to the exact table (table_slot probing).
 hipError_t launch_route_table(const RouteExclude& ex, uint32_t G, uint64_t* tkeys, uint32_t* tcounts, uint32_t tmask,

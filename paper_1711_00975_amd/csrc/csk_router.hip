@@ -1262,10 +1262,10 @@ hipError_t launch_route_score(const uint32_t* counts, uint32_t Gc, const uint64_
 }
 
 hipError_t launch_admit_dev(const uint64_t* cells, const float* logits, const uint64_t* m_dev, uint64_t cap, uint32_t A,
-                            int32_t* ord, SelState* st, uint64_t* sk, int32_t* se, uint32_t* rank, uint64_t* ok,
+                            int32_t* ord, SelState* st, uint64_t* sk, int32_t* se, uint64_t* ok,
                             int32_t* oe, uint32_t* err, uint64_t* admitted, uint32_t* na, hipStream_t s) {
   hipLaunchKernelGGL(logit_order_dev_kernel, dim3(grid_of(cap, 256, 8192)), dim3(256), 0, s, logits, m_dev, cap, ord);
-  hipError_t e = launch_select_pairs_dev(cells, ord, m_dev, (uint32_t)cap, A, st, sk, se, rank, ok, oe, err, s);
+  hipError_t e = launch_select_pairs_dev(cells, ord, m_dev, (uint32_t)cap, A, st, sk, se, ok, oe, err, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(admit_sort_kernel, dim3((A + 255) / 256), dim3(256), 0, s, ok, st, A, admitted, na);
   return hipGetLastError();
