@@ -701,7 +701,8 @@ csk_status csk_collect_dictionary(csk_sketch* s, double delta, double L, int32_t
   const uint32_t* filter = nullptr;
   const uint32_t* hot = nullptr;
   if (s->filter != nullptr && theta > 0) {
-    CSK_HIP(launch_filter_build(t, s->M, theta, s->filter, s->filter + kFilterAllocWords, s->hot_table, false, st),
+    CSK_HIP(launch_filter_build(t, s->M, theta, s->filter, s->filter + kFilterAllocWords, s->hot_table,
+                                collect_field_form(t), st),
             "collect_dictionary (filter)");
     filter = s->filter;
     hot = s->filter + kFilterAllocWords;
@@ -726,8 +727,18 @@ csk_status csk_collect_children(csk_sketch* fine, csk_sketch* coarse, int32_t th
   if (fine->device != coarse->device) return fail(CSK_E_INVALID, "collect_children: handles on different devices");
   hipStream_t st = (hipStream_t)stream;
   const uint64_t ncells = (uint64_t)fine->mesh.G * fine->mesh.G * fine->mesh.G;
+  const Tables t = fine->tables();
+  const uint32_t* filter = nullptr;
+  if (fine->filter != nullptr && theta > 0) {
+    CSK_HIP(launch_filter_build(t, fine->M, theta, fine->filter, fine->filter + kFilterAllocWords, nullptr,
+                                collect_field_form(t), st, coarse->set_count(), coarse->max_cand, coarse->group,
+                                children_direct_keys(t)),
+            "collect_children (filter)");
+    filter = fine->filter;
+  }
   CSK_HIP(launch_collect_children(coarse->cand_key, coarse->set_count(), coarse->max_cand, coarse->group, ncells,
-                                  fine->tables(), fine->M, theta, fine->cand(), fine->err(), st),
+                                  fine->mesh.nch, t, fine->M, theta, filter,
+                                  filter ? filter + kFilterAllocWords : nullptr, fine->cand(), fine->err(), st),
           "collect_children");
   if (theta != INT32_MIN || coarse->partial_set) fine->partial_set = true;
   fine->cand_likely += ncells;

@@ -195,7 +195,10 @@ __global__ __launch_bounds__(kFilterThreads) void filter_build_kernel(const int3
                                                                       const uint32_t* __restrict__ fcols, uint32_t P,
                                                                       uint32_t* __restrict__ filter,
                                                                       uint32_t* __restrict__ hot,
-                                                                      uint32_t* __restrict__ hot_table) {
+                                                                      uint32_t* __restrict__ hot_table,
+                                                                      const uint32_t* __restrict__ gate, uint32_t cap,
+                                                                      uint32_t per, uint64_t most) {
+  if (gate != nullptr && (uint64_t)min(*gate, cap) * per <= most) return;   // no one will ask the filter
   filter_build_body(M, d, w, cm, bnorm, theta, fcols, P, filter, hot, hot_table, blockIdx.x, gridDim.x);
 }
 
@@ -231,7 +234,8 @@ static uint32_t filter_grid(uint32_t d, uint32_t w) {
 }
 
 hipError_t launch_filter_build(const Tables& t, const int32_t* M, int32_t theta, uint32_t* filter, uint32_t* hot,
-                               uint32_t* hot_table, bool field, hipStream_t s) {
+                               uint32_t* hot_table, bool field, hipStream_t s, const uint32_t* gate, uint32_t cap,
+                               uint32_t per, uint64_t most) {
   field = field && t.fcols != nullptr;
   FillSpans f{};   // the three clears in one launch
   f.p[0] = filter;
@@ -244,7 +248,7 @@ hipError_t launch_filter_build(const Tables& t, const int32_t* M, int32_t theta,
   hipError_t e = launch_fill_spans(f, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(filter_build_kernel, dim3(filter_grid(t.d, t.w)), dim3(kFilterThreads), 0, s, M, t.d, t.w, t.cm,
-                     t.bnorm, theta, field ? t.fcols : nullptr, t.fp, filter, hot, hot_table);
+                     t.bnorm, theta, field ? t.fcols : nullptr, t.fp, filter, hot, hot_table, gate, cap, per, most);
   return hipGetLastError();
 }
 

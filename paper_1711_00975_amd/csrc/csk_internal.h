@@ -266,9 +266,11 @@ hipError_t launch_query(const uint64_t* keys, uint64_t m, const Tables& t, const
 // Bloom filter of the (row, bucket, sign) items whose signed counter is >= theta
 // (theta > 0); filter: kFilterWords words, hot: item count (both zeroed here).
 // hot_table (kHotSlots words, may be NULL) receives every item when the count is at most
-// kHotMaxItems, and stays empty otherwise.
+// kHotMaxItems, and stays empty otherwise.  gate: nothing is built when min(*gate, cap) * per items
+// are at most `most` (the caller's pass then does without the filter by the same rule).
 hipError_t launch_filter_build(const Tables& t, const int32_t* M, int32_t theta, uint32_t* filter, uint32_t* hot,
-                               uint32_t* hot_table, bool field, hipStream_t s);
+                               uint32_t* hot_table, bool field, hipStream_t s, const uint32_t* gate = nullptr,
+                               uint32_t cap = 0, uint32_t per = 0, uint64_t most = 0);
 // A sketch's candidate-pass arguments (kernel argument, or one entry of a batch's
 // descriptor array).
 struct CollectDesc {
@@ -322,8 +324,11 @@ hipError_t launch_collect_dictionary(uint64_t nkeys, const Mesh& mesh, const Tab
 // *list_count; more than list_cap latches the capacity error in err) whose fine estimate is >=
 // theta into the fine set.
 hipError_t launch_collect_children(const uint64_t* list, const uint32_t* list_count, uint32_t list_cap, uint32_t group,
-                                   uint64_t ncells, const Tables& t, const int32_t* M, int32_t theta,
-                                   const CandSet& cand, uint32_t* err, hipStream_t s);
+                                   uint64_t ncells, uint32_t nch, const Tables& t, const int32_t* M, int32_t theta,
+                                   const uint32_t* filter, const uint32_t* hot, const CandSet& cand, uint32_t* err,
+                                   hipStream_t s);
+// At most this many children are tested without the filter (which is then not built).
+uint64_t children_direct_keys(const Tables& t);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
 // Up to kFillSpans spans of 32-bit words, span r set to v[r], in one launch (the clears of a
