@@ -574,6 +574,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_one_kernel(const uint64_t* __
   if (tid == 0) {
     st->m = m;
     st->n_sel = n;
+    st->T = T;   // (the rank kernel's, when it follows)
     sel_result(m, k, err, partial, st, out, host);
   }
   if (k <= kOneRank)

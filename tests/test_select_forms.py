@@ -83,6 +83,25 @@ def test_select_against_the_oracle(n, kind, variant):
         s.close()
 
 
+def test_few_candidates_after_many():
+    # one block selects, the rank kernel places (k > 1024): nothing is left of the selection before
+    d, w, seed = 5, 1 << 14, 3
+    T = oracle.hash_tables(seed, d)
+    s = csk.Sketch(d, w, seed)
+    try:
+        for n, kind in [(70_001, "near"), (5000, "near"), (70_001, "wide"), (4000, "ties"), (3000, "near")]:
+            pos, M = _cells(n, n), _counters(kind, d, w, n)
+            s.set_counters(_dev(M))
+            s.clear_candidates()
+            s.collect(_dev(pos), DELTA, L)
+            kg, eg, _ = s.topk(2500)
+            ko, eo = oracle.topk_keys(M, T, oracle.keys(pos, DELTA, L), csk.INT32_MIN, 2500)
+            assert np.array_equal(kg.cpu().numpy().view(np.uint64), ko), (n, kind)
+            assert np.array_equal(eg.cpu().numpy(), eo), (n, kind)
+    finally:
+        s.close()
+
+
 def test_a_full_candidate_list_is_an_error_and_clears():
     d, w, seed = 5, 1 << 14, 3
     pos, T = _cells(300, 9), oracle.hash_tables(seed, d)
