@@ -197,7 +197,7 @@ struct csk_sketch {
   uint32_t* fcols = nullptr; // the columns and salts of its row maps
   uint32_t dp = 0;
   uint32_t* filter = nullptr; // Bloom filter of hot items + [kFilterAllocWords] item count
-  uint32_t* hot_table = nullptr; // exact set of hot items (kHotSlots words)
+  uint32_t* hot_table = nullptr; // exact set of hot items (kHotSlots words), for the dictionary
   uint64_t* set = nullptr;
   uint32_t slots = 0;
   uint32_t max_cand = 0;
@@ -666,13 +666,12 @@ csk_status collect_impl(csk_sketch* s, const void* src, bool packed, uint64_t n,
   const uint32_t* filter = nullptr;
   const uint32_t* hot = nullptr;
   if (s->filter != nullptr && theta > 0) {
-    CSK_HIP(launch_filter_build(t, s->M, theta, s->filter, s->filter + kFilterAllocWords, s->hot_table, true, st),
+    CSK_HIP(launch_filter_build(t, s->M, theta, s->filter, s->filter + kFilterAllocWords, nullptr, true, st),
             "collect (filter)");
     filter = s->filter;
     hot = s->filter + kFilterAllocWords;
   }
-  CSK_HIP(launch_collect((const float*)src, n, mesh, t, s->M, theta, filter, hot, filter ? s->hot_table : nullptr,
-                         s->cand(), s->err(), true, st),
+  CSK_HIP(launch_collect((const float*)src, n, mesh, t, s->M, theta, filter, hot, s->cand(), s->err(), true, st),
           "collect");
   return CSK_OK;
 }
@@ -1126,7 +1125,7 @@ csk_status batch_create_impl(csk_batch** out, csk_sketch* const* sketches, const
       b->w_max = s->w > b->w_max ? s->w : b->w_max;
       b->cdesc_host[i] = CollectDesc{m,           t,           s->M,          s->filter,
                                      s->filter ? s->filter + kFilterAllocWords : nullptr,
-                                     s->hot_table, s->cand(),  s->err()};
+                                     s->cand(),   s->err()};
       uint64_t want = ct_total ? (cbudget * ct[i] + ct_total / 2) / ct_total : 1;
       if (want > ct[i]) want = ct[i];
       if (want < 1) want = 1;

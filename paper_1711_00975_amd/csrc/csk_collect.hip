@@ -1,6 +1,6 @@
 // csk_collect.hip — the candidate pass (Sec. 3.1 item 4: keep the cells whose estimate
-// passes a threshold) on gfx950: the Bloom filter and exact hot-item set of the heavy
-// (row, bucket, sign) items, built from the counters; the collect kernels, which drop a
+// passes a threshold) on gfx950: the Bloom filter of the heavy (row, bucket, sign) items (and the
+// exact set of them for the dictionary), built from the counters; the collect kernels, which drop a
 // particle whose rows miss the filter and test the rest exactly before inserting its key
 // into the candidate set; and their batched forms for many sketches in one set of launches.
 #include <hip/hip_runtime.h>
@@ -41,12 +41,16 @@ __global__ __launch_bounds__(256) void collect_kernel(const float* __restrict__ 
 }
 
 // The candidate pass of a short stream: one particle per thread, every row's counter read at once
-// and tested exactly, with no filter to build.
+// and tested exactly, with no filter to build.  A workgroup's new keys take their places in the list
+// with one add to the count: wave by wave those adds, all to one word, took longer than the reads (2.4e5
+// particles, 5e4 candidates: 186 us, 26 us so).
 template <int MAXD>
-__global__ __launch_bounds__(256) void collect_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
+__global__ __launch_bounds__(1024) void collect_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
                                                             Tables t, const int32_t* __restrict__ M, int32_t theta,
                                                             CandSet cand, uint32_t* err) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  __shared__ uint32_t found, base, room;
+  if (threadIdx.x == 0) found = 0;
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   uint64_t key;
   const bool in = i < n;
   const bool ok = particle_key(pos, in ? i : n - 1, mesh, key) && in;
@@ -56,7 +60,19 @@ __global__ __launch_bounds__(256) void collect_short_kernel(const float* __restr
 #pragma unroll
   for (int r = 0; r < MAXD; ++r)
     if ((uint32_t)r < t.d && row_estimate(t.tab + r * kTableWords, M + (uint64_t)r * t.w, t.w, t.cm, key) >= theta) ++pass;
-  if (ok && pass >= need) set_insert(cand, key, err);
+  const bool mine = ok && pass >= need;
+  if (!__syncthreads_or(mine)) return;
+  if (threadIdx.x == 0) room = __hip_atomic_load(cand.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < cand.max_cand;
+  __syncthreads();
+  const bool is_new = mine && set_claim(cand, key, err, [&]() { return room != 0; });
+  const uint32_t at = wave_append(&found, is_new);
+  __syncthreads();
+  if (threadIdx.x == 0) base = found ? atomicAdd(cand.count, found) : 0u;
+  __syncthreads();
+  if (is_new) {
+    if (base + at < cand.max_cand) cand.list[base + at] = key;
+    else atomicOr(err, kErrCapacity);
+  }
 }
 
 // Items (r, b, sign) with sign * M[r][b] >= theta (Count-Min: M[r][b] >= theta) go into
@@ -122,11 +138,17 @@ __device__ __forceinline__ void hot_insert(uint32_t* table, uint32_t item) {
   }
 }
 
+// The most hot items that a filter is used with.
+__host__ __device__ __forceinline__ uint32_t filter_most(bool field, uint32_t fspan) {
+  return field ? kFieldFilterMaxItems / fspan : kFilterMaxItems;
+}
+
 // One scan of the counters builds both the Bloom filter and the exact hot-item set (hot_table, may
 // be NULL).  A block gathers the hot items of its counters in LDS and then inserts them with every
 // lane busy: item by item where they were found, an insert kept one lane in 64 running through the
 // row map's 25 columns.  The first kHotMaxItems items counted go into the set, so that it stays at
-// most half full; when there are more, *hot says so and the set is not used.
+// most half full; when there are more, *hot says so and the set is not used.  most: the same for the
+// filter.  Bound by the global atomics of the items (64 sketches, 6.6e6 items: about 0.24 ms for one each).
 constexpr uint32_t kFilterThreads = 256;
 constexpr uint32_t kFilterChunk = kFilterThreads * 4 * kFilterVec;   // counters of one row a block takes at a time
 constexpr uint32_t kFilterQueue = 2 * kFilterChunk;
@@ -135,10 +157,13 @@ __device__ __forceinline__ void filter_build_body(const int32_t* __restrict__ M,
                                                   uint32_t bnorm, int32_t theta, const uint32_t* __restrict__ fcols,
                                                   uint32_t P, uint32_t* __restrict__ filter,
                                                   uint32_t* __restrict__ hot, uint32_t* __restrict__ hot_table,
-                                                  uint32_t bx, uint32_t nbx) {
+                                                  uint32_t most, uint32_t bx, uint32_t nbx) {
   __shared__ uint64_t queue[kFilterQueue];   // row << 32 | bucket << 1 | sign
   __shared__ uint32_t queued, base;
   __shared__ uint32_t cols[5 * kFieldCols];   // field probes: d <= 5
+  const uint32_t per_row = (uint32_t)(((uint64_t)w + kFilterChunk - 1) / kFilterChunk);
+  const uint64_t chunks = (uint64_t)d * per_row;
+  if (bx >= chunks) return;
   if (threadIdx.x == 0) queued = 0;
   if (fcols)
     for (uint32_t i = threadIdx.x; i < d * kFieldCols; i += kFilterThreads) cols[i] = fcols[i];
@@ -150,7 +175,9 @@ __device__ __forceinline__ void filter_build_body(const int32_t* __restrict__ M,
     for (uint32_t i = threadIdx.x; i < nq; i += kFilterThreads) {
       const uint64_t it = queue[i];
       const uint32_t r = (uint32_t)(it >> 32), b = (uint32_t)it >> 1, sg = (uint32_t)it & 1u;
-      if (fcols) {
+      if (base + i >= most) {
+        // the filter is not used
+      } else if (fcols) {
         field_insert(cols + r * kFieldCols, w, P, b, sg, filter);
       } else {
         const FilterProbe pr = filter_probe(r, b, sg, bnorm);
@@ -162,8 +189,6 @@ __device__ __forceinline__ void filter_build_body(const int32_t* __restrict__ M,
     if (threadIdx.x == 0) queued = 0;
     __syncthreads();
   };
-  const uint32_t per_row = (uint32_t)(((uint64_t)w + kFilterChunk - 1) / kFilterChunk);
-  const uint64_t chunks = (uint64_t)d * per_row;
   for (uint64_t ch = bx; ch < chunks; ch += nbx) {
     const uint32_t r = (uint32_t)(ch / per_row);
     const uint64_t b0 = (ch % per_row) * (uint64_t)kFilterChunk;
@@ -197,9 +222,9 @@ __global__ __launch_bounds__(kFilterThreads) void filter_build_kernel(const int3
                                                                       uint32_t* __restrict__ hot,
                                                                       uint32_t* __restrict__ hot_table,
                                                                       const uint32_t* __restrict__ gate, uint32_t cap,
-                                                                      uint32_t per, uint64_t most) {
+                                                                      uint32_t per, uint64_t most, uint32_t most_items) {
   if (gate != nullptr && (uint64_t)min(*gate, cap) * per <= most) return;   // no one will ask the filter
-  filter_build_body(M, d, w, cm, bnorm, theta, fcols, P, filter, hot, hot_table, blockIdx.x, gridDim.x);
+  filter_build_body(M, d, w, cm, bnorm, theta, fcols, P, filter, hot, hot_table, most_items, blockIdx.x, gridDim.x);
 }
 
 // Batched forms: blockIdx.y = sketch; a sketch whose call does not use its filter is skipped.
@@ -208,13 +233,11 @@ __global__ __launch_bounds__(256) void collect_clear_batch_kernel(const CollectD
   const uint32_t i = blockIdx.y;
   if (!call.use_filter[i]) return;
   const CollectDesc& c = descs[i];
-  const uint64_t nh = c.hot_table != nullptr ? kHotSlots : 0u;
-  const uint64_t total = (uint64_t)fw + 1u + nh;
+  const uint64_t total = (uint64_t)fw + 1u;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < total; j += stride) {
     if (j < fw) c.filter[j] = 0u;
-    else if (j == fw) *c.hot = 0u;
-    else c.hot_table[j - fw - 1u] = kHotEmpty;
+    else *c.hot = 0u;
   }
 }
 
@@ -224,13 +247,13 @@ __global__ __launch_bounds__(kFilterThreads) void filter_build_batch_kernel(cons
   if (!call.use_filter[i]) return;
   const CollectDesc& c = descs[i];
   filter_build_body(c.M, c.t.d, c.t.w, c.t.cm, c.t.bnorm, call.theta[i], field ? c.t.fcols : nullptr, c.t.fp,
-                    c.filter, c.hot, c.hot_table, blockIdx.x, gridDim.x);
+                    c.filter, c.hot, nullptr, filter_most(field, c.t.fspan), blockIdx.x, gridDim.x);
 }
 
-// Blocks of a filter build: one per chunk of counters up to 2048 of them (the LDS queue lets four
-// or five share a CU).
+// Blocks of a filter build: one per chunk of counters up to 1024 of them, which is what the LDS queues
+// let run at once (each adds its hot items to one count).
 static uint32_t filter_grid(uint32_t d, uint32_t w) {
-  return grid_for((uint64_t)d * (((uint64_t)w + kFilterChunk - 1) / kFilterChunk), 1, 2048);
+  return grid_for((uint64_t)d * (((uint64_t)w + kFilterChunk - 1) / kFilterChunk), 1, 1024);
 }
 
 hipError_t launch_filter_build(const Tables& t, const int32_t* M, int32_t theta, uint32_t* filter, uint32_t* hot,
@@ -248,7 +271,8 @@ hipError_t launch_filter_build(const Tables& t, const int32_t* M, int32_t theta,
   hipError_t e = launch_fill_spans(f, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(filter_build_kernel, dim3(filter_grid(t.d, t.w)), dim3(kFilterThreads), 0, s, M, t.d, t.w, t.cm,
-                     t.bnorm, theta, field ? t.fcols : nullptr, t.fp, filter, hot, hot_table, gate, cap, per, most);
+                     t.bnorm, theta, field ? t.fcols : nullptr, t.fp, filter, hot, hot_table, gate, cap, per, most,
+                     filter_most(field, t.fspan));
   return hipGetLastError();
 }
 
@@ -259,9 +283,11 @@ static void launch_collect2_d(uint32_t d, uint32_t mode, int hm, dim3 grid, dim3
   else launch_collect2_many(d, mode, hm, grid, block, lds, s, c);
 }
 
-size_t collect2_lds_bytes(const Tables& t, bool use_filter, bool field) {
-  return field ? ((size_t)kTableWords * 4 + 2 * kCollectCache + kFieldFilterWords) * sizeof(uint32_t)
-               : ((size_t)kTableWords * t.dp + 2 * kCollectCache + (use_filter ? kFilterWords : 0)) * sizeof(uint32_t);
+static size_t collect2_lds_bytes(const Tables& t, bool use_filter, bool field, uint32_t kb) {
+  if (t.d != 5) kb = kChars;   // other d hash all six bytes
+  if (field) return kb <= 5 ? collect2_lds<true, 5>(4, kFieldFilterWords) : collect2_lds<true, 6>(4, kFieldFilterWords);
+  const uint32_t fw = use_filter ? (uint32_t)kFilterWords : 0u;
+  return kb <= 5 ? collect2_lds<false, 5>(t.dp, fw) : collect2_lds<false, 6>(t.dp, fw);
 }
 
 bool collect_field_form(const Tables& t) {
@@ -269,28 +295,30 @@ bool collect_field_form(const Tables& t) {
 }
 
 bool collect_is_short(uint64_t n, const Tables& t) {
-  return t.d <= (uint32_t)kTabLdsRows && n <= kShortStream && n * t.d <= (5ull << 18) + (uint64_t)t.d * t.w / 21u;
+  return t.d <= (uint32_t)kTabLdsRows && n <= kShortStream && n <= (1ull << 19) + t.w / 32u;
 }
 
 hipError_t launch_collect_short(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const int32_t* M,
                                 int32_t theta, const CandSet& cand, uint32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(collect_short_kernel<kTabLdsRows>, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, pos,
+  const uint32_t nt = n <= (1u << 16) ? 256u : 1024u;   // few particles: over more CUs
+  hipLaunchKernelGGL(collect_short_kernel<kTabLdsRows>, dim3((uint32_t)((n + nt - 1) / nt)), dim3(nt), 0, s, pos,
                      (uint32_t)n, mesh, t, M, theta, cand, err);
   return hipGetLastError();
 }
 
 hipError_t launch_collect(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const int32_t* M,
-                          int32_t theta, const uint32_t* filter, const uint32_t* hot, const uint32_t* hot_table,
-                          const CandSet& cand, uint32_t* err, bool field, hipStream_t s) {
+                          int32_t theta, const uint32_t* filter, const uint32_t* hot, const CandSet& cand,
+                          uint32_t* err, bool field, hipStream_t s) {
   if (t.d <= (uint32_t)kTabLdsRows && mesh.group == 1u) {   // collect2_kernel takes ungrouped keys
     const uint32_t use_filter = (filter != nullptr && hot != nullptr) ? 1u : 0u;
     field = field && use_filter && collect_field_form(t);
-    const size_t lds = collect2_lds_bytes(t, use_filter != 0, field);
+    const uint32_t kb = key_bytes_kb(mesh.nch);
+    const size_t lds = collect2_lds_bytes(t, use_filter != 0, field, kb);
     const dim3 grid(grid_for((n + kCollectPPT - 1) / kCollectPPT, kCollectThreads, 256)), block(kCollectThreads);
     const CollectDesc cd{mesh, t, M, const_cast<uint32_t*>(filter), const_cast<uint32_t*>(hot),
-                         const_cast<uint32_t*>(hot_table), cand, err};
+                         cand, err};
     const CollectLaunch ca{&cd, pos, n, theta, use_filter, field, nullptr, nullptr, nullptr, nullptr, nullptr,
-                           key_bytes_kb(mesh.nch)};
+                           kb};
     launch_collect2_d(t.d, mesh.mode, t.hash_mode(), grid, block, lds, s, ca);
   } else {
     hipLaunchKernelGGL(collect_kernel<false>, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, pos, n, mesh, t, M, theta,
@@ -306,20 +334,22 @@ hipError_t launch_collect_batch(const CollectDesc* descs, const CollectDesc* hos
   if (count == 0 || nwg_total == 0) return hipSuccess;
   bool any_filter = false;
   size_t lds = 0;
+  uint32_t kb = 5;
+  for (uint32_t i = 0; i < count; ++i) kb = key_bytes_kb(host_descs[i].mesh.nch) > kb ? key_bytes_kb(host_descs[i].mesh.nch) : kb;
   for (uint32_t i = 0; i < count; ++i) {
     any_filter = any_filter || call.use_filter[i] != 0;
-    const size_t b = collect2_lds_bytes(host_descs[i].t, true, field);
+    const size_t b = collect2_lds_bytes(host_descs[i].t, true, field, kb);
     lds = b > lds ? b : lds;
   }
   if (any_filter) {
     const uint32_t fw = field ? kFieldFilterWords : (uint32_t)kFilterWords;
-    hipLaunchKernelGGL(collect_clear_batch_kernel, dim3(grid_for((uint64_t)fw + 1 + kHotSlots, 256, 256), count),
+    // the widest sketch decides the grid, so keep it low: the blocks of a narrow one have nothing to do
+    const uint32_t most = max(32u, 8192u / count), grid = min(filter_grid(d, w_max), most);
+    hipLaunchKernelGGL(collect_clear_batch_kernel, dim3(grid_for((uint64_t)fw + 1, 256, 256), count),
                        dim3(256), 0, s, descs, call, fw);
-    hipLaunchKernelGGL(filter_build_batch_kernel, dim3(filter_grid(d, w_max), count), dim3(kFilterThreads), 0, s, descs,
+    hipLaunchKernelGGL(filter_build_batch_kernel, dim3(grid, count), dim3(kFilterThreads), 0, s, descs,
                        call, field ? 1u : 0u);
   }
-  uint32_t kb = 5;
-  for (uint32_t i = 0; i < count; ++i) kb = key_bytes_kb(host_descs[i].mesh.nch) > kb ? key_bytes_kb(host_descs[i].mesh.nch) : kb;
   const CollectLaunch ca{nullptr, nullptr, 0, 0, 0, field, descs, wg_sketch, wg_first, wg_count, &call, kb};
   launch_collect2_d(d, mesh_mode, hm, dim3(nwg_total), dim3(kCollectThreads), lds, s, ca);
   return hipGetLastError();

@@ -33,6 +33,29 @@ void launch_collect2_five(uint32_t mode, int hm, dim3 grid, dim3 block, size_t l
 void launch_collect2_many(uint32_t d, uint32_t mode, int hm, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                           const CollectLaunch& c);
 
+// LDS of a collect workgroup: the hash (or probe) tables of kb key bytes, dw words an entry, the cache of
+// inserted keys, a queue of 64 keys (6 bytes each) per wave, the new keys that are not in the list yet
+// (with four control words), and the filter.  With the field-probe filter's 128 KiB the cache and the new
+// keys get what is left of the 160 KiB.
+constexpr int kCollectCache = 1024;
+template <bool FP, int KB>
+constexpr uint32_t collect2_cache() {
+  return FP ? (KB <= 5 ? 512u : 128u) : (uint32_t)kCollectCache;
+}
+template <bool FP, int KB>
+constexpr uint32_t collect2_fresh() {
+  return FP && KB > 5 ? 126u : 254u;
+}
+template <bool FP, int KB>
+constexpr size_t collect2_lds(uint32_t dw, uint32_t filter_words) {
+  return (size_t)KB * 1024 * dw + collect2_cache<FP, KB>() * 8ull + (kCollectThreads / 64) * 64 * 6ull +
+         collect2_fresh<FP, KB>() * 8ull + 16ull + filter_words * 4ull;
+}
+static_assert(collect2_lds<true, 6>(4, kFieldFilterWords) <= 160 * 1024 &&
+                  collect2_lds<true, 5>(4, kFieldFilterWords) <= 160 * 1024 &&
+                  collect2_lds<false, 6>(8, kFilterWords) <= 160 * 1024,
+              "one workgroup's LDS");
+
 namespace collect2 {
 
 // Row-interleaved collect for d <= 8 on an ungrouped mesh.  When a Bloom filter of the hot (row, bucket,
@@ -57,7 +80,6 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
   const int32_t* __restrict__ M = c.M;
   const uint32_t* __restrict__ filter = c.filter;
   const uint32_t* __restrict__ hot = c.hot;
-  const uint32_t* __restrict__ hot_table = c.hot_table;
   const CandSet& cand = c.cand;
   const uint64_t* set = cand.set;
   const uint32_t slot_mask = cand.slot_mask;
@@ -68,21 +90,29 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
   static_assert(!FP || (D <= 5 && (HM == kHashPacked || HM == kHashMulHi)),
                 "field probes: d <= 5 rows of 25 bits, packed or multiply-high buckets");
   extern __shared__ __align__(16) uint32_t lds3[];
+  constexpr uint32_t CE = collect2_cache<FP, KB>();
+  constexpr uint32_t kWaves = kCollectThreads / 64u;
   uint32_t* ti = lds3;
-  uint64_t* cache = (uint64_t*)(ti + kTableWords * DP);   // kCollectCache keys
-  uint32_t* filt = (uint32_t*)(cache + kCollectCache);
+  uint64_t* cache = (uint64_t*)(ti + KB * 256 * DP);   // CE keys
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* qlo = (uint32_t*)(cache + CE) + 64u * wave;   // this wave's queue of 64 keys: low words, then high halves
+  uint16_t* qhi = (uint16_t*)((uint32_t*)(cache + CE) + 64u * kWaves) + 64u * wave;
+  constexpr uint32_t NF = collect2_fresh<FP, KB>();
+  uint64_t* fresh = (uint64_t*)((uint32_t*)(cache + CE) + 96u * kWaves);   // NF new keys
+  // ctl: slots of fresh handed out, the first ones refused (all after are), the set is full, list base
+  uint32_t* ctl = (uint32_t*)(fresh + NF);
+  uint32_t* filt = ctl + 4;
   const uint32_t nhot = use_filter ? *hot : 0xFFFFFFFFu;
   // a hot item takes up to fspan entries of the field-probe filter (1 for w = 2^P)
   const bool uf = use_filter && (FP ? (uint64_t)nhot * t.fspan <= kFieldFilterMaxItems : nhot <= kFilterMaxItems);
-  // the exact hot-item set replaces the counter reads when it holds every hot item
-  const bool uh = use_filter && hot_table != nullptr && nhot <= kHotMaxItems;
   if (uf) {
     using V4 = uint32_t __attribute__((ext_vector_type(4)));
     static_assert(FW % 4 == 0, "16-byte pieces");
     for (uint32_t i = threadIdx.x; i < FW / 4; i += blockDim.x) ((V4*)filt)[i] = ((const V4*)filter)[i];
   }
-  for (uint32_t i = threadIdx.x; i < (uint32_t)kCollectCache; i += blockDim.x) cache[i] = kEmptyKey;
-  stage_tables<DP>(ti, FP ? t.tabq : (HM == kHashPacked ? t.tabp : t.tabi), (uint32_t)KB);
+  for (uint32_t i = threadIdx.x; i < CE; i += blockDim.x) cache[i] = kEmptyKey;
+  if (threadIdx.x < 4) ctl[threadIdx.x] = threadIdx.x == 1 ? NF : 0u;
+  stage_tables<DP>(ti, FP ? t.tabq : (HM == kHashPacked ? t.tabp : t.tabi), (uint32_t)KB, (uint32_t)KB);
   // (bucket, sign) of every row for the exact test: from the staged tables, or (FP) from
   // the packed or row-interleaved tables in device memory over all six key bytes
   auto exact_rows = [&](uint64_t key, uint32_t (&bk)[D], uint32_t (&ng)[D]) {
@@ -94,6 +124,56 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
   constexpr uint32_t NT = kCollectThreads;
   const uint64_t chunk = (uint64_t)NT * PPT;
   bool bad = false;
+  // The particles that may pass wait in the wave's queue and are looked up and tested 64 at a time:
+  // where a tenth of them reaches the test, a test in place runs with a tenth of its lanes.
+  uint32_t queued = 0;
+  auto cache_slot = [](uint64_t key) { return (uint32_t)(key ^ (key >> 21)) & (CE - 1u); };
+  auto flush = [&]() {
+    const bool act = lane < queued;
+    const uint64_t key = act ? (uint64_t)qhi[lane] << 32 | qlo[lane] : 0ull;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    queued = 0;
+    // a key already in the set needs no exact test: the set only ever gains keys
+    const uint64_t s0 = act ? set[(uint32_t)slot_mix(key) & slot_mask] : kEmptyKey;
+    bool in = act && s0 == key, is_new = false;
+    if (act && !in && s0 != kEmptyKey) in = set_contains(set, slot_mask, key);   // a longer probe run
+    if (act && !in) {
+      uint32_t bk[D], ng[D];
+      exact_rows(key, bk, ng);
+#pragma unroll
+      for (int r = 0; r < D; ++r) ng[r] &= t.cm ^ 1u;
+      in = rows_pass<D>(bk, ng, need, nullptr, M, t.w, theta);
+      if (in)
+        is_new = set_claim(cand, key, err, [&]() {
+          return __hip_atomic_load(&ctl[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
+        });
+    }
+    if (in) __hip_atomic_store(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    // New keys go into the list with the workgroup's others when it ends, past NF of them here and now:
+    // one or two at a time they kept the kernel waiting for the count (about 40 ns an add, one after
+    // the other over all XCDs).  The count tells then whether the set is full.
+    const uint64_t who = __ballot(is_new);
+    if (who == 0) return;
+    const uint32_t more = (uint32_t)__popcll(who);
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+    uint32_t at = 0;
+    if (lane == 0) at = __hip_atomic_fetch_add(&ctl[0], more, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (at + more <= NF) {
+      if (is_new) fresh[at + rank] = key;
+      return;
+    }
+    if (lane == 0) {
+      __hip_atomic_fetch_min(&ctl[1], at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      at = atomicAdd(cand.count, more);
+    }
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (is_new && at + rank < cand.max_cand) cand.list[at + rank] = key;
+    if (at + more > cand.max_cand && lane == 0) {
+      atomicOr(err, kErrCapacity);
+      __hip_atomic_store(&ctl[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  };
   for (uint64_t first = (uint64_t)g * chunk; first < n; first += (uint64_t)nwg * chunk) {
     const bool full = first + chunk <= n;
     // all PPT position loads are issued before any is used; float records come through a
@@ -169,113 +249,55 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j) verdict(j, (fine >> j) & 1u);
-    // The particles that may pass.  A key seen recently by this workgroup, or already in the
-    // set, needs no exact test: heavy cells repeat thousands of times, and the set only ever
-    // gains keys.  The first set slot of every candidate is loaded before any is compared,
-    // so that the thread waits on one round trip for all its keys rather than one per key.
-    auto cache_slot = [](uint64_t key) { return (uint32_t)(key ^ (key >> 21)) & (kCollectCache - 1); };
+    // The particles that may pass.  A key seen recently by this workgroup needs no look-up: heavy
+    // cells repeat thousands of times.
     uint32_t todo = maybe;
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      if ((todo >> j) & 1u)
-        if (__hip_atomic_load(&cache[cache_slot(keys[j])], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == keys[j])
-          todo &= ~(1u << j);
-    }
-    // the first slot of each key's probe sequence in the set
-    uint64_t s0[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      s0[j] = kEmptyKey;
-      if ((todo >> j) & 1u) s0[j] = set[(uint32_t)slot_mix(keys[j]) & slot_mask];
-    }
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      if (!((todo >> j) & 1u)) continue;
-      bool in = s0[j] == keys[j];
-      if (!in && s0[j] != kEmptyKey) in = set_contains(set, slot_mask, keys[j]);   // a longer probe run
-      if (in) {
-        __hip_atomic_store(&cache[cache_slot(keys[j])], keys[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int j = 0; j < PPT; ++j)
+      if (__hip_atomic_load(&cache[cache_slot(keys[j])], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == keys[j])
         todo &= ~(1u << j);
+    uint32_t some = 0;   // the particles j that some lane has to look up
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) some |= (__ballot((todo >> j) & 1u) != 0 ? 1u : 0u) << j;
+    static_assert(PPT == 8, "the selection below");
+#pragma unroll 1
+    for (; some != 0; some &= some - 1u) {
+      const uint32_t j = (uint32_t)__builtin_ctz(some);
+      uint64_t key;
+      switch (j) {
+        case 0: key = keys[0]; break;
+        case 1: key = keys[1]; break;
+        case 2: key = keys[2]; break;
+        case 3: key = keys[3]; break;
+        case 4: key = keys[4]; break;
+        case 5: key = keys[5]; break;
+        case 6: key = keys[6]; break;
+        default: key = keys[7]; break;
       }
+      const bool open = (todo >> j) & 1u;
+      const uint64_t who = __ballot(open);
+      const uint32_t more = (uint32_t)__popcll(who);
+      if (queued + more > 64u) flush();
+      if (open) {
+        const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+        qlo[at] = (uint32_t)key;
+        qhi[at] = (uint16_t)(key >> 32);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      queued += more;
     }
-    // Other threads of the workgroup may have inserted a key since the first cache check;
-    // looking again before the exact test spares it (one LDS read).
-    auto recheck = [&](uint64_t key) {
-      return __hip_atomic_load(&cache[cache_slot(key)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == key;
-    };
-    // The exact test of the rest.  With the hot-item set (2 MiB, resident in L2) the first
-    // slot of every row of a group of keys (four for d <= 5, else two) is loaded before any
-    // is compared.  Without it the counters are read row by row until the answer is known;
-    // in a large table those reads go to HBM, and reading all d rows at once was no faster.
-    if (uh) {
-      constexpr int GQ = D <= 5 ? 4 : 2;
-      static_assert(PPT % GQ == 0, "whole groups of keys");
-#pragma unroll
-      for (int j0 = 0; j0 < PPT; j0 += GQ) {
-        if (!((todo >> j0) & ((1u << GQ) - 1u))) continue;
-        uint32_t item[GQ][D], v[GQ][D];
-#pragma unroll
-        for (int q = 0; q < GQ; ++q) {
-          if (!((todo >> (j0 + q)) & 1u)) continue;
-          if (recheck(keys[j0 + q])) {
-            todo &= ~(1u << (j0 + q));
-            continue;
-          }
-          uint32_t bk[D], ng[D];
-          exact_rows(keys[j0 + q], bk, ng);
-#pragma unroll
-          for (int r = 0; r < D; ++r) {
-            item[q][r] = hot_item((uint32_t)r, bk[r], ng[r] & (t.cm ^ 1u));
-            v[q][r] = hot_table[hot_slot(item[q][r])];
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < GQ; ++q) {
-          const int j = j0 + q;
-          if (!((todo >> j) & 1u)) continue;
-          // row r passes (sign * M >= theta) exactly when its item is in the hot set
-          uint32_t pass = 0;
-#pragma unroll
-          for (int r = 0; r < D; ++r) {
-            bool hit = v[q][r] == item[q][r];
-            if (!hit && v[q][r] != kHotEmpty) {
-              uint32_t sl = (hot_slot(item[q][r]) + 1) & (kHotSlots - 1);
-              for (uint32_t probe = 1; probe < kHotSlots; ++probe) {
-                const uint32_t x = hot_table[sl];
-                if (x == item[q][r]) {
-                  hit = true;
-                  break;
-                }
-                if (x == kHotEmpty) break;
-                sl = (sl + 1) & (kHotSlots - 1);
-              }
-            }
-            pass += hit ? 1u : 0u;
-          }
-          if (pass >= need) {
-            set_insert(cand, keys[j], err);
-            __hip_atomic_store(&cache[cache_slot(keys[j])], keys[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          }
-        }
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < PPT; ++j) {
-        if (!((todo >> j) & 1u) || recheck(keys[j])) continue;
-        uint32_t bk[D], ng[D];
-        exact_rows(keys[j], bk, ng);
-        uint32_t pass = 0;
-#pragma unroll
-        for (int r = 0; r < D; ++r) {
-          if (pass >= need || pass + (uint32_t)(D - r) < need) break;
-          const uint32_t c = (uint32_t)M[(uint64_t)r * t.w + bk[r]];
-          if ((int32_t)((ng[r] & (t.cm ^ 1u)) ? 0u - c : c) >= theta) ++pass;
-        }
-        if (pass >= need) {
-          set_insert(cand, keys[j], err);
-          __hip_atomic_store(&cache[cache_slot(keys[j])], keys[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-      }
+  }
+  if (queued) flush();
+  __syncthreads();
+  const uint32_t nf = min(ctl[0], ctl[1]);   // the slots handed out before the first that was refused
+  if (nf != 0) {
+    if (threadIdx.x == 0) ctl[3] = atomicAdd(cand.count, nf);
+    __syncthreads();
+    const uint32_t base = ctl[3];
+    for (uint32_t i = threadIdx.x; i < nf; i += kCollectThreads) {
+      if (base + i < cand.max_cand) cand.list[base + i] = fresh[i];
+      else atomicOr(err, kErrCapacity);
     }
   }
   if (bad) atomicOr(err, kErrDomain);
@@ -329,11 +351,9 @@ void launch_collect2_m(int hm, dim3 grid, dim3 block, size_t lds, hipStream_t s,
       launch_collect2_one<D, MM, kHashPacked, true>(grid, block, lds, s, c);
       return;
     }
-    if constexpr (MM != kMeshPacked) {
-      if (hm == kHashMulHi && c.field) {
-        launch_collect2_one<D, MM, kHashMulHi, true>(grid, block, lds, s, c);
-        return;
-      }
+    if (hm == kHashMulHi && c.field) {
+      launch_collect2_one<D, MM, kHashMulHi, true>(grid, block, lds, s, c);
+      return;
     }
   }
   if constexpr (D >= 5) {

@@ -124,31 +124,9 @@ struct KeyWalk {
   __device__ __forceinline__ void test(uint64_t key) {
     uint32_t bk[D], ng[D];
     rows_bucket_sign_kb<D, HM, kChars>(HM == kHashPacked ? a.t.tabp : a.t.tabi, key, a.t.w, a.t.wshift, bk, ng);
-    uint32_t pass = 0;
-    if (uh) {
-      uint32_t item[D], v[D];
 #pragma unroll
-      for (int r = 0; r < D; ++r) {
-        item[r] = hot_item((uint32_t)r, bk[r], ng[r] & (a.t.cm ^ 1u));
-        v[r] = a.hot_table[hot_slot(item[r])];
-      }
-#pragma unroll
-      for (int r = 0; r < D; ++r) {
-        uint32_t sl = hot_slot(item[r]);
-        for (uint32_t probe = 0; probe < kHotSlots && v[r] != item[r] && v[r] != kHotEmpty; ++probe) {
-          sl = (sl + 1) & (kHotSlots - 1);
-          v[r] = a.hot_table[sl];
-        }
-        pass += v[r] == item[r] ? 1u : 0u;
-      }
-    } else {
-      uint32_t c[D];
-#pragma unroll
-      for (int r = 0; r < D; ++r) c[r] = (uint32_t)a.M[(uint64_t)r * a.t.w + bk[r]];
-#pragma unroll
-      for (int r = 0; r < D; ++r) pass += (int32_t)((ng[r] & (a.t.cm ^ 1u)) ? 0u - c[r] : c[r]) >= a.theta ? 1u : 0u;
-    }
-    if (pass >= need) set_insert(a.cand, key, a.err);
+    for (int r = 0; r < D; ++r) ng[r] &= a.t.cm ^ 1u;
+    if (rows_pass<D>(bk, ng, need, uh ? a.hot_table : nullptr, a.M, a.t.w, a.theta)) set_insert(a.cand, key, a.err);
   }
   // The lanes of who hold keys base + lane that pass the filter (who: the same in every lane).
   __device__ __forceinline__ void offer(uint64_t who, uint64_t base) {
@@ -226,26 +204,15 @@ struct KeyWalk {
   }
 };
 
-// Without a filter: all rows hashed from the tables in LDS and the counters read: first the rows that
-// no answer can do without, together, then the rest where the answer is still open.
+// Without a filter: all rows hashed from the tables in LDS and the counters read.
 template <int D, int HM>
 __device__ __forceinline__ void direct_test(const DictArgs& a, const uint32_t* ti, uint64_t key) {
-  constexpr int N0 = D - ((D - 1) >> 1);   // rows needed (Count Sketch)
-  const uint32_t need = a.t.cm ? (uint32_t)D : (uint32_t)N0;
-  uint32_t bk[D], ng[D], c[D];
+  const uint32_t need = a.t.cm ? (uint32_t)D : (uint32_t)(D - ((D - 1) >> 1));
+  uint32_t bk[D], ng[D];
   rows_bucket_sign<D, HM>(ti, key, a.nch, a.t.w, a.t.wshift, bk, ng);
-  uint32_t pass = 0;
 #pragma unroll
-  for (int r = 0; r < N0; ++r) c[r] = (uint32_t)a.M[(uint64_t)r * a.t.w + bk[r]];
-#pragma unroll
-  for (int r = 0; r < N0; ++r) pass += (int32_t)((ng[r] & (a.t.cm ^ 1u)) ? 0u - c[r] : c[r]) >= a.theta ? 1u : 0u;
-  if (pass < need && pass + (uint32_t)(D - N0) >= need) {
-#pragma unroll
-    for (int r = N0; r < D; ++r) c[r] = (uint32_t)a.M[(uint64_t)r * a.t.w + bk[r]];
-#pragma unroll
-    for (int r = N0; r < D; ++r) pass += (int32_t)((ng[r] & (a.t.cm ^ 1u)) ? 0u - c[r] : c[r]) >= a.theta ? 1u : 0u;
-  }
-  if (pass >= need) set_insert(a.cand, key, a.err);
+  for (int r = 0; r < D; ++r) ng[r] &= a.t.cm ^ 1u;
+  if (rows_pass<D>(bk, ng, need, nullptr, a.M, a.t.w, a.theta)) set_insert(a.cand, key, a.err);
 }
 
 template <int D, int HM, bool FP, bool LIST>

@@ -91,7 +91,6 @@ constexpr int kBin2Threads = 1024;                 // row-interleaved bin kernel
 constexpr int bin2_ppt(int d) { return d == 1 ? 16 : (d == 2 ? 12 : (d <= 5 ? 8 : 4)); }
 constexpr int kBin2Rows = 2;                       // rows sorted per LDS pass
 constexpr int kCollectThreads = 1024;
-constexpr int kCollectCache = 1024;               // per-workgroup cache of inserted keys
 constexpr int kCollectPPT = 8;                    // particles per thread per round (loads in flight)
 constexpr int kBinThreads = 512;
 constexpr int kBinPPT = 16;                       // particles per thread per tile
@@ -279,7 +278,6 @@ struct CollectDesc {
   const int32_t* M;
   uint32_t* filter;           // Bloom filter (device) or NULL
   uint32_t* hot;              // its hot-item count
-  uint32_t* hot_table;        // exact hot-item set or NULL
   CandSet cand;
   uint32_t* err;
 };
@@ -290,10 +288,9 @@ struct CollectCall {
   int32_t theta[kMaxBatch];
   uint32_t use_filter[kMaxBatch];   // theta > 0 and the sketch has a filter
 };
-size_t collect2_lds_bytes(const Tables& t, bool use_filter, bool field);
 // The field-probe filter serves this sketch (d = 5, packed hash, probe tables).
 bool collect_field_form(const Tables& t);
-// Batched candidate pass: the clears, the filter and hot-set builds of every sketch whose
+// Batched candidate pass: the clears and the filter builds of every sketch whose
 // theta is > 0, then one collect launch of nwg_total workgroups (workgroup g serves sketch
 // wg_sketch[g] as its workgroup g - wg_first[sketch] of wg_count[sketch]).  All sketches
 // share d, the mesh mode and the hash mode; field: every one uses the field-probe filter.
@@ -305,13 +302,13 @@ hipError_t launch_collect_batch(const CollectDesc* descs, const CollectDesc* hos
 // field: the filter is a field-probe filter (built with field = true; used only when the
 // sketch has probe tables, d = 5 and the packed hash).
 hipError_t launch_collect(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const int32_t* M,
-                          int32_t theta, const uint32_t* filter, const uint32_t* hot, const uint32_t* hot_table,
-                          const CandSet& cand, uint32_t* err, bool field, hipStream_t s);
+                          int32_t theta, const uint32_t* filter, const uint32_t* hot, const CandSet& cand,
+                          uint32_t* err, bool field, hipStream_t s);
 // Short streams: reading every row's counter for every particle takes less than building the filter
-// from all the counters and staging it.  Measured, clear and collect, exact reads against the filter:
-// d = 5: w = 2^16, 2^18 particles 32 and 70 us, 2^19 58 and 86, 2^20 271 and 214; w = 2^20, 2^19
-// 72 and 105, 2^20 131 and 132; w = 2^24, 2^20 156 and 206; d = 8, w = 2^16: 2^19 66 and 91, 2^20
-// 118 and 123.
+// from all the counters and staging it.  Measured, clear and collect in us, exact reads against the
+// filter: d = 5: w = 2^14, 2^19 particles 27 and 31, 2^20 54 and 61; w = 2^16, 2^18 17 and 28, 2^19 24
+// and 29, 2^20 56 and 31; w = 2^20, 2^18 25 and 38, 2^19 42 and 40, 2^20 76 and 41; w = 2^24, 2^20 105
+// and 110; d = 8, w = 2^16: 2^18 21 and 35, 2^19 32 and 36, 2^20 58 and 39.
 bool collect_is_short(uint64_t n, const Tables& t);
 hipError_t launch_collect_short(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, const int32_t* M,
                                 int32_t theta, const CandSet& cand, uint32_t* err, hipStream_t s);

@@ -119,33 +119,80 @@ __device__ __forceinline__ bool set_contains(const uint64_t* set, uint32_t mask,
   return false;
 }
 
-__device__ __forceinline__ void set_insert(const CandSet& c, uint64_t key, uint32_t* err) {
+// Put a key into the set: true when this call did (the caller then appends it to the list), false when
+// it was there already.  room(): may a new key still go in?  (No room is the capacity error.)
+template <class Room>
+__device__ __forceinline__ bool set_claim(const CandSet& c, uint64_t key, uint32_t* err, Room room) {
   const uint32_t mask = c.slot_mask;
   uint32_t i = (uint32_t)slot_mix(key) & mask;
   for (uint32_t probe = 0; probe <= mask && probe < kMaxProbe; ++probe) {
-    // A slot only ever changes from empty to a key, so a stale read can only show
-    // "empty"; the compare-and-swap then tells the truth.
+    // A slot only ever changes from empty to a key, so a stale read can only show "empty"; the
+    // compare-and-swap then tells the truth.
     const uint64_t cur = c.set[i];
-    if (cur == key) return;
+    if (cur == key) return false;
     if (cur == kEmptyKey) {
-      // a new key: once the set holds max_candidates keys no more go in (capacity error)
-      if (__hip_atomic_load(c.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= c.max_cand) {
-        atomicOr(err, kErrCapacity);
-        return;
-      }
+      if (!room()) break;
       const uint64_t old = atomicCAS((unsigned long long*)&c.set[i], (unsigned long long)kEmptyKey,
                                      (unsigned long long)key);
-      if (old == kEmptyKey) {
-        const uint32_t at = atomicAdd(c.count, 1u);
-        if (at < c.max_cand) c.list[at] = key;
-        else atomicOr(err, kErrCapacity);
-        return;
-      }
-      if (old == key) return;
+      if (old == kEmptyKey) return true;
+      if (old == key) return false;
     }
     i = (i + 1) & mask;
   }
   atomicOr(err, kErrCapacity);
+  return false;
+}
+
+// A key into the set and the list; once the set holds max_candidates keys no more go in.
+__device__ __forceinline__ void set_insert(const CandSet& c, uint64_t key, uint32_t* err) {
+  if (!set_claim(c, key, err, [&]() {
+        return __hip_atomic_load(c.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < c.max_cand;
+      }))
+    return;
+  const uint32_t at = atomicAdd(c.count, 1u);
+  if (at < c.max_cand) c.list[at] = key;
+  else atomicOr(err, kErrCapacity);
+}
+
+// Do at least `need` rows of an item (buckets bk, sign bits ng) pass, sign * M >= theta?  With the exact
+// hot-item set the first slots of all rows are loaded before any is compared; without it the counters:
+// first the rows that no answer can do without, together, then the rest where the answer is still open.
+template <int D>
+__device__ __forceinline__ bool rows_pass(const uint32_t (&bk)[D], const uint32_t (&ng)[D], uint32_t need,
+                                          const uint32_t* __restrict__ hot_table, const int32_t* __restrict__ M,
+                                          uint32_t w, int32_t theta) {
+  uint32_t pass = 0;
+  if (hot_table != nullptr) {
+    uint32_t item[D], v[D];
+#pragma unroll
+    for (int r = 0; r < D; ++r) {
+      item[r] = hot_item((uint32_t)r, bk[r], ng[r]);
+      v[r] = hot_table[hot_slot(item[r])];
+    }
+#pragma unroll
+    for (int r = 0; r < D; ++r) {
+      uint32_t sl = hot_slot(item[r]);
+      for (uint32_t probe = 1; probe < kHotSlots && v[r] != item[r] && v[r] != kHotEmpty; ++probe) {
+        sl = (sl + 1) & (kHotSlots - 1);
+        v[r] = hot_table[sl];
+      }
+      pass += v[r] == item[r] ? 1u : 0u;
+    }
+    return pass >= need;
+  }
+  constexpr int N0 = D - ((D - 1) >> 1);   // rows needed (Count Sketch)
+  uint32_t c[D];
+#pragma unroll
+  for (int r = 0; r < N0; ++r) c[r] = (uint32_t)M[(uint64_t)r * w + bk[r]];
+#pragma unroll
+  for (int r = 0; r < N0; ++r) pass += (int32_t)(ng[r] ? 0u - c[r] : c[r]) >= theta ? 1u : 0u;
+  if (pass < need && pass + (uint32_t)(D - N0) >= need) {
+#pragma unroll
+    for (int r = N0; r < D; ++r) c[r] = (uint32_t)M[(uint64_t)r * w + bk[r]];
+#pragma unroll
+    for (int r = N0; r < D; ++r) pass += (int32_t)(ng[r] ? 0u - c[r] : c[r]) >= theta ? 1u : 0u;
+  }
+  return pass >= need;
 }
 
 // ---- the admitted coarse cells of the learned router: an LDS hash of their keys (load at

@@ -1,0 +1,135 @@
+"""The candidate pass with its per-wave queues, against the oracle's estimates, exactly, where it can go
+wrong: every form of the filter for float and packed streams and odd widths, few hot counters, dense
+filters, too many for one (every particle reaches the exact test), more new keys in a workgroup than it
+holds back, a set that fills up, both sides of the short-stream rule, and a batch of all of these."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1711_00975_amd as csk
+
+pytestmark = pytest.mark.gpu
+
+L, DELTA, THETA = 100.0, 0.1, 10
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _stream(n, seed):
+    """Half of the particles in 60^3 cells (about two each at n = 9e5), a tenth in one cell, wrapped ones."""
+    rng = np.random.default_rng(seed)
+    pos = np.where((rng.random(n) < 0.5)[:, None], rng.uniform(0, L, (n, 3)), rng.uniform(40, 46, (n, 3)))
+    pos[rng.random(n) < 0.1] = 7.77
+    pos = pos.astype(np.float32)
+    pos[rng.choice(n, n // 100, replace=False), 1] = np.float32(-3.0)
+    return pos
+
+
+def _counters(d, w, share, variant, seed):
+    rng = np.random.default_rng(seed)
+    M = rng.integers(-THETA + 1, THETA, (d, w))
+    big = rng.integers(THETA, 1000, (d, w)) * (1 if variant else rng.choice([-1, 1], (d, w)))
+    return np.where(rng.random((d, w)) < share, big, np.abs(M) if variant else M).astype(np.int32)
+
+
+def _want(M, T, keys, theta, variant):
+    u = np.unique(keys)
+    e = oracle.estimate(M, T, u, variant).astype(np.int64)
+    u, e = u[e >= theta], e[e >= theta]
+    order = np.lexsort((u, -e))
+    return u[order], e[order]
+
+
+def _check(s, want):
+    kg, eg, _ = s.topk(len(want[0]) + 1)
+    assert np.array_equal(kg.cpu().numpy().view(np.uint64), want[0])
+    assert np.array_equal(eg.cpu().numpy(), want[1])
+
+
+@pytest.mark.parametrize("d,w,variant", [(5, 1 << 16, 0), (5, 70_001, 0), (5, 70_001, 1), (5, (1 << 24) + 5, 0),
+                                         (2, 1 << 16, 0), (4, 50_021, 1), (6, 1 << 16, 0), (8, 1 << 16, 0),
+                                         (8, 99_991, 0)])
+@pytest.mark.parametrize("share", [0.001, 0.3, 0.97])
+@pytest.mark.parametrize("packed", [False, True])
+def test_collect_forms(d, w, variant, share, packed):
+    print("queue", d, w, variant, share, packed, flush=True)
+    if w > 1 << 24:
+        share /= 100     # about 1e5 and 1e6 hot counters
+    n, seed = 1_300_003 if w <= 1 << 20 else (1 << 20) + 7, 5
+    pos = _stream(n, d + w)
+    words = oracle.pack(pos, L)
+    keys = oracle.keys_packed(words, DELTA, L) if packed else oracle.keys(pos, DELTA, L)
+    M, T = _counters(d, w, share, variant, d * w), oracle.hash_tables(seed, d)
+    s = csk.Sketch(d, w, seed, variant, 1 << 21)
+    try:
+        s.set_counters(_dev(M))
+        for theta in (THETA, 600):
+            s.clear_candidates()
+            if packed:
+                s.collect_packed(_dev(words.view(np.int64)), DELTA, L, theta)
+            else:
+                s.collect(_dev(pos), DELTA, L, theta)
+            _check(s, _want(M, T, keys, theta, variant))
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("w", [1 << 14, 1 << 20])
+@pytest.mark.parametrize("over", [0, 1])
+def test_both_sides_of_the_short_rule(w, over):
+    n, seed = (1 << 19) + w // 32 + over, 5
+    pos = _stream(n, n)
+    M, T = _counters(5, w, 0.2, 0, w), oracle.hash_tables(seed, 5)
+    s = csk.Sketch(5, w, seed, 0, 1 << 20)
+    try:
+        s.set_counters(_dev(M))
+        s.collect(_dev(pos), DELTA, L, THETA)
+        _check(s, _want(M, T, oracle.keys(pos, DELTA, L), THETA, 0))
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("n", [200_000, 1_300_003])
+@pytest.mark.parametrize("cap", [300, 5000])
+def test_a_set_that_fills_up(n, cap):
+    print("full", n, cap, flush=True)
+    seed = 5
+    pos = _stream(n, n + cap)
+    M, T = _counters(5, 1 << 16, 0.97, 0, cap), oracle.hash_tables(seed, 5)
+    s = csk.Sketch(5, 1 << 16, seed, 0, cap)
+    try:
+        s.set_counters(_dev(M))
+        s.collect(_dev(pos), DELTA, L, THETA)
+        with pytest.raises(csk.CskError) as ei:
+            s.topk(10)
+        assert ei.value.code == csk.CSK_E_CAPACITY
+        s.clear_candidates()
+        s.collect(_dev(pos[:cap]), DELTA, L, THETA)    # fits: the set is whole again
+        _check(s, _want(M, T, oracle.keys(pos[:cap], DELTA, L), THETA, 0))
+    finally:
+        s.close()
+
+
+def test_a_batch_of_them():
+    import torch
+    shapes = [(700_001, 1 << 16, 0.3), (90_000, 1 << 14, 0.97), (1_300_003, 1 << 17, 0.97), (5, 1 << 15, 0.5)]
+    sk = [csk.Sketch(5, w, 20 + i, 0, 1 << 20) for i, (_, w, _) in enumerate(shapes)]
+    try:
+        pos = [_stream(max(n, 100), 70 + i)[:n] for i, (n, _, _) in enumerate(shapes)]
+        b = csk.Batch(sk, [n for n, _, _ in shapes], DELTA, L)
+        try:
+            Ms = [_counters(5, w, share, 0, w) for _, w, share in shapes]
+            for s, M in zip(sk, Ms):
+                s.set_counters(_dev(M))
+            b.collect([_dev(p) for p in pos], [THETA] * len(sk))
+            torch.cuda.synchronize()
+        finally:
+            b.close()
+        for i, (s, M, p) in enumerate(zip(sk, Ms, pos)):
+            _check(s, _want(M, oracle.hash_tables(20 + i, 5), oracle.keys(p, DELTA, L), THETA, 0))
+    finally:
+        for s in sk:
+            s.close()
