@@ -52,31 +52,87 @@ hipError_t launch_pack(const float* pos, uint64_t n, const Mesh& pm, uint64_t* o
 
 // ------------------------------------------------------------------ query
 
-template <int MAXD, bool TAB_LDS>
+// Bound by the random counter reads (d per key, in tables beyond L2; about 5.5e10/s from 320 MiB, 7.3e10/s
+// from 20 MiB): the hash tables are staged in LDS, row-interleaved or packed, by few large workgroups
+// (3900 small ones staged 30 KiB each), and the counters of all rows of two keys are asked for before any is
+// used.  2^20 keys, d = 5: w = 2^20 111 us before, 74 us so; w = 2^24 130 and 101 us.
+template <int D, int HM>
+__global__ __launch_bounds__(1024) void query_rows_kernel(const uint64_t* __restrict__ keys, uint64_t m, Tables t,
+                                                          const int32_t* __restrict__ M, int32_t* __restrict__ est) {
+  __shared__ __align__(16) uint32_t ti[kTableWords * HashWords<D, HM>::value];
+  stage_tables<HashWords<D, HM>::value>(ti, HM == kHashPacked ? t.tabp : t.tabi, (uint32_t)kChars);
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += 2 * stride) {
+    const uint64_t i2 = i + stride;
+    const uint64_t key[2] = {keys[i] & 0xFFFFFFFFFFFFull, i2 < m ? keys[i2] & 0xFFFFFFFFFFFFull : 0ull};
+    uint32_t c[2][D], ng[2][D];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      uint32_t bk[D];
+      rows_bucket_sign_kb<D, HM, kChars>(ti, key[q], t.w, t.wshift, bk, ng[q]);
+#pragma unroll
+      for (int r = 0; r < D; ++r) c[q][r] = (uint32_t)M[(uint64_t)r * t.w + bk[r]];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      int32_t v[D];
+#pragma unroll
+      for (int r = 0; r < D; ++r) v[r] = (int32_t)((ng[q][r] & (t.cm ^ 1u)) ? 0u - c[q][r] : c[q][r]);
+      int32_t e;
+      if (t.cm) {
+        e = v[0];
+#pragma unroll
+        for (int r = 1; r < D; ++r) e = min(e, v[r]);
+      } else {
+        e = lower_median<D>(v, D);
+      }
+      if (q == 0) est[i] = e;
+      else if (i2 < m) est[i2] = e;
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void query_kernel(const uint64_t* __restrict__ keys, uint64_t m, Tables t,
                                                     const int32_t* __restrict__ M, int32_t* __restrict__ est) {
-  __shared__ uint32_t tabs_lds[TAB_LDS ? kTabLdsRows * kTableWords : 1];
-  const uint32_t* tabs = t.tab;
-  if (TAB_LDS) {
-    load_tables(tabs_lds, t.tab, t.d);
-    __syncthreads();
-    tabs = tabs_lds;
-  }
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
-    est[i] = estimate_key<MAXD>(tabs, M, t.d, t.w, t.cm, keys[i] & 0xFFFFFFFFFFFFull);
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride)
+    est[i] = estimate_key<32>(t.tab, M, t.d, t.w, t.cm, keys[i] & 0xFFFFFFFFFFFFull);
+}
+
+template <int D>
+static void launch_query_d(const uint64_t* keys, uint64_t m, const Tables& t, const int32_t* M, int32_t* est,
+                           hipStream_t s) {
+  const uint32_t nt = m < (1u << 18) ? 256u : 1024u;   // few keys: over more CUs, each reads so many words at a time
+  const dim3 grid(grid_for(m, nt, 512)), block(nt);
+  const int hm = t.hash_mode();
+  if constexpr (D >= 5) {
+    if (hm == kHashPacked) {
+      hipLaunchKernelGGL((query_rows_kernel<D, kHashPacked>), grid, block, 0, s, keys, m, t, M, est);
+      return;
+    }
   }
+  if (hm == kHashMulHi) hipLaunchKernelGGL((query_rows_kernel<D, kHashMulHi>), grid, block, 0, s, keys, m, t, M, est);
+  else hipLaunchKernelGGL((query_rows_kernel<D, kHashShift>), grid, block, 0, s, keys, m, t, M, est);
 }
 
 hipError_t launch_query(const uint64_t* keys, uint64_t m, const Tables& t, const int32_t* M, int32_t* est,
                         hipStream_t s) {
-  const dim3 grid(grid_for(m, 256, 8192));
-  if (t.d <= (uint32_t)kTabLdsRows)
-    hipLaunchKernelGGL((query_kernel<kTabLdsRows, true>), grid, dim3(256), 0, s, keys, m, t, M, est);
-  else
-    hipLaunchKernelGGL((query_kernel<32, false>), grid, dim3(256), 0, s, keys, m, t, M, est);
+  switch (t.d) {
+    case 1: launch_query_d<1>(keys, m, t, M, est, s); break;
+    case 2: launch_query_d<2>(keys, m, t, M, est, s); break;
+    case 3: launch_query_d<3>(keys, m, t, M, est, s); break;
+    case 4: launch_query_d<4>(keys, m, t, M, est, s); break;
+    case 5: launch_query_d<5>(keys, m, t, M, est, s); break;
+    case 6: launch_query_d<6>(keys, m, t, M, est, s); break;
+    case 7: launch_query_d<7>(keys, m, t, M, est, s); break;
+    case 8: launch_query_d<8>(keys, m, t, M, est, s); break;
+    default:
+      hipLaunchKernelGGL(query_kernel, dim3(grid_for(m, 256, 8192)), dim3(256), 0, s, keys, m, t, M, est);
+  }
   return hipGetLastError();
 }
+
+// ------------------------------------------------------------------ exact table
 
 // Every key of the router's exact table joins a candidate set.
 __global__ __launch_bounds__(256) void table_to_set_kernel(const uint64_t* __restrict__ tk, uint32_t tslots, CandSet cand,
