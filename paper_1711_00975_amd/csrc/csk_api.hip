@@ -1333,39 +1333,30 @@ struct csk_mlp {
   float* m2 = nullptr;
   float* H1 = nullptr;    // [max_batch][64]
   float* H2 = nullptr;
-  float* dA2 = nullptr;
-  float* dA1 = nullptr;
-  float* z = nullptr;     // [max_batch]
-  float* dz = nullptr;
-  float* loss = nullptr;  // [1]
-  float* part = nullptr;  // split-k partial products of the weight gradients
-  uint64_t part_floats = 0;
+  float* part = nullptr;  // the workgroups' gradients of a training step
 };
 
 namespace {
 
 void mlp_free(csk_mlp* m) {
-  void* ptrs[] = {m->p, m->g, m->m1, m->m2, m->H1, m->H2, m->dA2, m->dA1, m->z, m->dz, m->loss, m->part};
+  void* ptrs[] = {m->p, m->g, m->m1, m->m2, m->H1, m->H2, m->part};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
 }
 
-// forward of rows [0, b) of x into H1, H2 and z (logits)
-// The forward pass over b rows.  The training pass (y != NULL) rounds every matrix operand to
-// bf16; the scoring pass carries each as a hi + lo bf16 pair (three products per MFMA tile)
-// and does not round the output layer, so its logits stay within fp32 roundings of the fp32
-// forward pass of the same weights.
-hipError_t mlp_forward_rows(csk_mlp* m, const float* x, uint32_t b, float* z, const float* y, hipStream_t st) {
+// The scoring pass over b rows of x: H1, H2 and z (logits).  Each matrix operand is carried as a hi + lo
+// bf16 pair (three products per MFMA tile) and the output layer is not rounded, so the logits stay
+// within fp32 roundings of the fp32 forward pass of the same weights.
+hipError_t mlp_forward_rows(csk_mlp* m, const float* x, uint32_t b, float* z, hipStream_t st) {
   const float* P = m->p;
-  const bool split = (y == nullptr);
   hipError_t e = launch_gemm_bf16(b, kHidden, kFeatPad, x, kFeatPad, 1, P + kOffW1, 1, kFeatPad, m->H1, kHidden, 1,
-                                  0.0f, st, nullptr, 0, split);
+                                  0.0f, st, true);
   if (e == hipSuccess) e = launch_bias_act(m->H1, b, kHidden, P + kOffB1, true, st);
   if (e == hipSuccess)
     e = launch_gemm_bf16(b, kHidden, kHidden, m->H1, kHidden, 1, P + kOffW2, 1, kHidden, m->H2, kHidden, 1, 0.0f, st,
-                         nullptr, 0, split);
+                         true);
   if (e == hipSuccess) e = launch_bias_act(m->H2, b, kHidden, P + kOffB2, true, st);
-  if (e == hipSuccess) e = launch_head(m->H2, b, P + kOffW3, P + kOffB3, z, y, m->dz, m->loss, !split, st);
+  if (e == hipSuccess) e = launch_head(m->H2, b, P + kOffW3, P + kOffB3, z, st);
   return e;
 }
 
@@ -1395,13 +1386,7 @@ csk_status csk_mlp_create(csk_mlp** out, uint64_t seed, uint32_t max_batch) {
   if (e == hipSuccess) e = bmalloc(&m->m2, kParams);
   if (e == hipSuccess) e = bmalloc(&m->H1, hb);
   if (e == hipSuccess) e = bmalloc(&m->H2, hb);
-  if (e == hipSuccess) e = bmalloc(&m->dA2, hb);
-  if (e == hipSuccess) e = bmalloc(&m->dA1, hb);
-  if (e == hipSuccess) e = bmalloc(&m->z, max_batch);
-  if (e == hipSuccess) e = bmalloc(&m->dz, max_batch);
-  if (e == hipSuccess) e = bmalloc(&m->loss, 1);
-  m->part_floats = ((uint64_t)max_batch + kSplitK - 1) / kSplitK * kHidden * kHidden;
-  if (e == hipSuccess) e = bmalloc(&m->part, m->part_floats);
+  if (e == hipSuccess) e = bmalloc(&m->part, (uint64_t)train_workgroups(max_batch) * kTrainPart);
   if (e == hipSuccess) e = hipMemcpy(m->p, P.data(), kParams * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = launch_fill_u32((uint32_t*)m->m1, kParams, 0u, nullptr);
   if (e == hipSuccess) e = launch_fill_u32((uint32_t*)m->m2, kParams, 0u, nullptr);
@@ -1448,7 +1433,7 @@ csk_status csk_mlp_forward(csk_mlp* m, const float* x, uint64_t n, float* logits
   hipStream_t st = (hipStream_t)stream;
   for (uint64_t off = 0; off < n; off += m->max_batch) {
     const uint32_t b = (uint32_t)((n - off < m->max_batch) ? n - off : m->max_batch);
-    CSK_HIP(mlp_forward_rows(m, x + off * kFeatPad, b, logits + off, nullptr, st), "mlp_forward");
+    CSK_HIP(mlp_forward_rows(m, x + off * kFeatPad, b, logits + off, st), "mlp_forward");
   }
   return CSK_OK;
 }
@@ -1458,35 +1443,12 @@ csk_status csk_mlp_train_step(csk_mlp* m, const float* x, const float* y, uint32
   if (m == nullptr || x == nullptr || y == nullptr) return fail(CSK_E_INVALID, "mlp_train_step: NULL argument");
   if (n < 1 || n > m->max_batch) return fail(CSK_E_INVALID, "mlp_train_step: n=%u outside [1, %u]", n, m->max_batch);
   hipStream_t st = (hipStream_t)stream;
-  float* P = m->p;
-  float* G = m->g;
-  CSK_HIP(launch_fill_u32((uint32_t*)m->loss, 1, 0u, st), "mlp_train_step");
-  CSK_HIP(mlp_forward_rows(m, x, n, m->z, y, st), "mlp_train_step (forward)");
-  // output layer: dw3 = H2^T dz, db3 = sum dz
-  CSK_HIP(launch_colsum(m->H2, n, kHidden, kHidden, m->dz, G + kOffW3, st), "mlp_train_step");
-  CSK_HIP(launch_colsum(m->dz, n, 1, 1, nullptr, G + kOffB3, st), "mlp_train_step");
-  // second layer: dA2 = (dz w3^T) masked by ReLU; dW2 = dA2^T H1; db2 = colsum dA2
-  CSK_HIP(launch_head_back(m->dz, m->H2, P + kOffW3, n, m->dA2, st), "mlp_train_step");
-  CSK_HIP(launch_gemm_bf16(kHidden, kHidden, n, m->dA2, 1, kHidden, m->H1, kHidden, 1, G + kOffW2, kHidden, 1, 0.0f,
-                           st, m->part, m->part_floats),
-          "mlp_train_step");
-  CSK_HIP(launch_colsum(m->dA2, n, kHidden, kHidden, nullptr, G + kOffB2, st), "mlp_train_step");
-  // first layer: dA1 = (dA2 W2) masked by ReLU; dW1 = dA1^T X; db1 = colsum dA1
-  CSK_HIP(launch_gemm_bf16(n, kHidden, kHidden, m->dA2, kHidden, 1, P + kOffW2, kHidden, 1, m->dA1, kHidden, 1, 0.0f,
-                           st),
-          "mlp_train_step");
-  CSK_HIP(launch_relu_back(m->dA1, m->H1, (uint64_t)n * kHidden, st), "mlp_train_step");
-  CSK_HIP(launch_gemm_bf16(kHidden, kFeatPad, n, m->dA1, 1, kHidden, x, kFeatPad, 1, G + kOffW1, kFeatPad, 1, 0.0f,
-                           st, m->part, m->part_floats),
-          "mlp_train_step");
-  CSK_HIP(launch_colsum(m->dA1, n, kHidden, kHidden, nullptr, G + kOffB1, st), "mlp_train_step");
-  // Adam
   m->step += 1;
   const double b1 = 0.9, b2 = 0.999;
   const double lr_t = lr * std::sqrt(1.0 - std::pow(b2, (double)m->step)) / (1.0 - std::pow(b1, (double)m->step));
-  CSK_HIP(launch_adam(P, G, m->m1, m->m2, kParams, (float)lr_t, (float)b1, (float)b2, 1e-8f, st), "mlp_train_step");
-  if (loss != nullptr)
-    CSK_HIP(hipMemcpyAsync(loss, m->loss, sizeof(float), hipMemcpyDeviceToDevice, st), "mlp_train_step");
+  CSK_HIP(launch_train_step(x, y, n, m->p, m->g, m->m1, m->m2, m->part, (float)lr_t, (float)b1, (float)b2, 1e-8f, loss,
+                            st),
+          "mlp_train_step");
   return CSK_OK;
 }
 

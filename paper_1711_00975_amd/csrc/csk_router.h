@@ -23,22 +23,20 @@ hipError_t launch_sample_counts(const float* pos, uint64_t n, uint64_t index0, u
                                 const Mesh& coarse, uint32_t* counts, uint32_t* bitmap, hipStream_t s);
 hipError_t launch_features(const uint32_t* counts, uint32_t Gc, const uint64_t* cells, uint64_t m, float* feat,
                            hipStream_t s);
-// C = beta C + A B with bf16 operands and fp32 sums.  With `partial` (device scratch of
-// partial_floats floats), products with k >= 2 kSplitK and fewer than 256 tiles are split
-// over k in chunks of about kSplitK and the chunks summed in a fixed order.
-constexpr uint32_t kSplitK = 256;
+// C = beta C + A B with bf16 operands and fp32 sums (split: each operand a hi + lo pair of them).
 hipError_t launch_gemm_bf16(uint32_t M, uint32_t N, uint32_t K, const float* A, uint64_t sai, uint64_t sak,
                             const float* B, uint64_t sbk, uint64_t sbj, float* C, uint64_t sci, uint64_t scj,
-                            float beta, hipStream_t s, float* partial = nullptr, uint64_t partial_floats = 0,
-                            bool split = false);
+                            float beta, hipStream_t s, bool split = false);
 hipError_t launch_bias_act(float* Y, uint32_t M, uint32_t N, const float* bias, bool relu, hipStream_t s);
-hipError_t launch_head(const float* H2, uint32_t M, const float* w3, const float* b3, float* z, const float* y,
-                       float* dz, float* loss, bool round, hipStream_t s);
-hipError_t launch_head_back(const float* dz, const float* H2, const float* w3, uint32_t M, float* dA, hipStream_t s);
-hipError_t launch_relu_back(float* dA, const float* H, uint64_t total, hipStream_t s);
-hipError_t launch_colsum(const float* X, uint32_t M, uint32_t N, uint32_t ld, const float* w, float* out, hipStream_t s);
-hipError_t launch_adam(float* p, const float* g, float* m1, float* m2, uint32_t n, float lr_t, float b1, float b2,
-                       float eps, hipStream_t s);
+hipError_t launch_head(const float* H2, uint32_t M, const float* w3, const float* b3, float* z, hipStream_t s);
+// A training step over n rows (forward, backward, Adam); part: train_workgroups(n) rows of kTrainPart
+// floats; loss: one float or NULL.
+constexpr uint32_t kTrainPart = 6400;   // floats per workgroup: the gradients and the loss
+static_assert(kTrainPart > kParams, "the loss follows the gradients");
+// One workgroup per 64 rows up to 128 of them: more would only add partial gradients to sum.
+inline uint32_t train_workgroups(uint32_t n) { return n >= 128u * 64u ? 128u : (n + 63u) / 64u; }
+hipError_t launch_train_step(const float* x, const float* y, uint32_t n, float* p, float* g, float* m1, float* m2,
+                             float* part, float lr_t, float b1, float b2, float eps, float* loss, hipStream_t s);
 // The routing split: workgroups of kSplitThreads, kSplitPPT particles per lane per wave
 // tile, at most kSplitMaxWaves waves (each with one contiguous range of the stream), at
 // most kSplitMaxChildren admitted children (the LDS counters of one workgroup).

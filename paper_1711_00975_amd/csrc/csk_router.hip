@@ -277,43 +277,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(uint32_t M, uint32_t N, 
   }
 }
 
-// Split over k for products with a long k and few tiles (the weight gradients, k = batch
-// rows): chunk y = blockIdx.y covers k in [y kc, (y + 1) kc) and writes its partial tile to
-// P[y][i][j] (M x N row-major); splitk_reduce_kernel sums the chunks in order.
-__global__ __launch_bounds__(256) void gemm_bf16_splitk_kernel(uint32_t M, uint32_t N, uint32_t K, uint32_t kc,
-                                                               const float* __restrict__ A, uint64_t sai, uint64_t sak,
-                                                               const float* __restrict__ B, uint64_t sbk, uint64_t sbj,
-                                                               float* __restrict__ P) {
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t tiles_n = (N + 15) / 16;
-  const uint64_t tile = (uint64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  const uint64_t tiles = (uint64_t)((M + 15) / 16) * tiles_n;
-  if (tile >= tiles) return;
-  const uint32_t i0 = (uint32_t)(tile / tiles_n) * 16, j0 = (uint32_t)(tile % tiles_n) * 16;
-  const uint32_t k_lo = blockIdx.y * kc, k_hi = (k_lo + kc < K) ? k_lo + kc : K;
-  const f32x4 acc = gemm_tile<false>(M, N, k_lo, k_hi, A, sai, sak, B, sbk, sbj, i0, j0, lane);
-  float* out = P + (uint64_t)blockIdx.y * M * N;
-  const uint32_t r = lane & 15u, kq = (lane >> 4) * 4;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t i = i0 + kq + (uint32_t)e, j = j0 + r;
-    if (i < M && j < N) out[(uint64_t)i * N + j] = acc[e];
-  }
-}
-
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ P, uint32_t nsplit, uint32_t M,
-                                                            uint32_t N, float* __restrict__ C, uint64_t sci,
-                                                            uint64_t scj, float beta) {
-  const uint64_t total = (uint64_t)M * N;
-  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (uint64_t)gridDim.x * blockDim.x) {
-    float s = 0.0f;
-    for (uint32_t y = 0; y < nsplit; ++y) s += P[(uint64_t)y * total + t];
-    const uint32_t i = (uint32_t)(t / N), j = (uint32_t)(t % N);
-    float* c = C + i * sci + j * scj;
-    *c = (beta != 0.0f ? beta * *c : 0.0f) + s;
-  }
-}
-
 // Y[i][j] = act(Y[i][j] + bias[j]) over an M x N row-major block; act = ReLU if relu.
 __global__ __launch_bounds__(256) void bias_act_kernel(float* __restrict__ Y, uint32_t M, uint32_t N,
                                                        const float* __restrict__ bias, uint32_t relu) {
@@ -325,78 +288,211 @@ __global__ __launch_bounds__(256) void bias_act_kernel(float* __restrict__ Y, ui
   }
 }
 
-// Output layer and loss: z[i] = H2[i] . w3 + b3 in fp32 sums, with H2 and w3 rounded to
-// bf16 (round = 1, the training pass) or not (the scoring pass); with labels y,
-// dz[i] = (sigmoid(z) - y) / M and loss[0] += mean binary cross-entropy.
+// Output layer of the scoring pass: z[i] = H2[i] . w3 + b3 in fp32.
 __global__ __launch_bounds__(256) void head_kernel(const float* __restrict__ H2, uint32_t M, const float* __restrict__ w3,
-                                                   const float* __restrict__ b3, float* __restrict__ z,
-                                                   const float* __restrict__ y, float* __restrict__ dz,
-                                                   float* __restrict__ loss, uint32_t round) {
+                                                   const float* __restrict__ b3, float* __restrict__ z) {
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x) {
     float s = 0.0f;
-    for (int j = 0; j < kHidden; ++j) {
-      float wj = w3[j], hj = H2[(uint64_t)i * kHidden + j];
-      if (round) {
-        wj = bf16_value(to_bf16(wj));
-        hj = bf16_value(to_bf16(hj));
-      }
-      s = fmaf(hj, wj, s);
-    }
-    s += b3[0];
-    z[i] = s;
-    if (y != nullptr) {
-      const float p = 1.0f / (1.0f + expf(-s));
-      dz[i] = (p - y[i]) / (float)M;
-      // BCE with logits, stable form: max(z, 0) - z y + log(1 + exp(-|z|))
-      const float l = fmaxf(s, 0.0f) - s * y[i] + log1pf(expf(-fabsf(s)));
-      atomicAdd(loss, l / (float)M);
-    }
+    for (int j = 0; j < kHidden; ++j) s = fmaf(H2[(uint64_t)i * kHidden + j], w3[j], s);
+    z[i] = s + b3[0];
   }
 }
 
-// dA[i][j] = dz[i] * w3[j] where H2[i][j] > 0 (ReLU), else 0.
-__global__ __launch_bounds__(256) void head_back_kernel(const float* __restrict__ dz, const float* __restrict__ H2,
-                                                        const float* __restrict__ w3, uint32_t M,
-                                                        float* __restrict__ dA) {
-  const uint64_t total = (uint64_t)M * kHidden;
-  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t i = (uint32_t)(t / kHidden), j = (uint32_t)(t % kHidden);
-    dA[t] = H2[t] > 0.0f ? dz[i] * w3[j] : 0.0f;
+// ---- a training step: forward, backward and Adam in two launches.
+//
+// The matrices are small (64 x 64 weights, a minibatch of a few thousand rows), so a step is bound by its
+// launches and by the latencies inside each: layer by layer it was 20 launches of 3 to 21 us.  Here a
+// workgroup takes 64 rows through all layers and back with everything in LDS, in 16 x 16 tiles of
+// v_mfma_f32_16x16x32_bf16, keeps the weight gradients of all its rows in registers and writes them once;
+// a second launch sums the workgroups' gradients in a fixed order and takes the Adam step.  Operands of
+// the matrix products are rounded to bf16, sums and everything else are fp32, as before.  4096 rows: 140 us
+// a step before, 31 us so (18 and 4 us in the kernels).
+constexpr uint32_t kTrainThreads = 256, kTrainRows = 64;
+constexpr uint32_t kTrainS = 68;   // LDS row stride of the 64-wide matrices (16-byte rows, spread over banks)
+constexpr uint32_t kTrainX = 36;   // and of the 32-wide ones
+struct TrainLds {
+  float X[kTrainRows * kTrainX], W1[kHidden * kTrainX], W2[kHidden * kTrainS];
+  float H1[kTrainRows * kTrainS], H2[kTrainRows * kTrainS], dA2[kTrainRows * kTrainS];   // dA1 in H2's place
+  float b1[kHidden], b2[kHidden], w3[kHidden], dz[kTrainRows];
+  float red[5][kTrainThreads];
+};
+
+// One wave: acc += A B over k in [0, K) for a 16 x 16 tile, A(i, k) and B(k, j) with i, j < 16 in fp32.
+template <uint32_t K, class FA, class FB>
+__device__ __forceinline__ f32x4 train_tile(f32x4 acc, FA A, FB B) {
+  const uint32_t r = threadIdx.x & 15u, kq = ((threadIdx.x & 63u) >> 4) * 8;
+#pragma unroll
+  for (uint32_t k0 = 0; k0 < K; k0 += 32) {
+    s16x8 a, b;
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      a[e] = to_bf16(A(r, k0 + kq + e));
+      b[e] = to_bf16(B(k0 + kq + e, r));
+    }
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0,
+                                                  0, 0);
   }
+  return acc;
 }
 
-// dA[t] *= (H[t] > 0)
-__global__ __launch_bounds__(256) void relu_back_kernel(float* __restrict__ dA, const float* __restrict__ H, uint64_t total) {
-  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (uint64_t)gridDim.x * blockDim.x)
-    if (!(H[t] > 0.0f)) dA[t] = 0.0f;
-}
-
-// out[j] = sum_i X[i * ld + j] * (w ? w[i] : 1) for j < N: one block per column, a fixed
-// summation order (deterministic).
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ X, uint32_t M, uint32_t N, uint32_t ld,
-                                                     const float* __restrict__ w, float* __restrict__ out) {
-  __shared__ float part[256];
-  const uint32_t j = blockIdx.x;
-  float s = 0.0f;
-  for (uint32_t i = threadIdx.x; i < M; i += blockDim.x) s += X[(uint64_t)i * ld + j] * (w ? w[i] : 1.0f);
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (uint32_t h = blockDim.x / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) part[threadIdx.x] += part[threadIdx.x + h];
+// part: one row of kTrainPart floats per workgroup: the gradients, then the loss.
+__global__ __launch_bounds__(kTrainThreads) void train_kernel(const float* __restrict__ x, const float* __restrict__ y,
+                                                              uint32_t n, const float* __restrict__ P,
+                                                              float* __restrict__ part) {
+  extern __shared__ __align__(16) char train_lds[];
+  TrainLds& L = *(TrainLds*)train_lds;
+  float* dA1 = L.H2;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, i0 = 16 * wave;
+  const uint32_t r = tid & 15u, q4 = ((tid & 63u) >> 4) * 4;   // result rows q4 .. +3 of column r
+  const uint32_t col = tid & 63u;                              // of the column sums, rows i0 .. +15
+  for (uint32_t i = tid; i < kHidden * kFeatPad; i += kTrainThreads) L.W1[(i / kFeatPad) * kTrainX + i % kFeatPad] = P[kOffW1 + i];
+  for (uint32_t i = tid; i < kHidden * kHidden; i += kTrainThreads) L.W2[(i / kHidden) * kTrainS + i % kHidden] = P[kOffW2 + i];
+  if (tid < kHidden) {
+    L.b1[tid] = P[kOffB1 + tid];
+    L.b2[tid] = P[kOffB2 + tid];
+    L.w3[tid] = P[kOffW3 + tid];
+  }
+  const float b3 = P[kOffB3];
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 g1[2] = {zero, zero}, g2[4] = {zero, zero, zero, zero};   // dW1, dW2: rows i0 .. +15
+  float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
+  for (uint32_t row0 = blockIdx.x * kTrainRows; row0 < n; row0 += gridDim.x * kTrainRows) {
+    __syncthreads();   // the last rows' matrices are done with
+    for (uint32_t i = tid; i < kTrainRows * kFeatPad; i += kTrainThreads) {
+      const uint32_t row = row0 + i / kFeatPad;
+      L.X[(i / kFeatPad) * kTrainX + i % kFeatPad] = row < n ? x[(uint64_t)row * kFeatPad + i % kFeatPad] : 0.0f;
+    }
     __syncthreads();
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {   // H1 = relu(X W1^T + b1), this wave's rows
+      const f32x4 c = train_tile<kFeatPad>(zero, [&](uint32_t i, uint32_t k) { return L.X[(i0 + i) * kTrainX + k]; },
+                                           [&](uint32_t k, uint32_t j) { return L.W1[(16 * t + j) * kTrainX + k]; });
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        const float v = c[e] + L.b1[16 * t + r];
+        L.H1[(i0 + q4 + e) * kTrainS + 16 * t + r] = v > 0.0f ? v : 0.0f;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {   // H2 = relu(H1 W2^T + b2)
+      const f32x4 c = train_tile<kHidden>(zero, [&](uint32_t i, uint32_t k) { return L.H1[(i0 + i) * kTrainS + k]; },
+                                          [&](uint32_t k, uint32_t j) { return L.W2[(16 * t + j) * kTrainS + k]; });
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        const float v = c[e] + L.b2[16 * t + r];
+        L.H2[(i0 + q4 + e) * kTrainS + 16 * t + r] = v > 0.0f ? v : 0.0f;
+      }
+    }
+    __syncthreads();
+    {   // z = H2 . w3 + b3 (operands rounded to bf16), dz = (sigmoid(z) - y) / n and the loss: four lanes a row
+      const uint32_t row = tid >> 2, c0 = (tid & 3u) * 16;
+      float s = 0.0f;
+#pragma unroll
+      for (uint32_t j = 0; j < 16; ++j)
+        s = fmaf(bf16_value(to_bf16(L.H2[row * kTrainS + c0 + j])), bf16_value(to_bf16(L.w3[c0 + j])), s);
+      s += __shfl_xor(s, 1, 64);
+      s += __shfl_xor(s, 2, 64);
+      s += b3;
+      if ((tid & 3u) == 0) {
+        float d = 0.0f;
+        if (row0 + row < n) {
+          const float yr = y[row0 + row], p = 1.0f / (1.0f + expf(-s));
+          d = (p - yr) / (float)n;
+          // binary cross-entropy with logits, stable form: max(z, 0) - z y + log(1 + exp(-|z|))
+          loss += (fmaxf(s, 0.0f) - s * yr + log1pf(expf(-fabsf(s)))) / (float)n;
+        }
+        L.dz[row] = d;
+        gb3 += d;
+      }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (uint32_t i = i0; i < i0 + 16; ++i) {   // dA2 = (dz w3^T) where H2 > 0; dw3, db2
+      const float h = L.H2[i * kTrainS + col], d = L.dz[i];
+      const float v = h > 0.0f ? d * L.w3[col] : 0.0f;
+      L.dA2[i * kTrainS + col] = v;
+      gb2 += v;
+      gw3 += h * d;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {   // dA1 = (dA2 W2) where H1 > 0; dW2 += dA2^T H1
+      const f32x4 c = train_tile<kHidden>(zero, [&](uint32_t i, uint32_t k) { return L.dA2[(i0 + i) * kTrainS + k]; },
+                                          [&](uint32_t k, uint32_t j) { return L.W2[k * kTrainS + 16 * t + j]; });
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        const uint32_t at = (i0 + q4 + e) * kTrainS + 16 * t + r;
+        dA1[at] = L.H1[at] > 0.0f ? c[e] : 0.0f;
+      }
+      g2[t] = train_tile<kTrainRows>(g2[t], [&](uint32_t i, uint32_t k) { return L.dA2[k * kTrainS + i0 + i]; },
+                                     [&](uint32_t k, uint32_t j) { return L.H1[k * kTrainS + 16 * t + j]; });
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t)   // dW1 += dA1^T X
+      g1[t] = train_tile<kTrainRows>(g1[t], [&](uint32_t i, uint32_t k) { return dA1[k * kTrainS + i0 + i]; },
+                                     [&](uint32_t k, uint32_t j) { return L.X[k * kTrainX + 16 * t + j]; });
+#pragma unroll 4
+    for (uint32_t i = i0; i < i0 + 16; ++i) gb1 += dA1[i * kTrainS + col];
   }
-  if (threadIdx.x == 0 && j < N) out[j] = part[0];
+  float* out = part + (uint64_t)blockIdx.x * kTrainPart;
+#pragma unroll
+  for (uint32_t e = 0; e < 4; ++e) {
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) out[kOffW1 + (i0 + q4 + e) * kFeatPad + 16 * t + r] = g1[t][e];
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) out[kOffW2 + (i0 + q4 + e) * kHidden + 16 * t + r] = g2[t][e];
+  }
+  L.red[0][tid] = gb1;
+  L.red[1][tid] = gb2;
+  L.red[2][tid] = gw3;
+  L.red[3][tid] = gb3;
+  L.red[4][tid] = loss;
+  __syncthreads();
+  if (tid < kHidden) {
+    auto four = [&](uint32_t a) { return (L.red[a][tid] + L.red[a][tid + 64]) + (L.red[a][tid + 128] + L.red[a][tid + 192]); };
+    out[kOffB1 + tid] = four(0);
+    out[kOffB2 + tid] = four(1);
+    out[kOffW3 + tid] = four(2);
+    float b = four(3), l = four(4);
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) {
+      b += __shfl_xor(b, h, 64);
+      l += __shfl_xor(l, h, 64);
+    }
+    if (tid == 0) {
+      out[kOffB3] = b;
+      out[kParams] = l;
+    }
+  }
 }
 
-// Adam on the fp32 master weights (bias-corrected step sizes from the host).
-__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ p, const float* __restrict__ g,
-                                                   float* __restrict__ m1, float* __restrict__ m2, uint32_t n, float lr_t,
-                                                   float b1, float b2, float eps) {
-  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
-    m1[t] = b1 * m1[t] + (1.0f - b1) * g[t];
-    m2[t] = b2 * m2[t] + (1.0f - b2) * g[t] * g[t];
-    p[t] -= lr_t * m1[t] / (sqrtf(m2[t]) + eps);
+// The gradients (and the loss) summed over the workgroups' rows of part, in order within four quarters,
+// and Adam on the fp32 master weights (bias-corrected step size from the host).
+__global__ __launch_bounds__(256) void train_adam_kernel(const float* __restrict__ part, uint32_t rows,
+                                                         float* __restrict__ p, float* __restrict__ g,
+                                                         float* __restrict__ m1, float* __restrict__ m2, float lr_t,
+                                                         float b1, float b2, float eps, float* __restrict__ loss) {
+  __shared__ float sum[4][64];
+  const uint32_t t = blockIdx.x * 64 + (threadIdx.x & 63u), quarter = threadIdx.x >> 6;
+  float s = 0.0f;
+  if (t <= kParams) {
+#pragma unroll 8
+    for (uint32_t i = quarter; i < rows; i += 4) s += part[(uint64_t)i * kTrainPart + t];
   }
+  sum[quarter][threadIdx.x & 63u] = s;
+  __syncthreads();
+  if (quarter != 0 || t > kParams) return;
+  s = (sum[0][threadIdx.x] + sum[1][threadIdx.x]) + (sum[2][threadIdx.x] + sum[3][threadIdx.x]);
+  if (t == kParams) {
+    if (loss != nullptr) *loss = s;
+    return;
+  }
+  g[t] = s;
+  m1[t] = b1 * m1[t] + (1.0f - b1) * s;
+  m2[t] = b2 * m2[t] + (1.0f - b2) * s * s;
+  p[t] -= lr_t * m1[t] / (sqrtf(m2[t]) + eps);
 }
 
 // ------------------------------------------------------------------ routing
@@ -1067,27 +1163,13 @@ hipError_t launch_features(const uint32_t* counts, uint32_t Gc, const uint64_t* 
 
 hipError_t launch_gemm_bf16(uint32_t M, uint32_t N, uint32_t K, const float* A, uint64_t sai, uint64_t sak,
                             const float* B, uint64_t sbk, uint64_t sbj, float* C, uint64_t sci, uint64_t scj,
-                            float beta, hipStream_t s, float* partial, uint64_t partial_floats, bool split) {
+                            float beta, hipStream_t s, bool split) {
   const uint64_t tiles = (uint64_t)((M + 15) / 16) * ((N + 15) / 16);
-  uint64_t nsplit = (K + kSplitK - 1) / kSplitK;
-  if (partial != nullptr && (uint64_t)M * N > 0 && nsplit * (uint64_t)M * N > partial_floats)
-    nsplit = partial_floats / ((uint64_t)M * N);
-  if (split) {   // the scoring pass: no split over k
-    hipLaunchKernelGGL(gemm_bf16_kernel<true>, dim3((uint32_t)((tiles + 3) / 4)), dim3(256), 0, s, M, N, K, A, sai,
-                       sak, B, sbk, sbj, C, sci, scj, beta);
-    return hipGetLastError();
-  }
-  if (partial == nullptr || K < 2 * kSplitK || tiles >= 256 || nsplit < 2) {
-    hipLaunchKernelGGL(gemm_bf16_kernel<false>, dim3((uint32_t)((tiles + 3) / 4)), dim3(256), 0, s, M, N, K, A, sai,
-                       sak, B, sbk, sbj, C, sci, scj, beta);
-    return hipGetLastError();
-  }
-  const uint32_t kc = (uint32_t)(((K + nsplit - 1) / nsplit + 31) / 32 * 32);
-  nsplit = (K + kc - 1) / kc;
-  hipLaunchKernelGGL(gemm_bf16_splitk_kernel, dim3((uint32_t)((tiles + 3) / 4), (uint32_t)nsplit), dim3(256), 0, s, M,
-                     N, K, kc, A, sai, sak, B, sbk, sbj, partial);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid_of((uint64_t)M * N, 256, 1024)), dim3(256), 0, s, partial,
-                     (uint32_t)nsplit, M, N, C, sci, scj, beta);
+  const dim3 grid((uint32_t)((tiles + 3) / 4)), block(256);
+  if (split)   // the scoring pass
+    hipLaunchKernelGGL(gemm_bf16_kernel<true>, grid, block, 0, s, M, N, K, A, sai, sak, B, sbk, sbj, C, sci, scj, beta);
+  else
+    hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid, block, 0, s, M, N, K, A, sai, sak, B, sbk, sbj, C, sci, scj, beta);
   return hipGetLastError();
 }
 
@@ -1097,32 +1179,17 @@ hipError_t launch_bias_act(float* Y, uint32_t M, uint32_t N, const float* bias, 
   return hipGetLastError();
 }
 
-hipError_t launch_head(const float* H2, uint32_t M, const float* w3, const float* b3, float* z, const float* y,
-                       float* dz, float* loss, bool round, hipStream_t s) {
-  hipLaunchKernelGGL(head_kernel, dim3(grid_of(M, 256, 4096)), dim3(256), 0, s, H2, M, w3, b3, z, y, dz, loss,
-                     round ? 1u : 0u);
+hipError_t launch_head(const float* H2, uint32_t M, const float* w3, const float* b3, float* z, hipStream_t s) {
+  hipLaunchKernelGGL(head_kernel, dim3(grid_of(M, 256, 4096)), dim3(256), 0, s, H2, M, w3, b3, z);
   return hipGetLastError();
 }
 
-hipError_t launch_head_back(const float* dz, const float* H2, const float* w3, uint32_t M, float* dA, hipStream_t s) {
-  hipLaunchKernelGGL(head_back_kernel, dim3(grid_of((uint64_t)M * kHidden, 256, 4096)), dim3(256), 0, s, dz, H2, w3, M,
-                     dA);
-  return hipGetLastError();
-}
-
-hipError_t launch_relu_back(float* dA, const float* H, uint64_t total, hipStream_t s) {
-  hipLaunchKernelGGL(relu_back_kernel, dim3(grid_of(total, 256, 4096)), dim3(256), 0, s, dA, H, total);
-  return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float* X, uint32_t M, uint32_t N, uint32_t ld, const float* w, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(colsum_kernel, dim3(N), dim3(256), 0, s, X, M, N, ld, w, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(float* p, const float* g, float* m1, float* m2, uint32_t n, float lr_t, float b1, float b2,
-                       float eps, hipStream_t s) {
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_of(n, 256, 1024)), dim3(256), 0, s, p, g, m1, m2, n, lr_t, b1, b2, eps);
+hipError_t launch_train_step(const float* x, const float* y, uint32_t n, float* p, float* g, float* m1, float* m2,
+                             float* part, float lr_t, float b1, float b2, float eps, float* loss, hipStream_t s) {
+  const uint32_t wgs = train_workgroups(n);
+  hipLaunchKernelGGL(train_kernel, dim3(wgs), dim3(kTrainThreads), sizeof(TrainLds), s, x, y, n, p, part);
+  hipLaunchKernelGGL(train_adam_kernel, dim3(kParams / 64 + 1), dim3(256), 0, s, part, wgs, p, g, m1, m2, lr_t, b1, b2,
+                     eps, loss);
   return hipGetLastError();
 }
 
