@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -769,6 +770,15 @@ csk_status ensure_select_scratch(csk_sketch* s, uint32_t k, hipStream_t st, cons
   return CSK_OK;
 }
 
+// No item of the handle's mesh has a bit from here up.
+uint32_t key_bits(const csk_sketch* s) {
+  if (!s->mesh_set) return 8u * kChars;
+  const uint64_t n = ((uint64_t)s->mesh.G * s->mesh.G * s->mesh.G + s->group - 1) / s->group;
+  uint32_t b = 1;
+  while (b < 8u * kChars && ((n - 1) >> b) != 0) ++b;
+  return b;
+}
+
 struct ExactTable {   // the router's exact table, or none
   const uint64_t* keys;
   const uint32_t* counts;
@@ -785,8 +795,8 @@ csk_status topk_impl(csk_sketch* s, uint32_t k, uint64_t* keys, int32_t* est, ui
   if (k > 0)
     CSK_HIP(launch_topk(s->cand_key, s->set_count(), s->tables(), s->M, s->max_cand, s->cand_likely, k, s->sel,
                         s->cand_est, s->sel_key,
-                        s->sel_est, keys, est, s->err(), partial, out, out ? nullptr : s->host_sel, st, x.keys,
-                        x.counts, x.mask),
+                        s->sel_est, keys, est, s->err(), partial, out, out ? nullptr : s->host_sel,
+                        x.keys ? 8u * kChars : key_bits(s), st, x.keys, x.counts, x.mask),
             who);
   else if (out)
     CSK_HIP(launch_fill_u32(out, 2, 0u, st), who);
@@ -1260,7 +1270,9 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
     call.k[i] = k[i];
     call.partial[i] = b->sk[i]->partial_set ? 1u : 0u;
   }
-  CSK_HIP(launch_topk_batch(b->topk, b->count, b->d, mc_max, k_max, call, st), "batch_topk");
+  uint32_t bits = 0;
+  for (uint32_t i = 0; i < b->count; ++i) bits = std::max(bits, key_bits(b->sk[i]));
+  CSK_HIP(launch_topk_batch(b->topk, b->count, b->d, mc_max, k_max, call, bits, st), "batch_topk");
   return CSK_OK;
 }
 

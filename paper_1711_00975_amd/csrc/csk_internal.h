@@ -354,7 +354,7 @@ hipError_t launch_fill_spans_batch(const ResetSpans* spans, uint32_t count, uint
 hipError_t launch_topk(const uint64_t* list, const uint32_t* count, const Tables& t, const int32_t* M,
                        uint32_t max_cand, uint64_t likely, uint32_t k, SelState* st, int32_t* ce, uint64_t* sk,
                        int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err, uint32_t partial, uint32_t* out,
-                       SelHost* host, hipStream_t s, const uint64_t* ov_keys = nullptr, const uint32_t* ov_counts = nullptr,
+                       SelHost* host, uint32_t key_bits, hipStream_t s, const uint64_t* ov_keys = nullptr, const uint32_t* ov_counts = nullptr,
                        uint32_t ov_mask = 0);
 // One sketch of a batched top-k (device array, built once per batch).
 struct TopkDesc {
@@ -379,7 +379,7 @@ struct TopkCall {
   uint32_t partial[kMaxBatch];
 };
 hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint32_t max_cand_max, uint32_t k_max,
-                             const TopkCall& call, hipStream_t s);
+                             const TopkCall& call, uint32_t key_bits, hipStream_t s);
 
 // Top k of the m pairs (ck[i], ce[i]) in (ce desc, ck asc) order, keys distinct and below
 // 2^48 (equal keys only where they cannot reach the top k): winners in ok / oe, their number in

@@ -688,14 +688,15 @@ __global__ __launch_bounds__(kSelThreads) void sel_start_kernel(SelState* st, ui
   if (threadIdx.x == 0) st->m = m_dev ? (uint32_t)(*m_dev < m ? *m_dev : m) : m;
 }
 
-// The passes after the first, the gather and the rank placement.
+// The passes after the first, the gather and the rank placement.  key_bits: no key has a bit from there up
+// (the digits of the tie's key start at 0, so a pass over zero bits can be left out).
 static hipError_t select_rest(const uint64_t* ck, const int32_t* ce, uint32_t m_max, uint32_t k, SelState* st,
                               uint64_t* sk, int32_t* se, uint64_t* ok, int32_t* oe, const uint32_t* err,
-                              uint32_t partial, uint32_t* out, SelHost* host, hipStream_t s) {
+                              uint32_t partial, uint32_t* out, SelHost* host, uint32_t key_bits, hipStream_t s) {
   const dim3 g(grid_for(m_max, kSelItems, kSelGrid)), b(kSelThreads);
   hipLaunchKernelGGL((sel_pass_kernel<10, 11, false, false>), g, b, 0, s, ck, ce, st, k);
   hipLaunchKernelGGL((sel_pass_kernel<0, 10, false, false>), g, b, 0, s, ck, ce, st, k);
-  hipLaunchKernelGGL((sel_pass_kernel<36, 12, true, false>), g, b, 0, s, ck, ce, st, k);
+  if (key_bits > 36) hipLaunchKernelGGL((sel_pass_kernel<36, 12, true, false>), g, b, 0, s, ck, ce, st, k);
   hipLaunchKernelGGL((sel_pass_kernel<24, 12, true, false>), g, b, 0, s, ck, ce, st, k);
   hipLaunchKernelGGL((sel_pass_kernel<12, 12, true, false>), g, b, 0, s, ck, ce, st, k);
   hipLaunchKernelGGL((sel_pass_kernel<0, 12, true, false>), g, b, 0, s, ck, ce, st, k);
@@ -707,7 +708,7 @@ static hipError_t select_rest(const uint64_t* ck, const int32_t* ce, uint32_t m_
 hipError_t launch_topk(const uint64_t* list, const uint32_t* count, const Tables& t, const int32_t* M,
                        uint32_t max_cand, uint64_t likely, uint32_t k, SelState* st, int32_t* ce, uint64_t* sk, int32_t* se,
                        uint64_t* ok, int32_t* oe, const uint32_t* err, uint32_t partial, uint32_t* out, SelHost* host,
-                       hipStream_t s, const uint64_t* ov_keys, const uint32_t* ov_counts, uint32_t ov_mask) {
+                       uint32_t key_bits, hipStream_t s, const uint64_t* ov_keys, const uint32_t* ov_counts, uint32_t ov_mask) {
   const dim3 g(grid_for(max_cand, kSelItems, kSelGrid)), b(kSelThreads);
   if (likely <= kOneBlock) {
     if (t.d <= (uint32_t)kTabLdsRows)
@@ -725,7 +726,7 @@ hipError_t launch_topk(const uint64_t* list, const uint32_t* count, const Tables
   else
     hipLaunchKernelGGL((sel_estimate_kernel<32>), g, b, 0, s, list, count, max_cand, t, M, k, st, ce, ov_keys,
                        ov_counts, ov_mask);
-  return select_rest(list, ce, max_cand, k, st, sk, se, ok, oe, err, partial, out, host, s);
+  return select_rest(list, ce, max_cand, k, st, sk, se, ok, oe, err, partial, out, host, key_bits, s);
 }
 
 static hipError_t select_pairs(const uint64_t* ck, const int32_t* ce, uint32_t m, const uint64_t* m_dev, uint32_t k,
@@ -734,7 +735,7 @@ static hipError_t select_pairs(const uint64_t* ck, const int32_t* ce, uint32_t m
   hipLaunchKernelGGL(sel_start_kernel, dim3(1), dim3(kSelThreads), 0, s, st, m, m_dev);
   hipLaunchKernelGGL((sel_pass_kernel<21, 11, false, true>), dim3(grid_for(m, kSelItems, kSelGrid)), dim3(kSelThreads),
                      0, s, ck, ce, st, k);
-  return select_rest(ck, ce, m, k, st, sk, se, ok, oe, err, 0u, nullptr, nullptr, s);
+  return select_rest(ck, ce, m, k, st, sk, se, ok, oe, err, 0u, nullptr, nullptr, 8 * kChars, s);
 }
 
 hipError_t launch_select_pairs_dev(const uint64_t* ck, const int32_t* ce, const uint64_t* m_dev, uint32_t cap,
@@ -773,7 +774,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_rank_batch_kernel(const TopkD
 }
 
 hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint32_t max_cand_max, uint32_t k_max,
-                             const TopkCall& call, hipStream_t s) {
+                             const TopkCall& call, uint32_t key_bits, hipStream_t s) {
   if (count == 0) return hipSuccess;
   const dim3 g(grid_for(max_cand_max, kSelItems, kSelGrid), count), b(kSelThreads);
   if (d <= (uint32_t)kTabLdsRows)
@@ -782,7 +783,7 @@ hipError_t launch_topk_batch(const TopkDesc* D, uint32_t count, uint32_t d, uint
     hipLaunchKernelGGL((sel_estimate_batch_kernel<32>), g, b, 0, s, D, call);
   hipLaunchKernelGGL((sel_pass_batch_kernel<10, 11, false>), g, b, 0, s, D, call);
   hipLaunchKernelGGL((sel_pass_batch_kernel<0, 10, false>), g, b, 0, s, D, call);
-  hipLaunchKernelGGL((sel_pass_batch_kernel<36, 12, true>), g, b, 0, s, D, call);
+  if (key_bits > 36) hipLaunchKernelGGL((sel_pass_batch_kernel<36, 12, true>), g, b, 0, s, D, call);
   hipLaunchKernelGGL((sel_pass_batch_kernel<24, 12, true>), g, b, 0, s, D, call);
   hipLaunchKernelGGL((sel_pass_batch_kernel<12, 12, true>), g, b, 0, s, D, call);
   hipLaunchKernelGGL((sel_pass_batch_kernel<0, 12, true>), g, b, 0, s, D, call);

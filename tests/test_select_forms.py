@@ -83,6 +83,28 @@ def test_select_against_the_oracle(n, kind, variant):
         s.close()
 
 
+@pytest.mark.parametrize("G", [4096, 4097, 9000])
+def test_ties_up_to_the_highest_key_bits(G):
+    # 2^36 cells, the most whose keys' top digit pass is left out, and more
+    d, w, seed, n = 5, 1 << 14, 3, 20_000
+    rng = np.random.default_rng(G)
+    c = rng.integers(0, G, (n, 3))
+    c[: n // 2] = G - 1 - rng.integers(0, 3, (n // 2, 3)) * rng.integers(0, G // 3, (n // 2, 3))   # up to the last cell
+    pos = (c + 0.5).astype(np.float32)
+    M, T = _counters("ties", d, w, G), oracle.hash_tables(seed, d)
+    s = csk.Sketch(d, w, seed)
+    try:
+        s.set_counters(_dev(M))
+        s.collect(_dev(pos), 1.0, float(G))
+        ko, eo = oracle.topk_keys(M, T, oracle.keys(pos, 1.0, float(G)), csk.INT32_MIN, n)
+        for k in (1, 700, 5000, len(ko) - 1, len(ko)):
+            kg, eg, _ = s.topk(k)
+            assert np.array_equal(kg.cpu().numpy().view(np.uint64), ko[:k]), k
+            assert np.array_equal(eg.cpu().numpy(), eo[:k]), k
+    finally:
+        s.close()
+
+
 def test_few_candidates_after_many():
     # one block selects, the rank kernel places (k > 1024): nothing is left of the selection before
     d, w, seed = 5, 1 << 14, 3
