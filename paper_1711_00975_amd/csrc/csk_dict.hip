@@ -53,10 +53,11 @@ __device__ __forceinline__ uint32_t shift_by(uint32_t x, uint32_t b) {
 // per word and LDS is read for the filter alone.  FP: the field-probe filter, whose probe fields are
 // tabulated themselves (word address and bit positions kept apart in registers, XORed separately).
 // The few keys that pass are gathered in an LDS queue per wave and take the exact test 64 at a time.
-// Bound by the LDS reads, one of 4 bytes per row and key: 64 random words take 6.9 cycles (bank
-// conflicts), and the VALU (4.5 instructions per row) is idle a quarter of the time.  2000^3 keys, d = 5,
-// w = 2^22, 88655 hot counters: 34.8 ms with a hash of four LDS reads and a computed probe per key and
-// row, 7.95 ms so (1.0e12 keys/s); 34329 super-items of 1000 keys: 3.04 ms with every row's counter read,
+// The conflicts of the filter reads are those of the byte-0 entries (the rest of the address is the same
+// for all lanes), so their order over the lanes is chosen against them when the sketch is made.  Bound by
+// the VALU (4.5 instructions per row and key) and the LDS reads alike.  2000^3 keys, d = 5, w = 2^22, 88655
+// hot counters: 34.8 ms with a hash of four LDS reads and a computed probe per key and row, 7.95 ms so
+// with the values in their order (64 random words take 6.9 cycles), 7.03 ms in the chosen one (4.5 cycles); 34329 super-items of 1000 keys: 3.04 ms with every row's counter read,
 // 0.18 ms so.
 template <int D, int HM, bool FP>
 struct KeyWalk {
@@ -70,6 +71,7 @@ struct KeyWalk {
   uint32_t queued = 0;
   uint32_t need;
   bool uh;
+  uint32_t vs = 0;        // the byte-0 values of this lane's four keys
   uint32_t e0[4][NR];
 
   // registers of a table entry (linear: the registers of an XOR are the XOR of the registers)
@@ -114,8 +116,10 @@ struct KeyWalk {
     need = a.t.cm ? (uint32_t)D : (uint32_t)(D - ((D - 1) >> 1));
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      uint32_t q[TW];
-      entry(0, 64u * g + lane_id(), q);
+      uint32_t q[TW], v = 64u * g + lane_id();
+      if constexpr (FP) v = ((const uint8_t*)(a.t.tabq + kTableWords * TW))[v];   // see probe_order()
+      vs |= v << (8 * g);
+      entry(0, v, q);
       split(q, e0[g]);
     }
   }
@@ -128,11 +132,12 @@ struct KeyWalk {
     for (int r = 0; r < D; ++r) ng[r] &= a.t.cm ^ 1u;
     if (rows_pass<D>(bk, ng, need, uh ? a.hot_table : nullptr, a.M, a.t.w, a.theta)) set_insert(a.cand, key, a.err);
   }
-  // The lanes of who hold keys base + lane that pass the filter (who: the same in every lane).
-  __device__ __forceinline__ void offer(uint64_t who, uint64_t base) {
+  __device__ __forceinline__ uint32_t value(uint32_t g) const { return (vs >> (8 * g)) & 255u; }
+  // The lanes of who hold keys base + value(g) that pass the filter (who: the same in every lane).
+  __device__ __forceinline__ void offer(uint64_t who, uint64_t base, uint32_t g) {
     const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
-    if ((who >> lane_id()) & 1u) queue[at] = base + lane_id();
+    if ((who >> lane_id()) & 1u) queue[at] = base + value(g);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     queued = __builtin_amdgcn_readfirstlane(queued + (uint32_t)__popcll(who));
     if (queued >= 64u) {
@@ -193,13 +198,13 @@ struct KeyWalk {
     }
     if (end - first < 256u) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) who[g] &= __ballot(64u * g + lane_id() >= first && 64u * g + lane_id() < end);
+      for (int g = 0; g < 4; ++g) who[g] &= __ballot(value(g) >= first && value(g) < end);
     }
     if ((who[0] | who[1] | who[2] | who[3]) == 0) return;
 #pragma unroll 1
     for (uint32_t g = 0; g < 4; ++g) {
       const uint64_t w = g < 2 ? (g == 0 ? who[0] : who[1]) : (g == 2 ? who[2] : who[3]);
-      if (w) offer(w, base + 64u * g);
+      if (w) offer(w, base, g);
     }
   }
 };
