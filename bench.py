@@ -27,9 +27,9 @@ BYTES_PER_PARTICLE = 12         # algorithmic: each float32 position read once
 # rocprofv3 FETCH_SIZE (x2.000) and WRITE_SIZE (x1.000) scaled by a 1 GiB device copy
 # (profiles/update_kernels_plummer_2e30.md).  Reported only while the kernel sources hash
 # to what was profiled; any change to them makes `traffic` null until measured again.
-TRAFFIC = {"bytes": 45_239_779_984, "particles": 1 << 30,
-           "sources_sha256": "e0e1f7bd342daf50b0b5635228e7ed48f7592ae02dc0c50787f91da9329cb834"}
-TRAFFIC_SOURCES = ["csk_update.hip", "csk_sortbin.hip", "csk_sortbin_body.h", "csk_kernel_util.h", "csk_device.h",
+TRAFFIC = {"bytes": 35_602_396_160, "particles": 1 << 30,
+           "sources_sha256": "6fd9ae57a260c7eb1775bde6040eee7cb095c24c0bcac42e458a8a155b273fcf"}
+TRAFFIC_SOURCES = ["csk_update.hip", "csk_append.hip", "csk_append_body.h", "csk_kernel_util.h", "csk_device.h",
                    "csk_internal.h"]
 
 
@@ -1144,7 +1144,7 @@ def main():
         "update_ms": upd_ms,
         "update_particles_per_s": n / (upd_ms / 1e3),
         "collect_ms": col_ms,
-        "roofline": {"kernel": "csk_sketch_update (sortbin_kernel + accumulate_kernel)", "bound": "hbm",
+        "roofline": {"kernel": "csk_sketch_update (append_kernel + accumulate_kernel)", "bound": "hbm",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(n)},
     }

@@ -57,8 +57,8 @@ __device__ __forceinline__ uint32_t shift_by(uint32_t x, uint32_t b) {
 // for all lanes), so their order over the lanes is chosen against them when the sketch is made.  Bound by
 // the VALU (4.5 instructions per row and key) and the LDS reads alike.  2000^3 keys, d = 5, w = 2^22, 88655
 // hot counters: 34.8 ms with a hash of four LDS reads and a computed probe per key and row, 7.95 ms so
-// with the values in their order (64 random words take 6.9 cycles), 7.03 ms in the chosen one (4.5 cycles); 34329 super-items of 1000 keys: 3.04 ms with every row's counter read,
-// 0.18 ms so.
+// with the values in their order (64 random words take 6.9 cycles), 7.03 ms in the chosen one (4.5
+// cycles); 34329 super-items of 1000 keys: 3.04 ms with every row's counter read, 0.18 ms so.
 template <int D, int HM, bool FP>
 struct KeyWalk {
   static constexpr int TW = FP ? 4 : HashWords<D, HM>::value;   // words per table entry
