@@ -445,11 +445,11 @@ constexpr uint32_t kRankWide = 4;   // winners per lane when there are many
 __device__ __forceinline__ uint64_t rank_word(uint32_t dist, uint64_t k) {
   return dist > 0xFFFFu ? ~0ull : ((uint64_t)dist << 48) | (kKeyMax - k);
 }
-// The winners [i0, i0 + 64 R) at their ranks among n (every thread of the block calls it).  T: the
-// smallest winner's estimate with its sign flipped.
+// The items [i0, i0 + 64 R) at their ranks among n, those below `want` (every thread of the block calls
+// it).  T: the smallest item's estimate with its sign flipped.
 template <uint32_t R>
 __device__ __forceinline__ void rank_block(const uint64_t* __restrict__ sk, const int32_t* __restrict__ se, uint32_t n,
-                                           uint32_t T, uint32_t i0, uint64_t* __restrict__ ok,
+                                           uint32_t T, uint32_t want, uint32_t i0, uint64_t* __restrict__ ok,
                                            int32_t* __restrict__ oe) {
   __shared__ uint64_t tw[kSelThreads];
   __shared__ uint32_t td[kSelThreads];
@@ -501,7 +501,7 @@ __device__ __forceinline__ void rank_block(const uint64_t* __restrict__ sk, cons
   for (uint32_t r = 0; r < R; ++r)
     if (cnt[r]) atomicAdd(&rank[64 * r + lane], cnt[r]);
   __syncthreads();
-  if (tid < 64 * R && i0 + tid < n) {
+  if (tid < 64 * R && i0 + tid < n && rank[tid] < want) {
     ok[rank[tid]] = sk[i0 + tid];
     oe[rank[tid]] = se[i0 + tid];
   }
@@ -527,13 +527,16 @@ __device__ __forceinline__ void sel_rank_body(const uint64_t* __restrict__ sk, c
                                               uint32_t* out, SelHost* host) {
   const uint32_t n = min(st->n_sel, k);
   if (blockIdx.x == 0 && threadIdx.x == 0) sel_result(st->m, k, err, partial, st, out, host);
-  for (uint32_t i0 = blockIdx.x * 64 * R; i0 < n; i0 += gridDim.x * 64 * R) rank_block<R>(sk, se, n, st->T, i0, ok, oe);
+  for (uint32_t i0 = blockIdx.x * 64 * R; i0 < n; i0 += gridDim.x * 64 * R) rank_block<R>(sk, se, n, st->T, n, i0, ok, oe);
 }
 
 // The whole selection in one block, for few candidates (any number is right, a large one slow): the
 // same passes with their histograms in LDS, then the gather, and the rank placement when k is at
 // most kOneRank (else the rank kernel follows).
 constexpr uint32_t kOneRank = 1024;
+// So few candidates are ranked outright: the square of them takes less than the passes with their barriers
+// (the top-100 of a 4093-particle stream: 21.2 us with the passes, 17.6 us so).
+constexpr uint32_t kOneDirect = 512;
 template <int MAXD>
 __global__ __launch_bounds__(kSelThreads) void sel_one_kernel(const uint64_t* __restrict__ list,
                                                               const uint32_t* __restrict__ count, uint32_t max_cand,
@@ -546,9 +549,11 @@ __global__ __launch_bounds__(kSelThreads) void sel_one_kernel(const uint64_t* __
                                                               const uint32_t* __restrict__ ov_counts,
                                                               uint32_t ov_mask) {
   __shared__ uint32_t h[kSelBins];
-  __shared__ uint32_t n_sel;
+  __shared__ uint32_t n_sel, lowest;
   const uint32_t tid = threadIdx.x;
   const uint32_t m = min(*count, max_cand);
+  const bool direct = m <= kOneDirect && k <= kOneRank;
+  if (tid == 0) lowest = ~0u;
   uint32_t need = min(k, m), T = 0;
   uint64_t K = 0;
   auto clear = [&](uint32_t nb) {
@@ -563,9 +568,19 @@ __global__ __launch_bounds__(kSelThreads) void sel_one_kernel(const uint64_t* __
     const int64_t exact = ov_keys ? table_count(ov_keys, ov_counts, ov_mask, key) : -1;
     const int32_t e = exact >= 0 ? (int32_t)exact : estimate_key<MAXD>(t.tab, M, t.d, t.w, t.cm, key);
     ce[i] = e;
-    atomicAdd(&h[2047u - (((uint32_t)e ^ 0x80000000u) >> 21)], 1u);
+    if (direct) atomicMin(&lowest, (uint32_t)e ^ 0x80000000u);
+    else atomicAdd(&h[2047u - (((uint32_t)e ^ 0x80000000u) >> 21)], 1u);
   }
   __syncthreads();
+  if (direct) {
+    if (tid == 0) {
+      st->m = m;
+      st->n_sel = need;
+      sel_result(m, k, err, partial, st, out, host);
+    }
+    for (uint32_t i0 = 0; i0 < m; i0 += 64 * kRankWide) rank_block<kRankWide>(list, ce, m, lowest, need, i0, ok, oe);
+    return;
+  }
   SelDigit f = sel_digit<11>(h, false, need);
   T = (2047u - f.bin) << 21;
   need -= f.before;
@@ -634,7 +649,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_one_kernel(const uint64_t* __
     sel_result(m, k, err, partial, st, out, host);
   }
   if (k <= kOneRank)
-    for (uint32_t i0 = 0; i0 < n; i0 += 64) rank_block<1>(sk, se, n, T, i0, ok, oe);
+    for (uint32_t i0 = 0; i0 < n; i0 += 64) rank_block<1>(sk, se, n, T, n, i0, ok, oe);
 }
 
 // ---- one selection

@@ -105,6 +105,26 @@ def test_ties_up_to_the_highest_key_bits(G):
         s.close()
 
 
+@pytest.mark.parametrize("n", [255, 256, 257, 511, 512, 513])
+@pytest.mark.parametrize("kind", ["ties", "near", "wide"])
+def test_candidates_ranked_outright(n, kind):
+    # at most 512 candidates are ranked without a selection, unless k is above 1024
+    d, w, seed = 5, 1 << 14, 3
+    pos, T = _cells(n, n), oracle.hash_tables(seed, d)
+    M = _counters(kind, d, w, n)
+    ko, eo = oracle.topk_keys(M, T, oracle.keys(pos, DELTA, L), csk.INT32_MIN, n)
+    s = csk.Sketch(d, w, seed)
+    try:
+        s.set_counters(_dev(M))
+        s.collect(_dev(pos), DELTA, L)
+        for k in (1, 64, 255, 256, n - 1, n, 1024, 1025):
+            kg, eg, _ = s.topk(k)
+            assert np.array_equal(kg.cpu().numpy().view(np.uint64), ko[:k]), k
+            assert np.array_equal(eg.cpu().numpy(), eo[:k]), k
+    finally:
+        s.close()
+
+
 def test_few_candidates_after_many():
     # one block selects, the rank kernel places (k > 1024): nothing is left of the selection before
     d, w, seed = 5, 1 << 14, 3
