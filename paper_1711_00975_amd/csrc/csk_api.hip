@@ -178,6 +178,8 @@ uint8_t* noalloc_scratch(int device) {
 
 }  // namespace
 
+constexpr uint64_t kCaptureUnknown = ~0ull;   // capture_id(): the runtime does not say
+
 struct csk_sketch {
   int device = 0;
   uint32_t d = 0, w = 0;
@@ -218,7 +220,29 @@ struct csk_sketch {
   Mesh mesh{};
   uint64_t cand_likely = 0;   // items offered to the candidate set since the last clear, as the host saw them
   bool partial_set = false;   // some collect since the last clear used theta > INT32_MIN
+  // Where the candidates come from (capture_id() of the calls): a graph's replays clear and insert without
+  // the host.
+  uint64_t cand_home = 0;     // of the last clear
+  bool cand_astray = false;   // some insertion since was not of cand_home
+  bool cand_recorded = false; // some insertion was ever recorded by a capture
   uint64_t bytes = 0;
+
+  void note_clear(uint64_t id) {
+    cand_home = id;
+    cand_astray = false;
+    cand_likely = 0;
+  }
+  void note_insert(uint64_t id, uint64_t items) {
+    cand_astray = cand_astray || id != cand_home;
+    cand_recorded = cand_recorded || id != 0;
+    cand_likely += items;
+  }
+  // Does the host know every call whose items the set holds when work recorded under (or run with) this
+  // id runs?  Run at once: after a clear run at once, with no recorded insertion that a replay could
+  // repeat.  Recorded: after a clear and insertions of the same capture, which every replay runs first.
+  bool candidates_known(uint64_t id) const {
+    return id == cand_home && id != kCaptureUnknown && !cand_astray && (id != 0 || !cand_recorded);
+  }
 
   uint32_t* err() const { return ctl; }
   uint32_t* set_count() const { return ctl + 1; }
@@ -316,11 +340,23 @@ void latch_mesh(csk_sketch* s, double delta, double L, const Mesh& m) {
   s->mesh = m;
 }
 
+// The capture that work on this stream is recorded by (their ids are unique), or 0 when it runs.
+uint64_t capture_id(hipStream_t st) {
+  if (st == nullptr) return 0;   // the legacy stream is never captured
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(st, &status, &id) != hipSuccess) {
+    (void)hipGetLastError();
+    return kCaptureUnknown;
+  }
+  return status == hipStreamCaptureStatusNone ? 0 : (uint64_t)id;
+}
+
 csk_status clear_candidates(csk_sketch* s, hipStream_t st) {
   CSK_HIP(launch_fill_u64(s->set, s->slots, kEmptyKey, st), "clear candidates");
   CSK_HIP(launch_fill_u32(s->set_count(), 1, 0u, st), "clear candidates");
   s->partial_set = false;
-  s->cand_likely = 0;
+  s->note_clear(capture_id(st));
   return CSK_OK;
 }
 
@@ -692,7 +728,7 @@ csk_status collect_impl(csk_sketch* s, const void* src, bool packed, uint64_t n,
   if (n > 0 && src == nullptr) return fail(CSK_E_INVALID, "collect: NULL positions");
   latch_mesh(s, delta, L, mesh);
   if (theta != INT32_MIN) s->partial_set = true;
-  s->cand_likely += n;
+  s->note_insert(capture_id((hipStream_t)stream), n);
   if (n == 0) return CSK_OK;
   if (packed) mesh.mode = kMeshPacked;
   hipStream_t st = (hipStream_t)stream;
@@ -746,7 +782,7 @@ csk_status csk_collect_dictionary(csk_sketch* s, double delta, double L, int32_t
   }
   const uint64_t ncells = (uint64_t)mesh.G * mesh.G * mesh.G;
   const uint64_t nkeys = (ncells + s->group - 1) / s->group;   // the items: cell keys / group
-  s->cand_likely += nkeys;
+  s->note_insert(capture_id(st), nkeys);
   CSK_HIP(launch_collect_dictionary(nkeys, mesh, t, s->M, theta, filter, hot, filter ? s->hot_table : nullptr,
                                     s->cand(), s->err(), st),
           "collect_dictionary");
@@ -778,7 +814,7 @@ csk_status csk_collect_children(csk_sketch* fine, csk_sketch* coarse, int32_t th
                                   filter ? filter + kFilterAllocWords : nullptr, fine->cand(), fine->err(), st),
           "collect_children");
   if (theta != INT32_MIN || coarse->partial_set) fine->partial_set = true;
-  fine->cand_likely += ncells;
+  fine->note_insert(capture_id(st), ncells);
   return CSK_OK;
 }
 
@@ -807,9 +843,11 @@ csk_status ensure_select_scratch(csk_sketch* s, uint32_t k, hipStream_t st, cons
   return CSK_OK;
 }
 
-// No item of the handle's mesh has a bit from here up.
-uint32_t key_bits(const csk_sketch* s) {
-  if (!s->mesh_set) return 8u * kChars;
+// No candidate that a selection under this capture_id() will find has a bit from here up: those of the
+// latched mesh, unless a graph may have put others in, or this selection is recorded by itself and may be
+// replayed on another mesh.
+uint32_t key_bits(const csk_sketch* s, uint64_t id) {
+  if (!s->mesh_set || !s->candidates_known(id)) return 8u * kChars;
   const uint64_t n = ((uint64_t)s->mesh.G * s->mesh.G * s->mesh.G + s->group - 1) / s->group;
   uint32_t b = 1;
   while (b < 8u * kChars && ((n - 1) >> b) != 0) ++b;
@@ -833,7 +871,7 @@ csk_status topk_impl(csk_sketch* s, uint32_t k, uint64_t* keys, int32_t* est, ui
     CSK_HIP(launch_topk(s->cand_key, s->set_count(), s->tables(), s->M, s->max_cand, s->cand_likely, k, s->sel,
                         s->cand_est, s->sel_key,
                         s->sel_est, keys, est, s->err(), partial, out, out ? nullptr : s->host_sel,
-                        x.keys ? 8u * kChars : key_bits(s), st, x.keys, x.counts, x.mask),
+                        x.keys ? 8u * kChars : key_bits(s, capture_id(st)), st, x.keys, x.counts, x.mask),
             who);
   else if (out)
     CSK_HIP(launch_fill_u32(out, 2, 0u, st), who);
@@ -913,7 +951,7 @@ csk_status csk_reset(csk_sketch* s, void* stream) {
   CSK_HIP(launch_fill_spans(f, st), "reset");
   s->mesh_set = false;
   s->partial_set = false;
-  s->cand_likely = 0;
+  s->note_clear(capture_id(st));
   return CSK_OK;
 }
 
@@ -1308,7 +1346,8 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
     call.partial[i] = b->sk[i]->partial_set ? 1u : 0u;
   }
   uint32_t bits = 0;
-  for (uint32_t i = 0; i < b->count; ++i) bits = std::max(bits, key_bits(b->sk[i]));
+  const uint64_t id = capture_id(st);
+  for (uint32_t i = 0; i < b->count; ++i) bits = std::max(bits, key_bits(b->sk[i], id));
   CSK_HIP(launch_topk_batch(b->topk, b->count, b->d, mc_max, k_max, call, bits, st), "batch_topk");
   return CSK_OK;
 }
@@ -1316,10 +1355,11 @@ csk_status csk_batch_topk(csk_batch* b, const uint32_t* k, uint64_t* const* keys
 csk_status csk_batch_reset(csk_batch* b, void* stream) {
   if (b == nullptr) return fail(CSK_E_INVALID, "batch_reset: NULL batch");
   CSK_HIP(launch_fill_spans_batch(b->rspans, b->count, b->rmax, (hipStream_t)stream), "batch_reset");
+  const uint64_t id = capture_id((hipStream_t)stream);
   for (csk_sketch* s : b->sk) {
     s->mesh_set = false;
     s->partial_set = false;
-    s->cand_likely = 0;
+    s->note_clear(id);
   }
   return CSK_OK;
 }
@@ -1343,6 +1383,7 @@ csk_status csk_batch_collect(csk_batch* b, const float* const* pos, const uint64
     }
     return CSK_OK;
   }
+  const uint64_t id = capture_id(st);
   CollectCall call{};
   for (uint32_t i = 0; i < b->count; ++i) {
     csk_sketch* s = b->sk[i];
@@ -1350,7 +1391,7 @@ csk_status csk_batch_collect(csk_batch* b, const float* const* pos, const uint64
     (void)check_mesh(s, b->delta[i], b->L[i], &m);
     latch_mesh(s, b->delta[i], b->L[i], m);
     if (theta[i] != INT32_MIN) s->partial_set = true;
-    s->cand_likely += n[i];
+    s->note_insert(id, n[i]);
     call.pos[i] = n[i] ? pos[i] : nullptr;
     call.n[i] = n[i];
     call.theta[i] = theta[i];
@@ -1739,7 +1780,7 @@ csk_status csk_topk_with_table(csk_sketch* s, const uint64_t* table_keys, const 
   if (k > s->max_cand) return fail(CSK_E_INVALID, "topk_with_table: k=%u above max_candidates", k);
   hipStream_t st = (hipStream_t)stream;
   CSK_HIP(launch_table_to_set(table_keys, table_slots, s->cand(), s->err(), st), "topk_with_table");
-  s->cand_likely += table_slots;
+  s->note_insert(capture_id(st), table_slots);
   return topk_impl(s, k, keys, est, nullptr, k_out, ExactTable{table_keys, table_counts, table_slots - 1}, st,
                    "topk_with_table");
 }
@@ -1775,7 +1816,7 @@ csk_status topk_with_table_impl(csk_sketch* s, const uint64_t* table_keys, const
   if (k > 0 && (keys == nullptr || est == nullptr)) return fail(CSK_E_INVALID, "%s: NULL output", who);
   if (k > s->max_cand) return fail(CSK_E_INVALID, "%s: k=%u above max_candidates", who, k);
   CSK_HIP(launch_table_to_set(table_keys, table_slots, s->cand(), s->err(), st), who);
-  s->cand_likely += table_slots;
+  s->note_insert(capture_id(st), table_slots);
   return topk_impl(s, k, keys, est, out, nullptr, ExactTable{table_keys, table_counts, table_slots - 1}, st, who);
 }
 

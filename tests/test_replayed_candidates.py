@@ -1,0 +1,113 @@
+"""Selections where HIP graphs put candidates into a handle unseen by the host, against the oracle,
+exactly: a selection recorded on a small mesh and replayed on one with larger keys, and a recorded
+candidate pass replayed behind the host's back."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1711_00975_amd as csk
+
+pytestmark = pytest.mark.gpu
+
+D, W, SEED = 5, 1 << 14, 3
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _record(call):
+    import torch
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    return g
+
+
+def _mesh(G, n, seed):
+    """n particles at cell centres of a mesh of G cells a side, its last cell among them."""
+    c = np.random.default_rng(seed).integers(0, G, (n, 3))
+    c[0] = G - 1
+    return (c + 0.5).astype(np.float32), float(G)
+
+
+def _ties(seed):
+    return np.random.default_rng(seed).integers(3, 5, (D, W)).astype(np.int32)
+
+
+class Out:
+    def __init__(self, k):
+        import torch
+        self.keys = torch.empty(k, dtype=torch.int64, device="cuda")
+        self.est = torch.empty(k, dtype=torch.int32, device="cuda")
+        self.out = torch.zeros(2, dtype=torch.int32, device="cuda")
+
+    def check(self, want):
+        import torch
+        torch.cuda.synchronize()
+        m = len(want[0])
+        assert int(self.out[0]) == m
+        assert np.array_equal(self.keys[:m].cpu().numpy().view(np.uint64), want[0])
+        assert np.array_equal(self.est[:m].cpu().numpy(), want[1])
+        self.keys.zero_(), self.est.zero_(), self.out.zero_()
+
+
+@pytest.mark.parametrize("form", ["single", "batch"])
+@pytest.mark.parametrize("k", [700, 5000])
+def test_a_selection_recorded_before_a_larger_mesh(form, k):
+    # keys of the first mesh are below 2^36, those of the second reach beyond; ties at the threshold
+    n, o = 20_000, Out(k)
+    (small, Ls), (large, Ll) = _mesh(1000, n, 1), _mesh(9000, n, 2)
+    M, T = _ties(k), oracle.hash_tables(SEED, D)
+    s = csk.Sketch(D, W, SEED)
+    b = csk.Batch([s], [n], 1.0, Ls) if form == "batch" else None
+    try:
+        def select():
+            if b is None:
+                s.topk_async(k, o.keys, o.est, o.out)
+            else:
+                b.topk([k], [o.keys], [o.est], [o.out])
+
+        s.set_counters(_dev(M))
+        s.collect(_dev(small), 1.0, Ls)
+        select()
+        o.check(oracle.topk_keys(M, T, oracle.keys(small, 1.0, Ls), csk.INT32_MIN, k))
+        g = _record(select)
+        for pos, L in ((large, Ll), (small, Ls), (large, Ll)):
+            s.reset()
+            s.set_counters(_dev(M))
+            s.collect(_dev(pos), 1.0, L)
+            g.replay()
+            o.check(oracle.topk_keys(M, T, oracle.keys(pos, 1.0, L), csk.INT32_MIN, k))
+    finally:
+        if b is not None:
+            b.close()
+        s.close()
+
+
+def test_a_candidate_pass_replayed_after_a_smaller_mesh():
+    # the estimates have four values, about 10^4 cells each: the ties of the second one are all the
+    # small keys' and some of the large
+    n, k = 20_000, 18_000
+    (small, Ls), (large, Ll) = _mesh(1000, n, 3), _mesh(9000, n, 4)
+    M, T = _ties(9), oracle.hash_tables(SEED, D)
+    s = csk.Sketch(D, W, SEED)
+    try:
+        s.set_counters(_dev(M))
+        p = _dev(large)
+        s.collect(p, 1.0, Ll)
+        g = _record(lambda: s.collect(p, 1.0, Ll))
+        keys = np.concatenate([oracle.keys(small, 1.0, Ls), oracle.keys(large, 1.0, Ll)])
+        for rep in range(3):
+            s.reset()
+            s.set_counters(_dev(M))
+            s.collect(_dev(small), 1.0, Ls)
+            g.replay()
+            kg, eg, _ = s.topk(k)
+            ko, eo = oracle.topk_keys(M, T, keys, csk.INT32_MIN, k)
+            assert np.array_equal(kg.cpu().numpy().view(np.uint64), ko), rep
+            assert np.array_equal(eg.cpu().numpy(), eo), rep
+    finally:
+        s.close()
