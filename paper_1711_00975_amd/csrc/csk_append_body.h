@@ -258,7 +258,7 @@ __device__ __forceinline__ void append_body(const BinArgs* __restrict__ ap, cons
         }
       } else {
         if (tj < 4 * ng) x0[e] = src[tj];
-        if (ng && tj < 4) y[e] = src[4 * ng + tj];
+        if (8 * tj < (ng ? fill[e] % GT : 0u)) y[e] = src[4 * ng + tj];   // what is left, no more
       }
       full |= ng && done[e] + ng > sent_max;
     }

@@ -124,3 +124,9 @@ def test_packed_stream(w):
         s.close()
     keys = oracle.keys_packed(oracle.pack(pos, L), delta, L)
     assert np.array_equal(M, oracle.sketch_keys(keys, d, w, 5))
+
+
+@pytest.mark.parametrize("d,w", [(1, 1), (1, 1000), (2, 3), (1, 1 << 15)])
+def test_buffers_full_to_the_end_of_lds(d, w):
+    # one or two bins of 4096 tokens, the last of LDS, full at every flush
+    _check(300_001, d, w, 100.0, 0.1, 0, "mixed", 2)
