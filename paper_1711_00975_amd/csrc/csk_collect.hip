@@ -43,7 +43,9 @@ __global__ __launch_bounds__(256) void collect_kernel(const float* __restrict__ 
 // The candidate pass of a short stream: one particle per thread, every row's counter read at once
 // and tested exactly, with no filter to build.  A workgroup's new keys take their places in the list
 // with one add to the count: wave by wave those adds, all to one word, took longer than the reads (2.4e5
-// particles, 5e4 candidates: 186 us, 26 us so).
+// particles, 5e4 candidates: 186 us, 26 us so).  That holds back a workgroup's keys, and all of them
+// together may hold back a quarter of the slots; a stream that could claim more than there is (n particles
+// beside max_cand) lists key by key.
 template <int MAXD>
 __global__ __launch_bounds__(1024) void collect_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
                                                             Tables t, const int32_t* __restrict__ M, int32_t theta,
@@ -62,9 +64,18 @@ __global__ __launch_bounds__(1024) void collect_short_kernel(const float* __rest
     if ((uint32_t)r < t.d && row_estimate(t.tab + r * kTableWords, M + (uint64_t)r * t.w, t.w, t.cm, key) >= theta) ++pass;
   const bool mine = ok && pass >= need;
   if (!__syncthreads_or(mine)) return;
-  if (threadIdx.x == 0) room = __hip_atomic_load(cand.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < cand.max_cand;
+  if (threadIdx.x == 0) {
+    const uint32_t used = set_used(cand);
+    room = (uint64_t)used + n <= (uint64_t)cand.max_cand + (cand.slot_mask + 1u) / 4u ? 1u : 2u;
+    if (used >= cand.max_cand) room = latched(err, kErrCapacity) ? 3u : 0u;
+  }
   __syncthreads();
-  const bool is_new = mine && set_claim(cand, key, err, [&]() { return room != 0; });
+  if (room == 3u) return;   // uniform: no key can get in, and the error says so
+  if (room == 2u) {
+    if (mine) set_insert(cand, key, err);
+    return;
+  }
+  const bool is_new = mine && set_claim(cand, key, err, [&]() { return room != 0; }) == kClaimNew;
   const uint32_t at = wave_append(&found, is_new);
   __syncthreads();
   if (threadIdx.x == 0) base = found ? atomicAdd(cand.count, found) : 0u;

@@ -99,7 +99,10 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
   uint16_t* qhi = (uint16_t*)((uint32_t*)(cache + CE) + 64u * kWaves) + 64u * wave;
   constexpr uint32_t NF = collect2_fresh<FP, KB>();
   uint64_t* fresh = (uint64_t*)((uint32_t*)(cache + CE) + 96u * kWaves);   // NF new keys
-  // ctl: slots of fresh handed out, the first ones refused (all after are), the set is full, list base
+  // All workgroups together hold back at most a quarter of the slots: the set stays a table with room.
+  const uint32_t hold = min(NF, (slot_mask + 1u) / (4u * nwg));
+  // ctl: slots of fresh handed out, the first ones refused (all after are), a key was refused by the set, the
+  // set was full before this call (in the end: list base)
   uint32_t* ctl = (uint32_t*)(fresh + NF);
   uint32_t* filt = ctl + 4;
   const uint32_t nhot = use_filter ? *hot : 0xFFFFFFFFu;
@@ -111,7 +114,8 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
     for (uint32_t i = threadIdx.x; i < FW / 4; i += blockDim.x) ((V4*)filt)[i] = ((const V4*)filter)[i];
   }
   for (uint32_t i = threadIdx.x; i < CE; i += blockDim.x) cache[i] = kEmptyKey;
-  if (threadIdx.x < 4) ctl[threadIdx.x] = threadIdx.x == 1 ? NF : 0u;
+  if (threadIdx.x < 4)
+    ctl[threadIdx.x] = threadIdx.x == 1 ? hold : threadIdx.x == 3 && *cand.count >= cand.max_cand ? 1u : 0u;
   stage_tables<DP>(ti, FP ? t.tabq : (HM == kHashPacked ? t.tabp : t.tabi), (uint32_t)KB, (uint32_t)KB);
   // (bucket, sign) of every row for the exact test: from the staged tables, or (FP) from
   // the packed or row-interleaved tables in device memory over all six key bytes
@@ -129,6 +133,12 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
   uint32_t queued = 0;
   auto cache_slot = [](uint64_t key) { return (uint32_t)(key ^ (key >> 21)) & (CE - 1u); };
   auto flush = [&]() {
+    // a key was refused: the error is latched and no other can get in
+    if (__builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(&ctl[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0u) {
+      queued = 0;
+      return;
+    }
     const bool act = lane < queued;
     const uint64_t key = act ? (uint64_t)qhi[lane] << 32 | qlo[lane] : 0ull;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -143,13 +153,16 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
 #pragma unroll
       for (int r = 0; r < D; ++r) ng[r] &= t.cm ^ 1u;
       in = rows_pass<D>(bk, ng, need, nullptr, M, t.w, theta);
-      if (in)
-        is_new = set_claim(cand, key, err, [&]() {
-          return __hip_atomic_load(&ctl[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
+      if (in) {
+        const uint32_t got = set_claim(cand, key, err, [&]() {
+          return __hip_atomic_load(&ctl[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
         });
+        is_new = got == kClaimNew;
+        if (got == kClaimRefused) __hip_atomic_store(&ctl[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
     }
     if (in) __hip_atomic_store(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    // New keys go into the list with the workgroup's others when it ends, past NF of them here and now:
+    // New keys go into the list with the workgroup's others when it ends, past `hold` of them here and now:
     // one or two at a time they kept the kernel waiting for the count (about 40 ns an add, one after
     // the other over all XCDs).  The count tells then whether the set is full.
     const uint64_t who = __ballot(is_new);
@@ -159,7 +172,7 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
     uint32_t at = 0;
     if (lane == 0) at = __hip_atomic_fetch_add(&ctl[0], more, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     at = __builtin_amdgcn_readfirstlane(at);
-    if (at + more <= NF) {
+    if (at + more <= hold) {
       if (is_new) fresh[at + rank] = key;
       return;
     }

@@ -102,9 +102,11 @@ __device__ __forceinline__ void load_tables(uint32_t* dst, const uint32_t* __res
 
 // ------------------------------------------------------------------ candidate set
 
-// Longest probe sequence of the candidate set.  Inserts stop at max_candidates, so the
-// table (2^ceil(log2(2 max_candidates)) slots) stays at most about half full and real
-// probe runs are far shorter; the cap only bounds the work when the set is over capacity.
+// Longest probe sequence of the candidate set.  Inserts stop at max_candidates listed keys, and a
+// kernel holds back at most a quarter of the slots before it lists them, so the table
+// (2^ceil(log2(2 max_candidates)) slots) stays at most three quarters full but for what is in flight
+// when it fills up, and real probe runs are far shorter; the cap only bounds the work when the set is over
+// capacity.
 constexpr uint32_t kMaxProbe = 4096;
 
 // Is key already in the candidate set?  (A stale read can only miss a key.)
@@ -119,36 +121,47 @@ __device__ __forceinline__ bool set_contains(const uint64_t* set, uint32_t mask,
   return false;
 }
 
-// Put a key into the set: true when this call did (the caller then appends it to the list), false when
-// it was there already.  room(): may a new key still go in?  (No room is the capacity error.)
+// Is this error there already?
+__device__ __forceinline__ bool latched(const uint32_t* err, uint32_t bit) {
+  return (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) != 0u;
+}
+
+// Put a key into the set: kClaimNew when this call did (the caller then appends it to the list),
+// kClaimThere when it was there already, kClaimRefused (the capacity error, latched) when there is no
+// place for it.  room(): may a new key still go in?  A run of hundreds is one of a table that overflowed
+// while many keys were in flight: it ends when the error is there.
+constexpr uint32_t kClaimThere = 0, kClaimNew = 1, kClaimRefused = 2;
 template <class Room>
-__device__ __forceinline__ bool set_claim(const CandSet& c, uint64_t key, uint32_t* err, Room room) {
+__device__ __forceinline__ uint32_t set_claim(const CandSet& c, uint64_t key, uint32_t* err, Room room) {
   const uint32_t mask = c.slot_mask;
   uint32_t i = (uint32_t)slot_mix(key) & mask;
   for (uint32_t probe = 0; probe <= mask && probe < kMaxProbe; ++probe) {
     // A slot only ever changes from empty to a key, so a stale read can only show "empty"; the
     // compare-and-swap then tells the truth.
     const uint64_t cur = c.set[i];
-    if (cur == key) return false;
+    if (cur == key) return kClaimThere;
     if (cur == kEmptyKey) {
       if (!room()) break;
       const uint64_t old = atomicCAS((unsigned long long*)&c.set[i], (unsigned long long)kEmptyKey,
                                      (unsigned long long)key);
-      if (old == kEmptyKey) return true;
-      if (old == key) return false;
+      if (old == kEmptyKey) return kClaimNew;
+      if (old == key) return kClaimThere;
     }
+    if ((probe & 255u) == 255u && latched(err, kErrCapacity)) return kClaimRefused;
     i = (i + 1) & mask;
   }
   atomicOr(err, kErrCapacity);
-  return false;
+  return kClaimRefused;
+}
+
+// Keys listed, or about to be: a set is full from max_cand on.
+__device__ __forceinline__ uint32_t set_used(const CandSet& c) {
+  return __hip_atomic_load(c.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // A key into the set and the list; once the set holds max_candidates keys no more go in.
 __device__ __forceinline__ void set_insert(const CandSet& c, uint64_t key, uint32_t* err) {
-  if (!set_claim(c, key, err, [&]() {
-        return __hip_atomic_load(c.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < c.max_cand;
-      }))
-    return;
+  if (set_claim(c, key, err, [&]() { return set_used(c) < c.max_cand; }) != kClaimNew) return;
   const uint32_t at = atomicAdd(c.count, 1u);
   if (at < c.max_cand) c.list[at] = key;
   else atomicOr(err, kErrCapacity);

@@ -133,3 +133,39 @@ def test_a_batch_of_them():
     finally:
         for s in sk:
             s.close()
+
+
+@pytest.mark.parametrize("n", [1 << 19, 1 << 24])
+def test_a_set_that_is_full_ends_the_look_ups(n):
+    # once a key was refused (the error) no other can get in: the rest of the stream costs its hashes,
+    # not a walk through the whole table per particle
+    import time
+    import torch
+    print("full table", n, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    pos = torch.rand((n, 3), generator=gen, device="cuda") * L
+    same = torch.full((n, 3), 12.34, device="cuda")
+    s = csk.Sketch(5, 1 << 14, 5, 0, 1 << 12)
+    try:
+        def seconds(p):
+            best = float("inf")
+            for _ in range(3):
+                s.clear_candidates()
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                s.collect(p, DELTA, L)
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t)
+            return best
+
+        one = seconds(same)
+        kg, _, _ = s.topk(10)
+        assert len(kg) == 1
+        took = seconds(pos)
+        with pytest.raises(csk.CskError) as ei:
+            s.topk(10)
+        assert ei.value.code == csk.CSK_E_CAPACITY
+        print(f"{n} particles: one cell {one * 1e6:.0f} us, a full set {took * 1e6:.0f} us", flush=True)
+        assert took < 5 * one + 2e-3
+    finally:
+        s.close()
