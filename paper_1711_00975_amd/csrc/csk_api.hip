@@ -867,11 +867,13 @@ csk_status topk_impl(csk_sketch* s, uint32_t k, uint64_t* keys, int32_t* est, ui
   csk_status rc = ensure_select_scratch(s, k, st, who);
   if (rc != CSK_OK) return rc;
   const uint32_t partial = s->partial_set ? 1u : 0u;
+  const uint64_t id = capture_id(st);
+  // candidates that a graph may put in unseen: as many as the list holds
+  const uint64_t likely = s->candidates_known(id) ? s->cand_likely : s->max_cand;
   if (k > 0)
-    CSK_HIP(launch_topk(s->cand_key, s->set_count(), s->tables(), s->M, s->max_cand, s->cand_likely, k, s->sel,
-                        s->cand_est, s->sel_key,
-                        s->sel_est, keys, est, s->err(), partial, out, out ? nullptr : s->host_sel,
-                        x.keys ? 8u * kChars : key_bits(s, capture_id(st)), st, x.keys, x.counts, x.mask),
+    CSK_HIP(launch_topk(s->cand_key, s->set_count(), s->tables(), s->M, s->max_cand, likely, k, s->sel, s->cand_est,
+                        s->sel_key, s->sel_est, keys, est, s->err(), partial, out, out ? nullptr : s->host_sel,
+                        x.keys ? 8u * kChars : key_bits(s, id), st, x.keys, x.counts, x.mask),
             who);
   else if (out)
     CSK_HIP(launch_fill_u32(out, 2, 0u, st), who);

@@ -1,6 +1,8 @@
 """Selections where HIP graphs put candidates into a handle unseen by the host, against the oracle,
 exactly: a selection recorded on a small mesh and replayed on one with larger keys, and a recorded
-candidate pass replayed behind the host's back."""
+candidate pass replayed behind the host's back, whose candidates are also selected in good time."""
+import time
+
 import numpy as np
 import pytest
 
@@ -111,3 +113,60 @@ def test_a_candidate_pass_replayed_after_a_smaller_mesh():
             assert np.array_equal(eg.cpu().numpy(), eo), rep
     finally:
         s.close()
+
+
+def _best(call, before):
+    """The least of three times of call, in seconds, the device idle before and after."""
+    import torch
+    best = float("inf")
+    for _ in range(3):
+        before()
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("what", ["pass", "selection"])
+def test_replays_with_many_candidates_are_selected_by_many_blocks(what):
+    # 2^20 cells: one workgroup alone takes more than ten times as long as the card (the host sees
+    # few candidates or none: they come from a recorded pass, or after the selection was recorded)
+    n, k = 1 << 20, 100
+    few, L = _mesh(1000, 50, 5)
+    many, _ = _mesh(1000, n, 6)
+    M, T = np.random.default_rng(7).integers(-60000, 60000, (D, W)).astype(np.int32), oracle.hash_tables(SEED, D)
+    want = oracle.topk_keys(M, T, oracle.keys(many, 1.0, L), csk.INT32_MIN, k)
+    p, q, o = _dev(many), _dev(few), Out(k)
+    s, plain = csk.Sketch(D, W, SEED), csk.Sketch(D, W, SEED)
+    try:
+        for h in (s, plain):
+            h.set_counters(_dev(M))
+            h.collect(p, 1.0, L)
+            h.topk_async(k, o.keys, o.est, o.out)
+        o.check(want)
+
+        def fill(h):
+            h.clear_candidates()
+            h.collect(p, 1.0, L)
+
+        usual = _best(lambda: plain.topk_async(k, o.keys, o.est, o.out), lambda: fill(plain))
+        if what == "pass":
+            g = _record(lambda: s.collect(p, 1.0, L))
+
+            def before():
+                s.clear_candidates()
+                g.replay()
+            took = _best(lambda: s.topk_async(k, o.keys, o.est, o.out), before)
+        else:
+            s.clear_candidates()
+            s.collect(q, 1.0, L)
+            g = _record(lambda: s.topk_async(k, o.keys, o.est, o.out))
+            took = _best(g.replay, lambda: fill(s))
+        o.check(want)
+        print(f"selection of {n} candidates: {usual * 1e6:.0f} us, replayed {took * 1e6:.0f} us", flush=True)
+        assert took < 5 * usual + 100e-6
+    finally:
+        s.close()
+        plain.close()
