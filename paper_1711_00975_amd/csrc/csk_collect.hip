@@ -46,11 +46,15 @@ __global__ __launch_bounds__(256) void collect_kernel(const float* __restrict__ 
 // particles, 5e4 candidates: 186 us, 26 us so).  That holds back a workgroup's keys, and all of them
 // together may hold back a quarter of the slots; a stream that could claim more than there is (n particles
 // beside max_cand) lists key by key.
+// A key that many particles share claims once per workgroup: of the lanes whose key has the slot of `seen`,
+// the first one goes on (2^17 particles of one cell: 0.2 to 1.3 ms with a compare-and-swap each, 20 us so).
 template <int MAXD>
 __global__ __launch_bounds__(1024) void collect_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
                                                             Tables t, const int32_t* __restrict__ M, int32_t theta,
                                                             CandSet cand, uint32_t* err) {
+  __shared__ unsigned long long seen[1024];   // a slot per thread
   __shared__ uint32_t found, base, room;
+  seen[threadIdx.x] = kEmptyKey;
   if (threadIdx.x == 0) found = 0;
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   uint64_t key;
@@ -62,13 +66,16 @@ __global__ __launch_bounds__(1024) void collect_short_kernel(const float* __rest
 #pragma unroll
   for (int r = 0; r < MAXD; ++r)
     if ((uint32_t)r < t.d && row_estimate(t.tab + r * kTableWords, M + (uint64_t)r * t.w, t.w, t.cm, key) >= theta) ++pass;
-  const bool mine = ok && pass >= need;
+  bool mine = ok && pass >= need;
   if (!__syncthreads_or(mine)) return;
   if (threadIdx.x == 0) {
     const uint32_t used = set_used(cand);
     room = (uint64_t)used + n <= (uint64_t)cand.max_cand + (cand.slot_mask + 1u) / 4u ? 1u : 2u;
     if (used >= cand.max_cand) room = latched(err, kErrCapacity) ? 3u : 0u;
   }
+  if (mine)
+    mine = atomicCAS(&seen[(uint32_t)(slot_mix(key) >> 54) & (blockDim.x - 1u)], (unsigned long long)kEmptyKey,
+                     (unsigned long long)key) != key;
   __syncthreads();
   if (room == 3u) return;   // uniform: no key can get in, and the error says so
   if (room == 2u) {

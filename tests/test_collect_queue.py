@@ -169,3 +169,38 @@ def test_a_set_that_is_full_ends_the_look_ups(n):
         assert took < 5 * one + 2e-3
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("d,w", [(5, 1 << 16), (2, 5000), (9, 1 << 16)])
+@pytest.mark.parametrize("cells", [1, 64])
+def test_short_streams_of_few_cells(d, w, cells):
+    # a key that all particles share is claimed by a few of them: in the time of a stream of many cells
+    import time
+    import torch
+    n = 1 << 17
+    rng = np.random.default_rng(cells)
+    c = rng.uniform(0, L, (cells, 3)).astype(np.float32)[rng.integers(0, cells, n)]
+    spread = rng.uniform(0, L, (n, 3)).astype(np.float32)
+    M, T = _counters(d, w, 0.97, 0, d), oracle.hash_tables(5, d)
+    s = csk.Sketch(d, w, 5, 0, 1 << 20)
+    try:
+        s.set_counters(_dev(M))
+
+        def microseconds(p):
+            best = float("inf")
+            for _ in range(5):
+                s.clear_candidates()
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                s.collect(p, DELTA, L, csk.INT32_MIN)
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t)
+            return best * 1e6
+
+        usual, few = microseconds(_dev(spread)), microseconds(_dev(c))
+        print(f"d={d}: {n} particles of many cells {usual:.0f} us, of {cells} {few:.0f} us", flush=True)
+        _check(s, _want(M, T, oracle.keys(c, DELTA, L), csk.INT32_MIN, 0))
+        if d <= 8:      # more rows take the general kernel
+            assert few < 2 * usual + 50
+    finally:
+        s.close()
