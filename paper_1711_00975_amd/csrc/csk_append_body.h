@@ -381,7 +381,16 @@ __device__ __forceinline__ void append_body(const BinArgs* __restrict__ ap, cons
   }
   if (!mine)
     for (uint32_t s = tid; s < P; s += kNT) a.cnt[(uint64_t)s * pl.nwg + g] = 0;
-  if (bad) atomicOr(a.err, kErrDomain);
+  // The error once a workgroup: all go to one word.  (By hand, in counts that are done with: the barrier that
+  // ORs a predicate brings LDS of its own, and the dynamic part may be all there is.)
+  const bool some = __any(bad);
+  if (lane == 0) cnt[tid >> 6] = some ? 1u : 0u;
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t any = 0;
+    for (uint32_t i = 0; i < kNT / 64u; ++i) any |= cnt[i];
+    if (any) atomicOr(a.err, kErrDomain);
+  }
 }
 
 template <int D, uint32_t MODE, bool ROWS, bool EX, int KB, bool HOLD>

@@ -53,21 +53,26 @@ __global__ __launch_bounds__(1024) void collect_short_kernel(const float* __rest
                                                             Tables t, const int32_t* __restrict__ M, int32_t theta,
                                                             CandSet cand, uint32_t* err) {
   __shared__ unsigned long long seen[1024];   // a slot per thread
-  __shared__ uint32_t found, base, room;
+  __shared__ uint32_t found, base, room, some[16];   // some: bit 0 a passing particle of the wave, 1 one outside
   seen[threadIdx.x] = kEmptyKey;
   if (threadIdx.x == 0) found = 0;
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   uint64_t key;
   const bool in = i < n;
   const bool ok = particle_key(pos, in ? i : n - 1, mesh, key) && in;
-  if (in && !ok) atomicOr(err, kErrDomain);
   const uint32_t need = t.cm ? t.d : t.d - ((t.d - 1) >> 1);
   uint32_t pass = 0;
 #pragma unroll
   for (int r = 0; r < MAXD; ++r)
     if ((uint32_t)r < t.d && row_estimate(t.tab + r * kTableWords, M + (uint64_t)r * t.w, t.w, t.cm, key) >= theta) ++pass;
   bool mine = ok && pass >= need;
-  if (!__syncthreads_or(mine)) return;
+  const uint32_t of_wave = (__any(mine) ? 1u : 0u) | (__any(in && !ok) ? 2u : 0u);
+  if (lane_id() == 0) some[threadIdx.x >> 6] = of_wave;
+  __syncthreads();
+  uint32_t any = 0;
+  for (uint32_t wv = 0; wv < blockDim.x / 64u; ++wv) any |= some[wv];
+  if ((any & 2u) && threadIdx.x == 0) atomicOr(err, kErrDomain);   // one a workgroup: all go to one word
+  if (!(any & 1u)) return;   // uniform
   if (threadIdx.x == 0) {
     const uint32_t used = set_used(cand);
     room = (uint64_t)used + n <= (uint64_t)cand.max_cand + (cand.slot_mask + 1u) / 4u ? 1u : 2u;

@@ -309,17 +309,24 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
   }
   if (queued) flush();
   __syncthreads();
+  // The domain error once a workgroup: all go to one word.  (By hand, in the queues' first words, which are
+  // done with: the barrier that ORs a predicate brings LDS of its own, and the dynamic part is all there is.)
+  uint32_t* outside = (uint32_t*)(cache + CE);
+  const bool some_bad = __any(bad);
+  if (lane == 0) outside[wave] = some_bad ? 1u : 0u;
   const uint32_t nf = min(ctl[0], ctl[1]);   // the slots handed out before the first that was refused
-  if (nf != 0) {
-    if (threadIdx.x == 0) ctl[3] = atomicAdd(cand.count, nf);
-    __syncthreads();
-    const uint32_t base = ctl[3];
-    for (uint32_t i = threadIdx.x; i < nf; i += kCollectThreads) {
-      if (base + i < cand.max_cand) cand.list[base + i] = fresh[i];
-      else atomicOr(err, kErrCapacity);
-    }
+  if (threadIdx.x == 0 && nf != 0) ctl[3] = atomicAdd(cand.count, nf);
+  __syncthreads();
+  const uint32_t base = ctl[3];
+  for (uint32_t i = threadIdx.x; i < nf; i += kCollectThreads) {
+    if (base + i < cand.max_cand) cand.list[base + i] = fresh[i];
+    else atomicOr(err, kErrCapacity);
   }
-  if (bad) atomicOr(err, kErrDomain);
+  if (threadIdx.x == 0) {
+    uint32_t any = 0;
+    for (uint32_t i = 0; i < kWaves; ++i) any |= outside[i];
+    if (any) atomicOr(err, kErrDomain);
+  }
 }
 
 template <int D, uint32_t MODE, int HM, bool FP, int KB>

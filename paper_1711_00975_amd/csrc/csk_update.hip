@@ -835,7 +835,7 @@ __global__ __launch_bounds__(256) void update_short_kernel(const float* __restri
   uint64_t key;
   const bool in = i < n;
   const bool ok = particle_key(pos, in ? i : n - 1, mesh, key) && in;
-  if (in && !ok && r == 0) atomicOr(err, kErrDomain);
+  if (r == 0 && __syncthreads_or(in && !ok) && threadIdx.x == 0) atomicOr(err, kErrDomain);   // r is uniform
   const uint32_t h = row_hash(tab + r * kTableWords, key);   // every byte indexes its table in range
   const uint32_t b = bucket_of(h, w), neg = (h >> 31) & (cm ^ 1u);
   int32_t* Mr = M + (uint64_t)r * w;

@@ -204,3 +204,46 @@ def test_short_streams_of_few_cells(d, w, cells):
             assert few < 2 * usual + 50
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("n", [1 << 16, 1 << 19])
+def test_particles_outside_of_short_streams_are_latched_in_passing(n):
+    # half of the particles outside: reported, skipped, and in the time of a stream that is all inside
+    import time
+    import torch
+    d, w, seed = 2, 5000, 5
+    rng = np.random.default_rng(n)
+    pos = rng.uniform(0, L, (n, 3)).astype(np.float32)
+    out = pos.copy()
+    out[::2, 0] = np.nan
+    s = csk.Sketch(d, w, seed, 0, 1 << 21)
+    try:
+        def microseconds(call):
+            best = float("inf")
+            for _ in range(5):
+                s.reset()
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                call()
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t)
+            return best * 1e6
+
+        for call in (s.update, lambda *a: s.collect(*a, 1 << 20)):
+            inside, outside = _dev(pos), _dev(out)
+            usual = microseconds(lambda: call(inside, DELTA, L))
+            s.check()
+            took = microseconds(lambda: call(outside, DELTA, L))
+            with pytest.raises(csk.CskError) as ei:
+                s.check()
+            assert ei.value.code == csk.CSK_E_DOMAIN
+            print(f"{n} particles: all inside {usual:.0f} us, half outside {took:.0f} us", flush=True)
+            assert took < 1.5 * usual + 20
+        s.reset()
+        s.update(_dev(out), DELTA, L)
+        with pytest.raises(csk.CskError):
+            s.check()
+        M, skipped = oracle.sketch(out, d, w, seed, DELTA, L, threads=8)
+        assert skipped == n // 2 and np.array_equal(s.counters().cpu().numpy(), M)
+    finally:
+        s.close()
