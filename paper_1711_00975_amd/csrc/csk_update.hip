@@ -824,14 +824,20 @@ __global__ __launch_bounds__(256) void update_direct_kernel(const float* __restr
   }
 }
 
-// The direct update of a short stream: one thread per particle and row (blockIdx.y), so that a
-// few thousand particles are enough threads to hide the two memory round trips (position, the
-// row's six table entries) behind each other.  Lanes of a wave with the same counter and sign
+// The direct update of a short stream: one thread per particle and row, so that a few thousand
+// particles are enough threads to hide the two memory round trips (position, the row's six table entries)
+// behind each other.  The rows take turns every 8 blocks of particles: row after row, the blocks in flight
+// would all add to one row's counters (2^20 particles of 64 cells, d = 5, w = 2^16: 0.91 ms, 0.67 so), and
+// 8 blocks on, the same particles meet the same XCD, whose L2 has them.
+// Lanes of a wave with the same counter and sign
 // (a stream in structure order) add together, for the first few such groups of the wave.
+constexpr uint32_t kXcds = 8;
 __global__ __launch_bounds__(256) void update_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
-                                                           const uint32_t* __restrict__ tab, uint32_t w, uint32_t cm,
-                                                           int32_t* __restrict__ M, uint32_t* __restrict__ err) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
+                                                           const uint32_t* __restrict__ tab, uint32_t d, uint32_t w,
+                                                           uint32_t cm, int32_t* __restrict__ M,
+                                                           uint32_t* __restrict__ err) {
+  const uint32_t turn = blockIdx.x / kXcds, r = turn % d;
+  const uint32_t i = (turn / d * kXcds + blockIdx.x % kXcds) * 256 + threadIdx.x;
   uint64_t key;
   const bool in = i < n;
   const bool ok = particle_key(pos, in ? i : n - 1, mesh, key) && in;
@@ -854,8 +860,8 @@ __global__ __launch_bounds__(256) void update_short_kernel(const float* __restri
 hipError_t launch_update_direct(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, int32_t* M,
                                 uint32_t* err, hipStream_t s) {
   if (n <= kShortStream) {
-    hipLaunchKernelGGL(update_short_kernel, dim3((uint32_t)((n + 255) / 256), t.d), dim3(256), 0, s, pos, (uint32_t)n,
-                       mesh, t.tab, t.w, t.cm, M, err);
+    hipLaunchKernelGGL(update_short_kernel, dim3((uint32_t)((n + 256 * kXcds - 1) / (256 * kXcds)) * kXcds * t.d), dim3(256), 0,
+                       s, pos, (uint32_t)n, mesh, t.tab, t.d, t.w, t.cm, M, err);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(update_direct_kernel, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, pos, n, mesh, t.tab,

@@ -130,3 +130,33 @@ def test_packed_stream(w):
 def test_buffers_full_to_the_end_of_lds(d, w):
     # one or two bins of 4096 tokens, the last of LDS, full at every flush
     _check(300_001, d, w, 100.0, 0.1, 0, "mixed", 2)
+
+
+@pytest.mark.parametrize("d,w", [(5, 1 << 16), (2, 5000)])
+def test_direct_update_of_few_cells(d, w):
+    # up to 2^20 particles one thread takes a particle and row, above it a particle: with 64 cells the adds
+    # meet on few counters, and the first must not be the slower by more than a tenth
+    import time
+    import torch
+    rng = np.random.default_rng(d)
+    pos = rng.uniform(0, 100, (64, 3)).astype(np.float32)[rng.integers(0, 64, (1 << 20) + 1)]
+    s = csk.Sketch(d, w, 5)
+    try:
+        s.set_update_plan(csk.CSK_UPDATE_DIRECT, 0)
+        took = {}
+        for n in (1 << 20, (1 << 20) + 1):
+            p = _dev(pos[:n])
+            took[n] = float("inf")
+            for _ in range(8):
+                s.reset()
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                s.update(p, 0.1, 100.0)
+                torch.cuda.synchronize()
+                took[n] = min(took[n], time.perf_counter() - t)
+            Mo, _ = oracle.sketch(pos[:n], d, w, 5, 0.1, 100.0, threads=8)
+            assert np.array_equal(s.counters().cpu().numpy(), Mo), n
+        print("direct update of 64 cells:", {n: f"{t * 1e6:.0f} us" for n, t in took.items()}, flush=True)
+        assert took[1 << 20] < 1.1 * took[(1 << 20) + 1]
+    finally:
+        s.close()
