@@ -148,8 +148,8 @@ std::vector<uint32_t> probe_tables(const std::vector<uint32_t>& T, uint32_t d, u
   return Q;
 }
 
-// Scratch of csk_sketch_update_noalloc: the token regions of one bin plan, then their
-// counts.  Each device holds its own copy for the life of the process; host code never
+// Scratch of csk_sketch_update_noalloc: the token regions of one bin plan, their counts,
+// and partial slices in what is left.  Each device holds its own copy for the life of the process; host code never
 // uses the array's name as an address, only the per-device pointer that
 // hipGetSymbolAddress returns for it (noalloc_scratch()).
 constexpr uint64_t kNoAllocScratchBytes = 64ull << 20;
@@ -628,8 +628,14 @@ csk_status update_impl(csk_sketch* s, const void* src, bool packed, uint64_t n, 
     }
     uint16_t* tok = (uint16_t*)base;
     uint32_t* cnt = (uint32_t*)(base + tok_need);
+    // as many workgroups share a slice as the rest of the scratch has room for partial slices
+    const uint64_t part_at = (need + 255) & ~255ull, slices = (uint64_t)plan.P * kSlice * sizeof(int32_t);
+    const uint64_t room = part_at < kNoAllocScratchBytes ? (kNoAllocScratchBytes - part_at) / slices : 0;
+    uint32_t split = accumulate_split(plan, n, s->d);
+    if (split > room) split = room > 1 ? (uint32_t)room : 1u;
     CSK_HIP(launch_bin((const float*)src, n, mesh, t, plan, tok, cnt, s->M, s->err(), st), "update_noalloc (bin)");
-    CSK_HIP(launch_accumulate(tok, cnt, plan, s->w, s->M, 1, nullptr, st), "update_noalloc (accumulate)");
+    CSK_HIP(launch_accumulate(tok, cnt, plan, s->w, s->M, split, split > 1 ? (int32_t*)(base + part_at) : nullptr, st),
+            "update_noalloc (accumulate)");
     return CSK_OK;
   }
   latch_mesh(s, delta, L, mesh);

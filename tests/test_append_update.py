@@ -160,3 +160,38 @@ def test_direct_update_of_few_cells(d, w):
         assert took[1 << 20] < 1.1 * took[(1 << 20) + 1]
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("n,d,w", [(3_000_000, 5, 1 << 16), (3_000_000, 5, 1 << 14), (4_900_000, 5, 1 << 16), (1_200_001, 9, 40_000)])
+def test_noalloc_update_shares_its_few_slices(n, d, w):
+    # the general form of the update, slices shared by several workgroups as far as the fixed scratch has
+    # room for their parts (none at 4.9 million): the same counters, and with room in about the time of
+    # csk_sketch_update
+    import time
+    import torch
+    pos = _stream(n, 100.0, 5, "mixed")
+    s = csk.Sketch(d, w, 5)
+    try:
+        s.set_update_plan(csk.CSK_UPDATE_BINNED, 0)
+        s.set_update_tiling(csk.CSK_BIN_GENERAL, 0, 0, 0)
+        p = _dev(pos)
+
+        def seconds(call):
+            best = float("inf")
+            for _ in range(5):
+                s.reset()
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                call(p, 0.1, 100.0)
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t)
+            return best
+
+        usual, took = seconds(s.update), seconds(s.update_noalloc)
+        print(f"n={n} d={d} w={w}: update {usual * 1e6:.0f} us, without allocation {took * 1e6:.0f} us", flush=True)
+        Mo, _ = oracle.sketch(pos, d, w, 5, 0.1, 100.0, threads=8)
+        assert np.array_equal(s.counters().cpu().numpy(), Mo)
+        if n <= 3_000_000:
+            assert took < 1.3 * usual
+    finally:
+        s.close()
