@@ -18,10 +18,13 @@ XCD's L2) are measured by bench.py's ceilings and are orders of magnitude slower
 adds at these stream sizes.
 
 Results are cached as JSON, keyed by the device (name, architecture, compute units),
-in ``$CSK_AUTOTUNE_CACHE`` or ``~/.cache/csk_autotune.json``.
+in ``$CSK_AUTOTUNE_CACHE`` or ``~/.cache/csk_autotune.json``.  An entry says which kernels and
+candidates it was chosen among, and one that was chosen among others is not used: a plan pins a
+form, and the form that was the fastest then may keep a sketch from a faster one.
 """
 from __future__ import annotations
 
+import hashlib
 import json
 import math
 import os
@@ -48,6 +51,9 @@ BATCH_BUDGETS = [256, 512, 1024, 2048]
 BATCH_FORMS = [_plan(CSK_UPDATE_BINNED), _plan(CSK_UPDATE_BINNED, 0, CSK_BIN_GENERAL),
                _plan(CSK_UPDATE_BINNED, 0, CSK_BIN_SORT_WORD, 1024, 3, 1)]
 
+KERNELS = 1   # raised when the kernels behind the candidates change
+PLANS = f"{KERNELS}-" + hashlib.sha256(repr((UPDATE_CANDIDATES, BATCH_BUDGETS, BATCH_FORMS)).encode()).hexdigest()[:12]
+
 
 def plan_key(p: dict) -> str:
     return "{mode}:{max_wg}:{form}:{threads}:{rows}:{prefetch}".format(**p)
@@ -70,9 +76,10 @@ def device_key() -> str:
     return f"{p.name}|{getattr(p, 'gcnArchName', '')}|{p.multi_processor_count}"
 
 
-def size_class(w: int, n: int) -> str:
-    """Width and stream size rounded to powers of two."""
-    return f"w{round(math.log2(max(w, 1)))}_n{round(math.log2(max(n, 1)))}"
+def size_class(w: int, n: int, d: int | None = None) -> str:
+    """Width and stream size rounded to powers of two, and the rows: a short stream goes straight to
+    the counters by n d, and the forms of the kernels differ by d."""
+    return f"w{round(math.log2(max(w, 1)))}_n{round(math.log2(max(n, 1)))}" + ("" if d is None else f"_d{d}")
 
 
 def batch_class(d: int, widths, counts) -> str:
@@ -82,7 +89,7 @@ def batch_class(d: int, widths, counts) -> str:
 class Tuner:
     """The cache: {device key: {class: plan}} with plans {"mode", "max_wg", "form",
     "threads", "rows", "prefetch", "ms"} for one sketch and {"wg_budget", "form", ..., "ms"}
-    for a batch."""
+    for a batch, each with the "plans" it was chosen among."""
 
     def __init__(self, path: str | None = None, device: str | None = None):
         self.path = path or default_cache_path()
@@ -98,10 +105,11 @@ class Tuner:
         return self.device
 
     def lookup(self, cls: str):
-        return self.data.get(self._dev(), {}).get(cls)
+        plan = self.data.get(self._dev(), {}).get(cls)
+        return plan if plan is not None and plan.get("plans") == PLANS else None
 
     def record(self, cls: str, plan: dict) -> None:
-        self.data.setdefault(self._dev(), {})[cls] = plan
+        self.data.setdefault(self._dev(), {})[cls] = dict(plan, plans=PLANS)
 
     def save(self) -> None:
         os.makedirs(os.path.dirname(os.path.abspath(self.path)), exist_ok=True)
@@ -138,12 +146,13 @@ class Tuner:
         s.close()
         key = min(times, key=times.get)
         plan = dict(plans[key], ms=times[key], all_ms=times)
-        self.record(size_class(w, n), plan)
+        self.record(size_class(w, n, d), plan)
+        self.record(size_class(w, n), plan)      # the last one tuned, whatever its rows
         return plan
 
     def apply(self, sketch: Sketch, n: int) -> bool:
-        """Set the tuned plan of sketch's (w, n) class if there is one."""
-        plan = self.lookup(size_class(sketch.w, n))
+        """Set the tuned plan of sketch's (w, n, d) class if there is one."""
+        plan = self.lookup(size_class(sketch.w, n, sketch.d))
         if plan is None:
             return False
         set_plan(sketch, plan)

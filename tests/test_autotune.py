@@ -58,3 +58,42 @@ def test_tuner_end_to_end(tmp_path):
     s = csk.Sketch(5, 1 << 20, 9)
     assert autotune.Tuner(str(tmp_path / "tune.json")).apply(s, 300_000)
     s.close()
+
+
+class _Plans:
+    """Stands in for a sketch: the plan set on it."""
+    def __init__(self, d, w):
+        self.d, self.w, self.plan = d, w, None
+
+    def set_update_plan(self, mode, max_wg):
+        self.plan = (mode, max_wg)
+
+    def set_update_tiling(self, *tiling):
+        self.plan += tiling
+
+
+def test_plans_chosen_among_other_kernels_are_not_used(tmp_path):
+    # a cache written before entries said what they were chosen among, and one of other candidates
+    path = str(tmp_path / "tune.json")
+    stale = dict(autotune._plan(csk.CSK_UPDATE_BINNED, 256, csk.CSK_BIN_GENERAL), ms=0.1)
+    cls = autotune.size_class(1 << 20, 1 << 24, 5)
+    with open(path, "w") as f:
+        json.dump({"dev-A": {cls: stale, "w20_n24": stale, "batch_d5_m2_n20": dict(stale, wg_budget=256),
+                             "w16_n16_d5": dict(stale, plans="0-other")}}, f)
+    t = autotune.Tuner(path, device="dev-A")
+    for c in (cls, "w20_n24", "batch_d5_m2_n20", "w16_n16_d5"):
+        assert t.lookup(c) is None
+    s = _Plans(5, 1 << 20)
+    assert not t.apply(s, 1 << 24) and s.plan is None
+    assert t.batch_budget([s, s], [1 << 19, 1 << 19]) == 0 and s.plan is None
+
+
+def test_plans_are_kept_by_their_rows(tmp_path):
+    path = str(tmp_path / "tune.json")
+    t = autotune.Tuner(path, device="dev-A")
+    t.record(autotune.size_class(1 << 16, 70_000, 5), autotune._plan(csk.CSK_UPDATE_DIRECT))
+    t.save()
+    t = autotune.Tuner(path, device="dev-A")
+    five, eight = _Plans(5, 1 << 16), _Plans(8, 1 << 16)
+    assert t.apply(five, 70_000) and five.plan[0] == csk.CSK_UPDATE_DIRECT
+    assert not t.apply(eight, 70_000) and eight.plan is None
