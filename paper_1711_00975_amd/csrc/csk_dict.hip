@@ -156,7 +156,7 @@ struct KeyWalk {
     uint64_t who[4];
     uint32_t x[4][D];
     if constexpr (FP) {   // all the reads of the block before any is used
-      // the filter is at LDS address 0: the byte offset is the address
+      // the filter is at LDS address 0 (the kernel sees to it): the byte offset is the address
 #pragma unroll
       for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -233,6 +233,10 @@ __global__ __launch_bounds__(kDictThreads) void dict_kernel(DictArgs a) {
   bool uf = a.filter != nullptr && !(LIST && (uint64_t)m * a.group <= a.direct);
   const uint32_t nhot = uf ? *a.hot : 0xFFFFFFFFu;
   uf = uf && (FP ? (uint64_t)nhot * a.t.fspan <= kFieldFilterMaxItems : nhot <= kFilterMaxItems);
+  // The walk takes byte offsets into the field-probe filter for LDS addresses.  They are, as long as the
+  // dynamic LDS is all the kernel has; static LDS would come first, and every key would take the exact
+  // test.  (Adding the base costs an instruction per row and key.)
+  if (FP && (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint32_t*)lds4 != 0u) uf = false;
   if (!uf) {
     stage_tables<HashWords<D, HM>::value>(lds4, HM == kHashPacked ? a.t.tabp : a.t.tabi, a.nch);
     if (LIST) {
