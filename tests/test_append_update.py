@@ -195,3 +195,81 @@ def test_noalloc_update_shares_its_few_slices(n, d, w):
             assert took < 1.3 * usual
     finally:
         s.close()
+
+
+# ---- full regions: the append kernel's plan, and a stream that overfills one region of a workgroup
+
+def _append_plan(n, d, w, max_wg, words, kb):
+    """Particles of the fullest workgroup, region capacity, buffer tokens, granule, particles a flush: as
+    plan_append() lays them out (words per table entry, key bytes looked up)."""
+    Pr = (w + 32767) // 32768
+    P = d * Pr
+    fixed = 256 * words * kb * 4 + 4 * (P + 64) + 2 * P + 15 & ~15
+    ring = min(((160 * 1024 - fixed - 16) // (2 * P)) & ~7, 4096)
+    granule = 16 if ring < 48 else 32
+    if granule == 16:
+        assert ring >= 24
+        ring = 24
+    per_iter = 1024.0 * min(1.0, 32768 / w)
+    pp = 8
+    while pp > 2 and pp * per_iter + 2.5 * (pp * per_iter) ** 0.5 + granule - 1 > ring:
+        pp //= 2
+    pieces = -(-n // 1024)
+    nwg = min(pieces, max_wg)
+    per_wg = -(-pieces // nwg) * 1024
+    cap = min(-(-per_wg * min(w, 32768) * 13 // (w * 10)) + 64, per_wg)
+    return per_wg, -(-cap // 32) * 32, ring, granule, 1024 * pp
+
+
+def _cells_of_one_slice(count, d, w, seed, L, G):
+    """Centres of `count` cells whose row-0 buckets lie in the first slice."""
+    T = oracle.hash_tables(seed, d)[0].astype(np.int64)
+    rng = np.random.default_rng(w)
+    got = np.zeros((0, 3), dtype=np.int64)
+    while len(got) < count:
+        c = rng.integers(0, G, (200_000, 3))
+        key = (c[:, 0] * G + c[:, 1]) * G + c[:, 2]
+        h = T[0][key & 255]
+        for b in range(1, 6):
+            h = h ^ T[b][(key >> (8 * b)) & 255]
+        got = np.concatenate([got, c[((h & 0x7FFFFFFF) * w) >> 31 < min(w, 32768)]])
+    return ((got[:count] + 0.5) * (L / G)).astype(np.float32)
+
+
+@pytest.mark.parametrize("d,w,G,words,variant", [
+    (5, 1 << 24, 1000, 4, 0),             # half a piece waits in registers when the region fills
+    (5, 1 << 20, 1000, 4, 0),
+    (8, 3 * (1 << 20) + 5, 768, 8, 1),    # row tables
+    (4, 1 << 20, 1000, 4, 0),
+    (5, 1 << 23, 1000, 4, 0),
+])
+@pytest.mark.parametrize("n", [200_704, 200_003])
+def test_full_regions(d, w, G, words, variant, n):
+    # 96 cells in random order: a wave has each less than twice, so next to none goes to the counters
+    # straight away, and all of row 0 falls into one bin, far above its region
+    print("full regions", d, w, n, flush=True)
+    L, max_wg, seed = 250.0, 2, 5
+    cells = _cells_of_one_slice(96, d, w, seed, L, G)
+    which = np.random.default_rng(n).integers(0, len(cells), n)
+    per_wg, cap, ring, granule, flush = _append_plan(n, d, w, max_wg, words, 4)
+    waves = which[:n // 64 * 64].reshape(-1, 64)
+    like = (waves == waves[:, :1]).sum(1) + (waves == waves[:, 29:30]).sum(1)
+    assert np.mean(like < 8) > 0.9     # these waves append everything
+    wait = region = 0                  # the fullest bin: what its buffer takes between two flushes
+    for _ in range(per_wg // flush):
+        wait = min(ring, wait + int(0.9 * flush))
+        region += wait // granule * granule
+        wait %= granule
+    assert region > 1.1 * cap
+    s = csk.Sketch(d, w, seed, variant)
+    try:
+        s.set_update_plan(csk.CSK_UPDATE_BINNED, max_wg)
+        pos = cells[which]
+        s.update(_dev(pos), L / G, L)
+        s.update(_dev(pos[: n // 2]), L / G, L)
+        M = s.counters().cpu().numpy()
+    finally:
+        s.close()
+    Mo, _ = oracle.sketch(pos, d, w, seed, L / G, L, variant=variant, threads=8)
+    M2, _ = oracle.sketch(pos[: n // 2], d, w, seed, L / G, L, variant=variant, threads=8)
+    assert np.array_equal(M, Mo + M2)
