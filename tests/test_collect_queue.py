@@ -247,3 +247,45 @@ def test_particles_outside_of_short_streams_are_latched_in_passing(n):
         assert skipped == n // 2 and np.array_equal(s.counters().cpu().numpy(), M)
     finally:
         s.close()
+
+
+def _line(w):
+    """The most particles that the short form of the candidate pass takes (d <= 8)."""
+    return min(1 << 20, (1 << 19) + w // 32)
+
+
+@pytest.mark.parametrize("d,w,group,variant", [(1, 1 << 14, 1, 0), (5, 3 * 9973, 1, 1), (8, 1 << 15, 1, 0),
+                                               (8, 1 << 15, 1, 1), (3, 1 << 24, 1, 0), (5, 1 << 25, 1, 0),
+                                               (5, 1 << 14, 8, 0), (5, 30_011, 1000, 1), (2, 5000, 64, 0)])
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("packed", [False, True])
+def test_both_sides_of_the_short_rule_for_every_stream(d, w, group, variant, over, packed):
+    # on one side one thread tests a particle against every row's counter; on the other the filter and the
+    # queues, or for grouped items the general kernel
+    print("short rule", d, w, group, variant, over, packed, flush=True)
+    n, seed = _line(w) + over, 7
+    rng = np.random.default_rng(n + d)
+    pos = _stream(n, n + d)
+    if not packed:
+        pos[rng.choice(n, 20, replace=False), 2] = np.float32(np.nan)   # outside the domain
+    words = oracle.pack(pos, L)
+    keys = oracle.keys_packed(words, DELTA, L) if packed else oracle.keys(pos, DELTA, L)
+    keys = keys[keys != np.uint64(2**64 - 1)] // np.uint64(group)
+    M, T = _counters(d, w, 0.05 if w <= 1 << 20 else 0.001, variant, d * w), oracle.hash_tables(seed, d)
+    s = csk.Sketch(d, w, seed, variant, 1 << 21, group)
+    try:
+        s.set_counters(_dev(M))
+        for theta in (THETA, 600, -5):
+            if theta < 0 and group == 1 and d != 5:
+                continue
+            s.clear_candidates()
+            if packed:
+                s.collect_packed(_dev(words.view(np.int64)), DELTA, L, theta)
+            else:
+                s.collect(_dev(pos), DELTA, L, theta)
+                with pytest.raises(csk.CskError) as ei:
+                    s.check()
+                assert ei.value.code == csk.CSK_E_DOMAIN
+            _check(s, _want(M, T, keys, theta, variant))
+    finally:
+        s.close()
