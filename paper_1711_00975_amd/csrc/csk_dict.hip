@@ -220,6 +220,14 @@ __device__ __forceinline__ void direct_test(const DictArgs& a, const uint32_t* t
   if (rows_pass<D>(bk, ng, need, nullptr, a.M, a.t.w, a.theta)) set_insert(a.cand, key, a.err);
 }
 
+// How many of the `workers` (waves, quarter workgroups) take one of m super-items together, 256 keys in turn:
+// few large ones would leave the others idle (d = 5, w = 2^18: 10 of 30000 keys, read directly: 340 us with a
+// quarter workgroup each, 31 us so; 3 of 10^6 through the filter: 2.1 ms with a wave each, 42 us so).
+__device__ __forceinline__ uint32_t list_share(uint32_t workers, uint32_t m, uint32_t group) {
+  const uint32_t blocks = group / 256u + 1u;
+  return m != 0 && m < workers ? min(workers / m, blocks) : 1u;
+}
+
 template <int D, int HM, bool FP, bool LIST>
 __global__ __launch_bounds__(kDictThreads) void dict_kernel(DictArgs a) {
   using W = KeyWalk<D, HM, FP>;
@@ -240,12 +248,15 @@ __global__ __launch_bounds__(kDictThreads) void dict_kernel(DictArgs a) {
   if (!uf) {
     stage_tables<HashWords<D, HM>::value>(lds4, HM == kHashPacked ? a.t.tabp : a.t.tabi, a.nch);
     if (LIST) {
-      // a quarter of a workgroup per super-item
+      // a quarter of a workgroup per super-item, or several where there are few of them
       const uint32_t part = blockIdx.x * 4u + (threadIdx.x >> 8), parts = gridDim.x * 4u;
-      for (uint32_t i = part; i < m; i += parts) {
+      const uint32_t share = list_share(parts, m, a.group);
+      for (uint32_t u = part; u < m * share; u += parts) {
+        const uint32_t i = share == 1u ? u : u / share;
         const uint64_t lo = a.list[i] * a.group;
         const uint64_t hi = lo + a.group < a.nkeys ? lo + a.group : a.nkeys;
-        for (uint64_t key = lo + (threadIdx.x & 255u); key < hi; key += 256) direct_test<D, HM>(a, lds4, key);
+        for (uint64_t key = lo + 256u * (u - i * share) + (threadIdx.x & 255u); key < hi; key += 256u * share)
+          direct_test<D, HM>(a, lds4, key);
       }
     } else {
       const uint64_t stride = (uint64_t)gridDim.x * kDictThreads;
@@ -264,10 +275,12 @@ __global__ __launch_bounds__(kDictThreads) void dict_kernel(DictArgs a) {
   // neighbours in the stream of work on different CUs
   const uint32_t w0 = wave * gridDim.x + blockIdx.x, nw = gridDim.x * kWaves;
   if (LIST) {
-    for (uint32_t i = w0; i < m; i += nw) {
+    const uint32_t share = list_share(nw, m, a.group);   // waves per super-item
+    for (uint32_t u = w0; u < m * share; u += nw) {
+      const uint32_t i = share == 1u ? u : u / share;
       const uint64_t lo = a.list[i] * a.group;
       const uint64_t hi = lo + a.group < a.nkeys ? lo + a.group : a.nkeys;
-      for (uint64_t base = lo & ~255ull; base < hi; base += 256) {
+      for (uint64_t base = (lo & ~255ull) + 256u * (u - i * share); base < hi; base += 256u * share) {
         uint32_t q[W::TW], f[W::NR];
         walk.upper(base, 1, q);
         W::split(q, f);

@@ -108,3 +108,56 @@ def test_children(d, w, variant, share, group, side):
     finally:
         coarse.close()
         fine.close()
+
+
+@pytest.mark.parametrize("d,w,variant", [(5, 1 << 18, 0), (5, 70_001, 0), (3, 1 << 18, 0), (8, 1 << 18, 1)])
+@pytest.mark.parametrize("items,group,like", [(1, 300_000, 300), (10, 30_000, 300), (7, 999, 7), (3, 1_000_000, 3000),
+                                              (100, 40_000, 4000)])
+def test_children_of_few_large_super_items(d, w, variant, items, group, like):
+    # as many children in few super-items as in many, directly and through the filter: the same keys as by
+    # the oracle, and not much slower than the `like` super-items of 1000
+    import time
+    import torch
+    G, L, theta, seed = 1000, 100.0, 600, 5
+    rng = np.random.default_rng(items * group + d)
+    M = rng.integers(0, 599, (d, w))
+    hot = rng.random((d, w)) < 0.02
+    M = np.where(hot, rng.integers(600, 2000, (d, w)), M)
+    M = (M if variant else M * rng.choice([-1, 1], (d, w))).astype(np.int32)
+    fine = csk.Sketch(d, w, seed, variant, 1 << 21)
+    try:
+        def children(n, of):
+            """Time of the children of n random super-items of so many keys, and the super-items."""
+            coarse = csk.Sketch(d, w, 9, variant, 1 << 16, group=of)
+            try:
+                at = rng.choice(G ** 3 // of, n, replace=False).astype(np.int64) * of
+                c = np.stack([at // G ** 2, at // G % G, at % G], 1)
+                coarse.collect(_dev(((c + 0.5) * (L / G)).astype(np.float32)), L / G, L)
+                best = float("inf")
+                for _ in range(4):
+                    fine.clear_candidates()
+                    torch.cuda.synchronize()
+                    t = time.perf_counter()
+                    fine.collect_children(coarse, theta)
+                    torch.cuda.synchronize()
+                    best = min(best, time.perf_counter() - t)
+                return best * 1e6, at
+            finally:
+                coarse.close()
+
+        fine.update(_dev(np.zeros((1, 3), dtype=np.float32)), L / G, L)     # latches the mesh
+        fine.set_counters(_dev(M))
+        usual, _ = children(like, 1000)
+        took, at = children(items, group)
+        print(f"children of {like} x 1000: {usual:.0f} us, of {items} x {group}: {took:.0f} us", flush=True)
+        keys = (at[:, None] + np.arange(group)).ravel().astype(np.uint64)
+        keys = keys[keys < G ** 3]
+        est = oracle.estimate(M, oracle.hash_tables(seed, d), keys, variant)
+        keys, est = keys[est >= theta], est[est >= theta]
+        order = np.lexsort((keys, -est.astype(np.int64)))
+        kg, eg, _ = fine.topk(len(keys) + 1)
+        assert np.array_equal(kg.cpu().numpy().view(np.uint64), keys[order])
+        assert np.array_equal(eg.cpu().numpy(), est[order])
+        assert took < 2 * usual + 50
+    finally:
+        fine.close()
