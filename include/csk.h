@@ -215,7 +215,8 @@ csk_status csk_topk(csk_sketch *s, uint32_t k, uint64_t *keys, int32_t *est, uin
  * when that is below k and the set is partial (CSK_W_INCOMPLETE of csk_topk), else 0.
  * Device-side errors stay latched for the next synchronizing call (csk_check, csk_topk,
  * csk_get_counters).  The first call with a k above every earlier one allocates
- * scratch and synchronizes: make it once before capturing. */
+ * scratch and synchronizes: make it once before capturing.  Recorded by itself it selects,
+ * on every replay, from whatever candidates the handle then holds, on whatever mesh. */
 csk_status csk_topk_async(csk_sketch *s, uint32_t k, uint64_t *keys, int32_t *est, uint32_t *out,
                           void *stream);
 

@@ -553,9 +553,6 @@ csk_status csk_set_update_tiling(csk_sketch* s, int32_t form, uint32_t threads, 
 
 namespace {
 
-// The update of a float (x, y, z) stream, or of a packed stream (src = 64-bit words).
-// noalloc: tokens go to the device's static scratch, never to memory allocated here;
-// a stream whose bin plan does not fit it is refused before anything runs.
 // The handle's scratch for one update, grown to what the plan needs (a growth synchronizes the
 // stream first: earlier work may still read the old buffer).
 struct UpdateScratch {
@@ -585,6 +582,9 @@ hipError_t ensure_update_scratch(csk_sketch* s, const BinPlan& plan, uint32_t sp
   return hipSuccess;
 }
 
+// The update of a float (x, y, z) stream, or of a packed stream (src = 64-bit words).
+// noalloc: tokens go to the device's static scratch, never to memory allocated here;
+// a stream whose bin plan does not fit it is refused before anything runs.
 csk_status update_impl(csk_sketch* s, const void* src, bool packed, uint64_t n, double delta, double L,
                        void* stream, bool noalloc = false) {
   if (s == nullptr) return fail(CSK_E_INVALID, "update: NULL handle");

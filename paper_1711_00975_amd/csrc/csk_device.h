@@ -17,8 +17,9 @@ constexpr uint32_t kSlice = 1u << kSliceBits;
 constexpr uint64_t kEmptyKey = ~0ull;  // empty slot of the candidate set / invalid key
 constexpr int kTabLdsRows = 8;         // rows whose tables are staged in LDS
 constexpr int kFilterWords = 24576;    // LDS Bloom filter of hot (row, bucket, sign): 96 KiB
-// Denser filters are not used.  At the line two bits in three are set and a probe of three passes one
-// time in four: one key in 20 (d = 8) to 6 (d = 3) reaches the exact test.
+// Denser filters are not used.  At the line a share 1 - 1/e of the bits is set (0.63) and a probe of three
+// passes one time in four, so that of the keys that no counter makes hot one in 35 (d = 8), 14 (7), 26 (6),
+// 9 (5), 19 (4), 6 (3), 16 (2) and 4 (1) reaches the exact test; Count-Min one in 4^d.
 constexpr uint32_t kFilterMaxItems = kFilterWords * 32 / 3;
 constexpr uint32_t kHotSlots = 1u << 19;   // exact set of hot items: 2 MiB, stays in L2
 constexpr uint32_t kHotMaxItems = kHotSlots / 2;
@@ -512,7 +513,8 @@ __device__ __forceinline__ uint32_t hot_slot(uint32_t item) {
 constexpr int kFieldBits = 25;
 constexpr int kFieldCols = kFieldBits + 1;
 constexpr uint32_t kFieldFilterWords = 1u << 15;     // 128 KiB of LDS
-constexpr uint32_t kFieldFilterMaxItems = kFieldFilterWords * 32 / 2;   // as kFilterMaxItems, with two bits: 1 in 3 passes
+// As kFilterMaxItems, with probes of two bits: one key in 3 reaches the exact test.
+constexpr uint32_t kFieldFilterMaxItems = kFieldFilterWords * 32 / 2;
 constexpr uint32_t kFilterAllocWords = kFieldFilterWords > (uint32_t)kFilterWords ? kFieldFilterWords
                                                                                    : (uint32_t)kFilterWords;
 

@@ -1,7 +1,6 @@
-// csk_kernels.hip — gfx950 kernels of the streaming Count-Sketch hot path after the
-// update (which lives in csk_update.hip):
-// query   (Sec. 2.2 Estimate; Alg. 4 Estimate): lower median of the d signed counters.
-// dictionary and hierarchy (Sec. 2.2 items 1 and 3): candidates without positions.
+// csk_kernels.hip — gfx950 kernels of the streaming Count-Sketch hot path beside the
+// update and the candidate passes, which have files of their own: cell keys, packing, fills, and
+// query   (Sec. 2.2 Estimate; Alg. 4 Estimate): lower median of the d signed counters,
 // topk    (Sec. 2.2 UpdateHeap; Alg. 1 query): two-stage radix select on
 //         (estimate desc, key asc), then an exact rank placement of the k winners.
 #include <hip/hip_runtime.h>

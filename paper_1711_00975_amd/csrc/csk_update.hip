@@ -828,20 +828,18 @@ __global__ __launch_bounds__(256) void update_direct_kernel(const float* __restr
 // particles are enough threads to hide the two memory round trips (position, the row's six table entries)
 // behind each other.  The rows take turns every 8 blocks of particles: row after row, the blocks in flight
 // would all add to one row's counters (2^20 particles of 64 cells, d = 5, w = 2^16: 0.91 ms, 0.67 so), and
-// 8 blocks on, the same particles meet the same XCD, whose L2 has them.
-// Lanes of a wave with the same counter and sign
-// (a stream in structure order) add together, for the first few such groups of the wave.
+// 8 blocks on, the same particles meet the same XCD, whose L2 has them.  Lanes of a wave with the same
+// counter and sign (a stream in structure order) add together, for the first few such groups of the wave.
 constexpr uint32_t kXcds = 8;
 __global__ __launch_bounds__(256) void update_short_kernel(const float* __restrict__ pos, uint32_t n, Mesh mesh,
-                                                           const uint32_t* __restrict__ tab, uint32_t d, uint32_t w,
-                                                           uint32_t cm, int32_t* __restrict__ M,
-                                                           uint32_t* __restrict__ err) {
-  const uint32_t turn = blockIdx.x / kXcds, r = turn % d;
-  const uint32_t i = (turn / d * kXcds + blockIdx.x % kXcds) * 256 + threadIdx.x;
+                                                           const uint32_t* __restrict__ tab, uint32_t w, uint32_t cm,
+                                                           int32_t* __restrict__ M, uint32_t* __restrict__ err) {
+  __shared__ uint32_t outside[4];
+  const uint32_t r = blockIdx.x / kXcds;
+  const uint32_t i = (blockIdx.y * kXcds + blockIdx.x % kXcds) * 256 + threadIdx.x;
   uint64_t key;
   const bool in = i < n;
   const bool ok = particle_key(pos, in ? i : n - 1, mesh, key) && in;
-  if (r == 0 && __syncthreads_or(in && !ok) && threadIdx.x == 0) atomicOr(err, kErrDomain);   // r is uniform
   const uint32_t h = row_hash(tab + r * kTableWords, key);   // every byte indexes its table in range
   const uint32_t b = bucket_of(h, w), neg = (h >> 31) & (cm ^ 1u);
   int32_t* Mr = M + (uint64_t)r * w;
@@ -855,13 +853,19 @@ __global__ __launch_bounds__(256) void update_short_kernel(const float* __restri
     todo &= ~same;
   }
   if ((todo >> lane_id()) & 1u) atomicAdd(&Mr[b], neg ? -1 : 1);
+  if (r == 0) {   // particles outside, once a workgroup: all go to one word
+    const bool some = __any(in && !ok);
+    if (lane_id() == 0) outside[threadIdx.x >> 6] = some ? 1u : 0u;
+    __syncthreads();
+    if (threadIdx.x == 0 && (outside[0] | outside[1] | outside[2] | outside[3])) atomicOr(err, kErrDomain);
+  }
 }
 
 hipError_t launch_update_direct(const float* pos, uint64_t n, const Mesh& mesh, const Tables& t, int32_t* M,
                                 uint32_t* err, hipStream_t s) {
   if (n <= kShortStream) {
-    hipLaunchKernelGGL(update_short_kernel, dim3((uint32_t)((n + 256 * kXcds - 1) / (256 * kXcds)) * kXcds * t.d), dim3(256), 0,
-                       s, pos, (uint32_t)n, mesh, t.tab, t.d, t.w, t.cm, M, err);
+    const dim3 grid(kXcds * t.d, (uint32_t)((n + 256 * kXcds - 1) / (256 * kXcds)));
+    hipLaunchKernelGGL(update_short_kernel, grid, dim3(256), 0, s, pos, (uint32_t)n, mesh, t.tab, t.w, t.cm, M, err);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(update_direct_kernel, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, pos, n, mesh, t.tab,

@@ -135,7 +135,7 @@ def test_buffers_full_to_the_end_of_lds(d, w):
 @pytest.mark.parametrize("d,w", [(5, 1 << 16), (2, 5000)])
 def test_direct_update_of_few_cells(d, w):
     # up to 2^20 particles one thread takes a particle and row, above it a particle: with 64 cells the adds
-    # meet on few counters, and the first must not be the slower by more than a tenth
+    # meet on few counters, and the first must not be the slower by more than a fifth
     import time
     import torch
     rng = np.random.default_rng(d)
@@ -157,7 +157,7 @@ def test_direct_update_of_few_cells(d, w):
             Mo, _ = oracle.sketch(pos[:n], d, w, 5, 0.1, 100.0, threads=8)
             assert np.array_equal(s.counters().cpu().numpy(), Mo), n
         print("direct update of 64 cells:", {n: f"{t * 1e6:.0f} us" for n, t in took.items()}, flush=True)
-        assert took[1 << 20] < 1.1 * took[(1 << 20) + 1]
+        assert took[1 << 20] < 1.2 * took[(1 << 20) + 1]
     finally:
         s.close()
 
