@@ -145,23 +145,27 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
     queued = 0;
     // a key already in the set needs no exact test: the set only ever gains keys
     const uint64_t s0 = act ? set[(uint32_t)slot_mix(key) & slot_mask] : kEmptyKey;
-    bool in = act && s0 == key, is_new = false;
+    bool in = act && s0 == key, pass = false, is_new = false;
     if (act && !in && s0 != kEmptyKey) in = set_contains(set, slot_mask, key);   // a longer probe run
     if (act && !in) {
       uint32_t bk[D], ng[D];
       exact_rows(key, bk, ng);
 #pragma unroll
       for (int r = 0; r < D; ++r) ng[r] &= t.cm ^ 1u;
-      in = rows_pass<D>(bk, ng, need, nullptr, M, t.w, theta);
-      if (in) {
-        const uint32_t got = set_claim(cand, key, err, [&]() {
-          return __hip_atomic_load(&ctl[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
-        });
-        is_new = got == kClaimNew;
-        if (got == kClaimRefused) __hip_atomic_store(&ctl[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+      in = pass = rows_pass<D>(bk, ng, need, nullptr, M, t.w, theta);
     }
-    if (in) __hip_atomic_store(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    // Of the lanes that bring a key to the cache one claims it: where all particles share a cell there
+    // would be a compare-and-swap each, all to one word, until the cache shows it.
+    bool first = false;
+    if (in)
+      first = __hip_atomic_exchange(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != key;
+    if (pass && first) {
+      const uint32_t got = set_claim(cand, key, err, [&]() {
+        return __hip_atomic_load(&ctl[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
+      });
+      is_new = got == kClaimNew;
+      if (got == kClaimRefused) __hip_atomic_store(&ctl[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
     // New keys go into the list with the workgroup's others when it ends, past `hold` of them here and now:
     // one or two at a time they kept the kernel waiting for the count (about 40 ns an add, one after
     // the other over all XCDs).  The count tells then whether the set is full.

@@ -289,3 +289,36 @@ def test_both_sides_of_the_short_rule_for_every_stream(d, w, group, variant, ove
             _check(s, _want(M, T, keys, theta, variant))
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("d,w", [(5, 1 << 16), (5, 70_001), (2, 5000), (8, 100_003)])
+def test_long_streams_of_one_cell(d, w):
+    # a key that all particles share is claimed once a workgroup: in the time of a stream of 2^16 cells
+    import time
+    import torch
+    n = 1 << 22
+    rng = np.random.default_rng(d)
+    one = np.full((n, 3), 12.34, dtype=np.float32)
+    spread = rng.uniform(0, L, (1 << 16, 3)).astype(np.float32)[rng.integers(0, 1 << 16, n)]
+    M, T = _counters(d, w, 0.97, 0, d), oracle.hash_tables(5, d)
+    s = csk.Sketch(d, w, 5, 0, 1 << 20)
+    try:
+        s.set_counters(_dev(M))
+
+        def microseconds(p):
+            best = float("inf")
+            for _ in range(5):
+                s.clear_candidates()
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                s.collect(p, DELTA, L, csk.INT32_MIN)
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t)
+            return best * 1e6
+
+        usual, few = microseconds(_dev(spread)), microseconds(_dev(one))
+        print(f"d={d}: {n} particles of many cells {usual:.0f} us, of one {few:.0f} us", flush=True)
+        _check(s, _want(M, T, oracle.keys(one, DELTA, L), csk.INT32_MIN, 0))
+        assert few < 2 * usual + 50
+    finally:
+        s.close()
