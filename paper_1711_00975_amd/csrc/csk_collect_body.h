@@ -154,12 +154,10 @@ __device__ __forceinline__ void collect2_body(const CollectDesc* __restrict__ cp
       for (int r = 0; r < D; ++r) ng[r] &= t.cm ^ 1u;
       in = pass = rows_pass<D>(bk, ng, need, nullptr, M, t.w, theta);
     }
+    if (in && !pass) __hip_atomic_store(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     // Of the lanes that bring a key to the cache one claims it: where all particles share a cell there
     // would be a compare-and-swap each, all to one word, until the cache shows it.
-    bool first = false;
-    if (in)
-      first = __hip_atomic_exchange(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != key;
-    if (pass && first) {
+    if (pass && __hip_atomic_exchange(&cache[cache_slot(key)], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != key) {
       const uint32_t got = set_claim(cand, key, err, [&]() {
         return __hip_atomic_load(&ctl[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
       });
