@@ -27,8 +27,8 @@ BYTES_PER_PARTICLE = 12         # algorithmic: each float32 position read once
 # rocprofv3 FETCH_SIZE (x2.000) and WRITE_SIZE (x1.000) scaled by a 1 GiB device copy
 # (profiles/update_kernels_plummer_2e30.md).  Reported only while the kernel sources hash
 # to what was profiled; any change to them makes `traffic` null until measured again.
-TRAFFIC = {"bytes": 35_601_478_656, "particles": 1 << 30,
-           "sources_sha256": "ce602ba89bf4e073cbfffc5161b32136d5407f18515e7fb4771d5392c8fdd6da"}
+TRAFFIC = {"bytes": 35_603_609_632, "particles": 1 << 30,
+           "sources_sha256": "9c2577e8bf245c7a1c7378c2f1f6360ef73dfe2d4a1f7a16712022026f721f09"}
 TRAFFIC_SOURCES = ["csk_update.hip", "csk_append.hip", "csk_append_body.h", "csk_kernel_util.h", "csk_device.h",
                    "csk_internal.h"]
 
